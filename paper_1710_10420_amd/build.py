@@ -21,7 +21,17 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libprs.so")
 
-SOURCES = ["prs_ensemble.hip", "prs_kernels.hip", "prs_kernels_f64.hip", "prs_api.cpp"]
+# (source, object, definitions), the longest compilations first
+SOURCES = [("prs_fwd3d.hip", "prs_fwd3d_f32", ["-DPRS_REAL=float"]),
+           ("prs_fwd2d.hip", "prs_fwd2d_f32", ["-DPRS_REAL=float"]),
+           ("prs_adjoint.hip", "prs_adjoint_f32", ["-DPRS_REAL=float"]),
+           ("prs_fwd2d.hip", "prs_fwd2d_f64", ["-DPRS_REAL=double"]),
+           ("prs_fwd3d.hip", "prs_fwd3d_f64", ["-DPRS_REAL=double"]),
+           ("prs_adjoint.hip", "prs_adjoint_f64", ["-DPRS_REAL=double"]),
+           ("prs_ensemble.hip", "prs_ensemble", []),
+           ("prs_kernels.hip", "prs_kernels", []),
+           ("prs_kernels_f64.hip", "prs_kernels_f64", []),
+           ("prs_api.cpp", "prs_api", [])]
 ARCH = os.environ.get("PRS_OFFLOAD_ARCH", "gfx950")
 
 
@@ -63,17 +73,15 @@ def build(verbose=False):
     tmpdir = os.path.join(PKG, "_build")
     os.makedirs(tmpdir, exist_ok=True)
     procs = []
-    for src in SOURCES:                       # the sources compile in parallel
-        obj = os.path.join(tmpdir, os.path.splitext(src)[0] + ".o")
-        cmd = [hipcc(), "--offload-arch=" + ARCH, "-c", os.path.join(CSRC, src), "-o", obj] + flags()
-        if src.endswith(".cpp"):
-            cmd = [hipcc(), "-x", "hip", "--offload-arch=" + ARCH, "-c",
-                   os.path.join(CSRC, src), "-o", obj] + flags()
+    for src, name, defs in SOURCES:           # the units compile in parallel
+        obj = os.path.join(tmpdir, name + ".o")
+        lang = ["-x", "hip"] if src.endswith(".cpp") else []
+        cmd = [hipcc()] + lang + ["--offload-arch=" + ARCH, "-c", os.path.join(CSRC, src), "-o", obj] + flags() + defs
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append((src, subprocess.Popen(cmd)))
+        procs.append((name, subprocess.Popen(cmd)))
         objs.append(obj)
-    failed = [src for src, pr in procs if pr.wait() != 0]
+    failed = [name for name, pr in procs if pr.wait() != 0]
     if failed:
         raise RuntimeError("compilation failed: " + ", ".join(failed))
     tmp = LIB + ".tmp%d" % os.getpid()

@@ -48,7 +48,7 @@ prs_status hip_fail(hipError_t e, const char* what)
     } while (0)
 
 constexpr size_t kAlign = 256;
-constexpr int64_t kRecCap = 1024;   // device records buffered before a flush
+constexpr int64_t kRecCap = 1024;   // records buffered before a flush
 constexpr int64_t kMinRows = 8;     // smallest marching tile the workspace allows
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -190,9 +190,9 @@ struct prs_ctx {
     int cur;
     void* pi;
     WavePartial* partials;
-    int64_t partial_cap;
-    prs_stats* drec;
-    prs_stats* hrec;   // pinned staging buffer
+    int64_t partial_cap;     // most wave tiles of a pass
+    int64_t partial_total;   // entries of the partial buffer: the partials of several records
+    prs_stats* hrec;   // pinned record buffer, which the reductions write
     void* pi_alt;      // second phi_dot buffer (workspace) for multi-step passes
     Tiling adj_til;    // tiling of the reverse-sweep kernel
     int32_t adj_tblock;   // steps per reverse pass
@@ -285,12 +285,52 @@ double area_scale(const prs_params& p)
     return std::pow(p.dx, p.ndim - 1) / ((double)sites_of(p) * std::pow(p.dx, p.ndim));
 }
 
+// Records whose wave partials are written but not yet reduced.  Each keeps
+// its own part of the partial buffer, so that one launch reduces up to
+// kFinBatch of them: reduced one by one, between the passes, a record cost
+// 5 to 8 us of launch and latency (5 % of a 2048^2 run with a record every
+// 64 steps).
+struct RecordQueue {
+    WavePartial* base;
+    int64_t cap;               // entries of the buffer
+    double area_scale;
+    FinJob job[kFinBatch];
+    int n = 0;
+    int64_t used = 0;
+
+    hipError_t reduce(hipStream_t s)
+    {
+        if (n == 0) return hipSuccess;
+        const hipError_t e = launch_finalize(job, n, area_scale, s);
+        n = 0;
+        used = 0;
+        return e;
+    }
+    // Partials of the next record, whose pass has `count` wave tiles (<= cap).
+    hipError_t add(int64_t count, prs_stats* rec, int64_t step, double eta, hipStream_t s, WavePartial** parts)
+    {
+        if (n == kFinBatch || used + count > cap) {
+            const hipError_t e = reduce(s);
+            if (e != hipSuccess) return e;
+        }
+        *parts = base + used;
+        job[n++] = FinJob{base + used, count, rec, step, eta};
+        used += count;
+        return hipSuccess;
+    }
+};
+
+// The partial buffer of a run holds the partials of up to kFinBatch records
+// as far as they take at most 2 MiB (larger lattices' passes need few of the
+// capacity's entries and still get several records in).
+int64_t partial_entries(int64_t cap)
+{
+    return std::max<int64_t>(cap, std::min<int64_t>(kFinBatch * cap, (int64_t)((2u << 20) / sizeof(WavePartial))));
+}
+
 prs_status flush(prs_ctx* c, int64_t count, prs_stats* dst)
 {
     if (count == 0) return PRS_OK;
-    HIP_TRY(hipMemcpyAsync(c->hrec, c->drec, (size_t)count * sizeof(prs_stats),
-                           hipMemcpyDeviceToHost, c->stream),
-            "record copy");
     HIP_TRY(hipStreamSynchronize(c->stream), "stream synchronize");
     std::memcpy(dst, c->hrec, (size_t)count * sizeof(prs_stats));
     return PRS_OK;
@@ -304,8 +344,7 @@ size_t prs_workspace_bytes(const prs_params* p)
 {
     if (validate(p) != PRS_OK) return 0;
     const Geometry g = geometry_of(*p);
-    size_t b = align_up((size_t)partial_capacity(g) * sizeof(WavePartial)) +
-               align_up((size_t)kRecCap * sizeof(prs_stats));
+    size_t b = align_up((size_t)partial_entries(partial_capacity(g)) * sizeof(WavePartial));
     b += align_up(field_bytes(*p));   // second phi_dot for multi-step passes
     return b;
 }
@@ -338,14 +377,12 @@ prs_status prs_init(const prs_params* p, void* phi_a, void* phi_b, void* dphi, v
     c->cur = 0;
     c->pi = dphi;
     c->partial_cap = partial_capacity(c->geo);
+    c->partial_total = partial_entries(c->partial_cap);
     c->partials = static_cast<WavePartial*>(workspace);
-    c->drec = reinterpret_cast<prs_stats*>(
-        static_cast<char*>(workspace) + align_up((size_t)c->partial_cap * sizeof(WavePartial)));
-    c->pi_alt = nullptr;
     c->adj_til = c->til;
     c->adj_tblock = p->ndim == 2 ? 4 : 1;
     c->adj_scheme = p->ndim == 2 ? PRS_ADJ_FUSED : PRS_ADJ_STORED;
-    c->pi_alt = reinterpret_cast<char*>(c->drec) + align_up((size_t)kRecCap * sizeof(prs_stats));
+    c->pi_alt = static_cast<char*>(workspace) + align_up((size_t)c->partial_total * sizeof(WavePartial));
     c->tblock = p->ndim == 2 ? 2 : 1;
     c->stream = static_cast<hipStream_t>(hip_stream);
     c->step = 0;
@@ -381,9 +418,9 @@ prs_status prs_step_n(prs_ctx* c, int64_t nsteps, prs_stats* series, int64_t cap
         prs_status st = check_stable_until(c->p, c->V0, c->step + nsteps - 1);
         if (st != PRS_OK) return st;
     }
-    const double ascale = area_scale(c->p);
     const TileCounts tc = tile_counts(c->geo, c->til);
     const int64_t K = c->p.diag_every;
+    RecordQueue queue{c->partials, c->partial_total, area_scale(c->p)};
 
     const int T = tb_supported(c->geo) ? c->tblock : 1;
     const std::vector<uint8_t> plan = plan_passes(c->geo, c->til, c->partial_cap, c->step, nsteps, T, want ? K : 0);
@@ -419,9 +456,13 @@ prs_status prs_step_n(prs_ctx* c, int64_t nsteps, prs_stats* series, int64_t cap
             }
             if (dom) ++c->lt_count[spans];
         }
-        WavePartial* parts = diag ? c->partials : nullptr;
+        WavePartial* parts = nullptr;
+        if (diag) {
+            const int64_t ntiles = L > 1 ? tb_tiles(c->geo, c->til, L) : tc.ntiles;
+            HIP_TRY(queue.add(ntiles, c->hrec + pending, n, c->p.eta0 + (double)n * c->p.deta, c->stream, &parts),
+                    "finalize launch");
+        }
         const DiagCoef dc = diag_coef(c, n);
-        int64_t ntiles = tc.ntiles;
         if (L > 1) {
             StepCoef64 k[kMaxPassSteps];
             for (int i = 0; i < L; ++i) k[i] = coef_for(c, n + i);
@@ -429,27 +470,23 @@ prs_status prs_step_n(prs_ctx* c, int64_t nsteps, prs_stats* series, int64_t cap
                                 parts, dc, c->stream),
                     "multi-step kernel launch");
             std::swap(pi_cur, pi_oth);
-            ntiles = tb_tiles(c->geo, c->til, L);
         } else {
             HIP_TRY(launch_step(c->geo, c->til, c->phi[c->cur], c->phi[c->cur ^ 1], pi_cur, pi_cur,
                                 coef_for(c, n), true, diag, parts, dc, c->stream),
                     "step kernel launch");
         }
-        if (diag) {
-            HIP_TRY(launch_finalize(c->partials, ntiles, c->drec + pending, n,
-                                    c->p.eta0 + (double)n * c->p.deta, ascale, c->stream),
-                    "finalize launch");
-            if (++pending == kRecCap) {
-                prs_status st = flush(c, pending, series + written);
-                if (st != PRS_OK) return st;
-                written += pending;
-                pending = 0;
-            }
+        if (diag && ++pending == kRecCap) {
+            HIP_TRY(queue.reduce(c->stream), "finalize launch");
+            prs_status st = flush(c, pending, series + written);
+            if (st != PRS_OK) return st;
+            written += pending;
+            pending = 0;
         }
         c->cur ^= 1;
         c->step += L;
     }
     if (want) {
+        HIP_TRY(queue.reduce(c->stream), "finalize launch");
         prs_status st = flush(c, pending, series + written);
         if (st != PRS_OK) return st;
         written += pending;
@@ -542,9 +579,8 @@ prs_status prs_wall_stats(prs_ctx* c, prs_stats* out)
     HIP_TRY(launch_step(c->geo, c->til, c->phi[c->cur], nullptr, c->pi, nullptr, coef_for(c, n), false, true,
                         c->partials, diag_coef(c, n), c->stream),
             "diagnostics kernel launch");
-    HIP_TRY(launch_finalize(c->partials, tc.ntiles, c->drec, n, c->p.eta0 + (double)n * c->p.deta,
-                            area_scale(c->p), c->stream),
-            "finalize launch");
+    const FinJob job{c->partials, tc.ntiles, c->hrec, n, c->p.eta0 + (double)n * c->p.deta};
+    HIP_TRY(launch_finalize(&job, 1, area_scale(c->p), c->stream), "finalize launch");
     return flush(c, 1, out);
 }
 
@@ -653,9 +689,8 @@ prs_status slab_pass(const prs_params* p, int64_t n0, int32_t steps, int32_t vec
                            diag ? diag_coef(&tmp, n0) : DiagCoef{}, s),
             "slab pass launch");
     if (!diag) return PRS_OK;
-    HIP_TRY(launch_finalize(parts, ntiles, record_on_device ? record : drec, n0, p->eta0 + (double)n0 * p->deta,
-                            area_scale(*p), s),
-            "finalize launch");
+    const FinJob job{parts, ntiles, record_on_device ? record : drec, n0, p->eta0 + (double)n0 * p->deta};
+    HIP_TRY(launch_finalize(&job, 1, area_scale(*p), s), "finalize launch");
     if (record_on_device) return PRS_OK;
     HIP_TRY(hipMemcpyAsync(record, drec, sizeof(prs_stats), hipMemcpyDeviceToHost, s), "record copy");
     HIP_TRY(hipStreamSynchronize(s), "record sync");
@@ -1502,6 +1537,7 @@ struct ItemCursor {
     std::vector<PassEntry> plan;
     size_t next;
     prs_ctx coef;            // parameters for the coefficient schedule
+    RecordQueue queue;
 };
 
 prs_status batch_item_begin(prs_batch* b, int32_t r, ItemCursor& cur, hipStream_t s)
@@ -1510,6 +1546,8 @@ prs_status batch_item_begin(prs_batch* b, int32_t r, ItemCursor& cur, hipStream_
     cur.item = r;
     cur.plan = batch_plan(it, b->geo[r], b->til[r], b->part_cap[r], b->tblock[r]);
     cur.next = 0;
+    cur.queue = RecordQueue{reinterpret_cast<WavePartial*>(static_cast<char*>(b->ws) + b->off_part + b->part_off[r]),
+                            2 * b->part_cap[r], area_scale(it.p)};
     cur.coef = prs_ctx{};
     cur.coef.p = it.p;
     cur.coef.V0 = v0_of(it.p);
@@ -1537,18 +1575,22 @@ prs_status batch_item_pass(prs_batch* b, ItemCursor& cur, hipStream_t s)
     void* pi_now = e.alt ? alt : dphi;
     void* pi_next = e.alt ? dphi : alt;
     const bool diag = e.rec >= 0;
-    WavePartial* parts = diag ? reinterpret_cast<WavePartial*>(base + b->off_part + b->part_off[r]) : nullptr;
     const int64_t n = e.first;
+    WavePartial* parts = nullptr;
+    if (diag) {
+        prs_stats* recs = reinterpret_cast<prs_stats*>(base + b->off_rec) + b->rec_off[r];
+        const int64_t ntiles = e.steps > 1 ? tb_tiles(g, t, e.steps) : tile_counts(g, t).ntiles;
+        HIP_TRY(cur.queue.add(ntiles, recs + e.rec, n, it.p.eta0 + (double)n * it.p.deta, s, &parts),
+                "finalize launch");
+    }
     const DiagCoef dc = diag_coef(&cur.coef, n);
     void* phi_in = phi[idx & 1];
     void* phi_out = phi[(idx + 1) & 1];
-    int64_t ntiles = tile_counts(g, t).ntiles;
     if (e.steps > 1) {
         StepCoef64 k[kMaxPassSteps];
         for (int i = 0; i < e.steps; ++i) k[i] = coef_for(&cur.coef, n + i);
         HIP_TRY(launch_tb(e.steps, g, t, phi_in, phi_out, pi_now, pi_next, k, diag, parts, dc, s),
                 "multi-step kernel launch");
-        ntiles = tb_tiles(g, t, e.steps);
     } else if (e.steps == 1) {
         HIP_TRY(launch_step(g, t, phi_in, phi_out, pi_now, pi_now, coef_for(&cur.coef, n), true, diag, parts, dc,
                             s),
@@ -1558,12 +1600,8 @@ prs_status batch_item_pass(prs_batch* b, ItemCursor& cur, hipStream_t s)
                             s),
                 "diagnostics kernel launch");
     }
-    if (diag) {
-        prs_stats* recs = reinterpret_cast<prs_stats*>(base + b->off_rec) + b->rec_off[r];
-        HIP_TRY(launch_finalize(parts, ntiles, recs + e.rec, n, it.p.eta0 + (double)n * it.p.deta,
-                                area_scale(it.p), s),
-                "finalize launch");
-    }
+    // the final state's record is the plan's last entry
+    if (cur.next == cur.plan.size()) HIP_TRY(cur.queue.reduce(s), "finalize launch");
     return PRS_OK;
 }
 

@@ -236,6 +236,14 @@ __device__ __forceinline__ double from_right_lane(double v)
     return __builtin_bit_cast(double, ((uint64_t)h << 32) | l);
 }
 
+__device__ __forceinline__ double u64_as_double(uint32_t lo, uint32_t hi)
+{
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Diagnostic sums of one wave.  The counts are wave totals (the same value
+// in every lane, added as populations of lane masks); area and ek are
+// per-lane partial sums.
 struct DiagAcc {
     uint32_t links[3];
     uint32_t walls;
@@ -244,62 +252,123 @@ struct DiagAcc {
     double ek;
 };
 
-// Eqs. (7)-(8) contribution of one site: forward links along each axis,
-// the wall flag from forward and backward links, the area weight
-// |g| / sum|g_d| from centred differences (the 1/(2 dx) factor cancels), and
-// (1/2) phi_dot^2 / V at wall sites.
-template <int D, typename R>
-__device__ __forceinline__ void site_diag(R c, R pi, const R (&nm)[D], const R (&np)[D], const DiagCoef& dc,
-                                          DiagAcc& a)
+__device__ __forceinline__ void zero_diag(DiagAcc& a)
 {
-    const bool sc = c >= R(0);
-    int cross = 0;
-    bool wall = false;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        const bool fwd = sc != (np[d] >= R(0));
-        const bool bwd = sc != (nm[d] >= R(0));
-        a.links[d] += fwd ? 1u : 0u;
-        cross += fwd ? 1 : 0;
-        wall = wall || fwd || bwd;
-    }
-    if (!(__builtin_isfinite(c) && __builtin_isfinite(pi))) a.nonfinite += 1u;
-    a.walls += wall ? 1u : 0u;
-    // The FP64 terms are evaluated only by waves that have a crossing link
-    // (a wall site) among their lanes: walls are sparse once the network has
-    // coarsened, and without the wave-uniform test the compiler evaluates
-    // both square root and divisions on every site.
-    if (__builtin_amdgcn_ballot_w64(cross != 0)) {
-        if (cross) {
-            double gsq = 0.0, gabs = 0.0;
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                double h = (double)np[d] - (double)nm[d];
-                gsq += h * h;
-                gabs += fabs(h);
-            }
-            double w = gabs > 0.0 ? sqrt(gsq) / gabs : 1.0;
-            a.area += (double)cross * w;
-        }
-    }
-    if (__builtin_amdgcn_ballot_w64(wall)) {
-        if (wall) {
-            double cd = (double)c;
-            double q = cd * cd * dc.kc - 1.0;
-            double V = dc.V0 * q * q;
-            if (V > 0.0) {
-                double pd = (double)pi;
-                a.ek += 0.5 * pd * pd / V;
-            }
-        }
-    }
+    a.links[0] = a.links[1] = a.links[2] = 0u;
+    a.walls = a.nonfinite = 0u;
+    a.area = a.ek = 0.0;
 }
 
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
+// Lanes whose value is non-negative (-0 included).
+template <typename R>
+__device__ __forceinline__ uint64_t sign_mask(R v) { return __builtin_amdgcn_ballot_w64(v >= R(0)); }
+
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// 1.0 in the mask's lanes, else 0.0 (a select of the high word: the low word
+// of both is 0).
+__device__ __forceinline__ double one_if(uint64_t m)
 {
+    return u64_as_double(0u, in_mask(m) ? 0x3FF00000u : 0u);
+}
+
+// True for a positive normal FP64 value (not zero, denormal, inf or NaN).
+__device__ __forceinline__ bool pos_normal(double x) { return __builtin_amdgcn_class(x, 0x100); }
+
+// x^(-1/2) and 1/x of a positive normal x, to about an ulp: the hardware's
+// estimate (2^-24) and one third-order step.
+__device__ __forceinline__ double rsqrt_step(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * y), y, 1.0);
+    return fma(y, e * fma(0.375, e, 0.5), y);      // y (1 + e/2 + 3/8 e^2), e = 1 - x y^2
+}
+
+__device__ __forceinline__ double rcp_step(double x)
+{
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);                // r (1 + e + e^2), e = 1 - x r
+}
+
+// Eqs. (7)-(8) contributions of N sites of every lane with `own`: forward
+// links along each axis, the wall flag from forward and backward links, the
+// area weight |g| / sum|g_d| from centred differences (the 1/(2 dx) factor
+// cancels), and (1/2) phi_dot^2 / V at wall sites.  Called by whole waves
+// (lanes without `own` add nothing): signs and links are lane masks, combined
+// and counted on the scalar unit, so a site without a wall costs its
+// comparisons only.  The FP64 terms are evaluated in waves with a wall among
+// the N sites (walls are sparse once the network has coarsened), for the N
+// sites at once and without branches, other lanes' terms replaced by 0: what
+// bounds them is the latency of their chains, which a branch per site ran
+// one after the other.  The weight is gsq (gsq gabs^2)^(-1/2), half the
+// instructions of a square root and a division; where that product or a V is
+// not a positive normal number (a gradient of 0, V = 0, inf, NaN, float64
+// fields of magnitudes past 10^+-77) the wave takes the plain forms.
+// Diagnostic passes with per-lane counters, a branch per site and the plain
+// forms, and now: 256^2 (vec 4, 2 steps) 30.3 and 19.0 us, an 8192 x 1024
+// slab of random values (vec 2, 8 steps) 107 and 86 us, 128^3 29.0 and
+// 22.7 us, 1024^3 9.37 and 7.83 ms; passes without diagnostics take 6.7 us,
+// 44 us, 13.0 us and 4.38 ms.
+template <int D, int N, typename R>
+__device__ __forceinline__ void sites_diag(const R (&c)[N], const R (&pi)[N], const R (&nm)[N][D],
+                                           const R (&np)[N][D], bool own, const DiagCoef& dc, DiagAcc& a)
+{
+    // lane masks: forward links per axis, sites with one, wall sites
+    uint64_t fwd[N][D], cut[N], wall[N], some = 0;
+    const uint64_t mine = __builtin_amdgcn_ballot_w64(own);
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+    for (int j = 0; j < N; ++j) {
+        const uint64_t sc = sign_mask(c[j]);
+        cut[j] = wall[j] = 0;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            fwd[j][d] = (sc ^ sign_mask(np[j][d])) & mine;
+            cut[j] |= fwd[j][d];
+            wall[j] |= sc ^ sign_mask(nm[j][d]);
+            a.links[d] += (uint32_t)__builtin_popcountll(fwd[j][d]);
+        }
+        wall[j] = (wall[j] & mine) | cut[j];
+        a.walls += (uint32_t)__builtin_popcountll(wall[j]);
+        const uint64_t bad = __builtin_amdgcn_ballot_w64(!__builtin_isfinite(c[j])) |
+                             __builtin_amdgcn_ballot_w64(!__builtin_isfinite(pi[j]));
+        a.nonfinite += (uint32_t)__builtin_popcountll(bad & mine);
+        some |= wall[j];
+    }
+    if (some == 0) return;
+    double gsq[N], gabs[N], cross[N], w[N], num[N], V[N], t[N];
+    uint64_t odd = 0;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const double h = (double)np[j][d] - (double)nm[j][d];
+            gsq[j] = d == 0 ? h * h : fma(h, h, gsq[j]);
+            gabs[j] = d == 0 ? fabs(h) : gabs[j] + fabs(h);
+            cross[j] = d == 0 ? one_if(fwd[j][d]) : cross[j] + one_if(fwd[j][d]);
+        }
+        const double cd = (double)c[j], pd = (double)pi[j];
+        const double q = cd * cd * dc.kc - 1.0;
+        V[j] = dc.V0 * q * q;
+        num[j] = 0.5 * pd * pd;
+        const double x = gsq[j] * (gabs[j] * gabs[j]);
+        w[j] = gsq[j] * rsqrt_step(x);
+        t[j] = num[j] * rcp_step(V[j]);
+        odd |= (cut[j] & ~__builtin_amdgcn_ballot_w64(pos_normal(x))) |
+               (wall[j] & ~__builtin_amdgcn_ballot_w64(pos_normal(V[j])));
+    }
+    if (odd) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            w[j] = gabs[j] > 0.0 ? sqrt(gsq[j]) / gabs[j] : 1.0;
+            t[j] = V[j] > 0.0 ? num[j] / V[j] : 0.0;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        a.area += in_mask(cut[j]) ? cross[j] * w[j] : 0.0;
+        a.ek += in_mask(wall[j]) ? t[j] : 0.0;
+    }
 }
 
 __device__ __forceinline__ double wave_sum_f64(double v)
@@ -309,53 +378,110 @@ __device__ __forceinline__ double wave_sum_f64(double v)
     return v;
 }
 
-// Adds `count` wave partials into one record, with one wave, in a fixed
-// order: lane l sums partials l, l+64, l+128, ... and the 64 lane sums are
-// combined by a fixed butterfly.  Every path that produces a record (single
-// run, standalone diagnostics, batched ensemble) calls this function, so a
-// record depends only on the partials, never on which kernel reduced them.
+// Writes a wave's diagnostic sums to its partial.
+__device__ __forceinline__ void put_partial(const DiagAcc& acc, WavePartial& out)
+{
+    WavePartial w;
+    w.links[0] = acc.links[0];
+    w.links[1] = acc.links[1];
+    w.links[2] = acc.links[2];
+    w.walls = acc.walls;
+    w.nonfinite = acc.nonfinite;
+    w.pad = 0u;
+    w.area = wave_sum_f64(acc.area);
+    w.ek = wave_sum_f64(acc.ek);
+    if ((threadIdx.x & (kWave - 1)) == 0) out = w;
+}
+
+// A record is the sum of its wave partials in a fixed order: virtual lane v
+// of kFinLanes sums partials v, v + kFinLanes, ..., lane l of a wave adds the
+// virtual lanes l, l + 64, ... in turn, and the 64 lane sums are combined by
+// a fixed butterfly.  Every path that produces a record (single run,
+// standalone diagnostics, batched ensemble) sums in this order, so a record
+// depends only on the partials, never on which kernel reduced them.
+constexpr int kFinLanes = 512;
+constexpr int kFinGroups = kFinLanes / kWave;
+
+struct RecordSums {
+    uint64_t l0, l1, l2, wl, nf;
+    double ar, ek;
+};
+
+__device__ __forceinline__ void zero_sums(RecordSums& r)
+{
+    r.l0 = r.l1 = r.l2 = r.wl = r.nf = 0;
+    r.ar = r.ek = 0.0;
+}
+
+// Counts are whole numbers (any order gives the same sum).
+__device__ __forceinline__ void add_counts(RecordSums& r, const WavePartial& p)
+{
+    r.l0 += p.links[0];
+    r.l1 += p.links[1];
+    r.l2 += p.links[2];
+    r.wl += p.walls;
+    r.nf += p.nonfinite;
+}
+
+// Butterfly over one wave's lane sums and the record (lane 0).
+__device__ __forceinline__ void write_record(RecordSums v, prs_stats* __restrict__ rec, int64_t step, double eta,
+                                             double area_scale)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        v.l0 += __shfl_xor(v.l0, o, kWave);
+        v.l1 += __shfl_xor(v.l1, o, kWave);
+        v.l2 += __shfl_xor(v.l2, o, kWave);
+        v.wl += __shfl_xor(v.wl, o, kWave);
+        v.nf += __shfl_xor(v.nf, o, kWave);
+        v.ar += __shfl_xor(v.ar, o, kWave);
+        v.ek += __shfl_xor(v.ek, o, kWave);
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        prs_stats r;
+        r.step = step;
+        r.eta = eta;
+        r.links_dir[0] = v.l0;
+        r.links_dir[1] = v.l1;
+        r.links_dir[2] = v.l2;
+        r.links = v.l0 + v.l1 + v.l2;
+        r.wall_sites = v.wl;
+        r.nonfinite = v.nf;
+        r.area_density = v.ar * area_scale;
+        r.gv2 = v.wl ? v.ek / (double)v.wl : 0.0;
+        *rec = r;
+    }
+}
+
+// One wave reduces `count` partials (the ensemble kernel's record).
 __device__ __forceinline__ void finalize_wave(const WavePartial* __restrict__ parts, int64_t count,
                                               prs_stats* __restrict__ rec, int64_t step, double eta,
                                               double area_scale)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    uint64_t l0 = 0, l1 = 0, l2 = 0, wl = 0, nf = 0;
-    double ar = 0.0, ek = 0.0;
-#pragma unroll 8
-    for (int64_t i = lane; i < count; i += kWave) {
-        const WavePartial p = parts[i];
-        l0 += p.links[0];
-        l1 += p.links[1];
-        l2 += p.links[2];
-        wl += p.walls;
-        nf += p.nonfinite;
-        ar += p.area;
-        ek += p.ek;
+    RecordSums v;
+    zero_sums(v);
+    double ar[kFinGroups], ek[kFinGroups];
+#pragma unroll
+    for (int g = 0; g < kFinGroups; ++g) ar[g] = ek[g] = 0.0;
+    for (int64_t base = lane; base < count; base += kFinLanes) {
+#pragma unroll
+        for (int g = 0; g < kFinGroups; ++g) {
+            const int64_t i = base + (int64_t)g * kWave;
+            if (i < count) {
+                const WavePartial p = parts[i];
+                add_counts(v, p);
+                ar[g] += p.area;
+                ek[g] += p.ek;
+            }
+        }
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        l0 += __shfl_xor(l0, o, kWave);
-        l1 += __shfl_xor(l1, o, kWave);
-        l2 += __shfl_xor(l2, o, kWave);
-        wl += __shfl_xor(wl, o, kWave);
-        nf += __shfl_xor(nf, o, kWave);
-        ar += __shfl_xor(ar, o, kWave);
-        ek += __shfl_xor(ek, o, kWave);
+    for (int g = 0; g < kFinGroups; ++g) {
+        v.ar += ar[g];
+        v.ek += ek[g];
     }
-    if (lane == 0) {
-        prs_stats r;
-        r.step = step;
-        r.eta = eta;
-        r.links_dir[0] = l0;
-        r.links_dir[1] = l1;
-        r.links_dir[2] = l2;
-        r.links = l0 + l1 + l2;
-        r.wall_sites = wl;
-        r.nonfinite = nf;
-        r.area_density = ar * area_scale;
-        r.gv2 = wl ? ek / (double)wl : 0.0;
-        *rec = r;
-    }
+    write_record(v, rec, step, eta, area_scale);
 }
 
 template <typename R>
@@ -572,10 +698,12 @@ __device__ __forceinline__ void step_plane(const StepArgsT<R>& A, const TileSetu
     for (int t = 0; t < TY; ++t) {
         if (t >= S.nvalid) continue;
         R out_phi[VEC], out_pi[VEC];
+        R nms[VEC][D], nps[VEC][D];
 #pragma unroll
         for (int j = 0; j < VEC; ++j) {
             const R c = Pc.v[t][j];
-            R nm[D], np[D];
+            R(&nm)[D] = nms[j];
+            R(&np)[D] = nps[j];
             neighbours<D, VEC, TY>(Pm, Pc, Pn, left, right, S.nvalid, t, j, nm, np);
             if constexpr (UPDATE) {
                 R ns;
@@ -585,10 +713,8 @@ __device__ __forceinline__ void step_plane(const StepArgsT<R>& A, const TileSetu
                     ns = nsum2(nm[0], np[0], nm[1], np[1]);
                 kick_drift<D, UNIT>(c, ns, pic[t][j], A.k, out_pi[j], out_phi[j]);
             }
-            if constexpr (DIAG) {
-                if (S.active) site_diag<D>(c, pic[t][j], nm, np, A.dc, acc);
-            }
         }
+        if constexpr (DIAG) sites_diag<D, VEC>(Pc.v[t], pic[t], nms, nps, S.active, A.dc, acc);
         if constexpr (UPDATE) {
             if (S.active) {
                 store_vec<VEC>(phi_out + S.off[t], out_phi);
@@ -622,9 +748,7 @@ __device__ __forceinline__ void step_tile(const StepArgsT<R>& A, int64_t tile)
     load_point<VEC, TY>(A.pi, S.s0, S, pi0);
 
     DiagAcc acc;
-    acc.links[0] = acc.links[1] = acc.links[2] = 0u;
-    acc.walls = acc.nonfinite = 0u;
-    acc.area = acc.ek = 0.0;
+    zero_diag(acc);
 
     for (int64_t s = S.s0; s < S.s1; s += 4) {
         step_plane<D, VEC, TY, UPDATE, DIAG, UNIT>(A, S, s, P0, P1, P2, P3, pi0, pi1, acc);
@@ -637,16 +761,7 @@ __device__ __forceinline__ void step_tile(const StepArgsT<R>& A, int64_t tile)
     }
 
     if constexpr (DIAG) {
-        WavePartial w;
-        w.links[0] = wave_sum_u32(acc.links[0]);
-        w.links[1] = wave_sum_u32(acc.links[1]);
-        w.links[2] = wave_sum_u32(acc.links[2]);
-        w.walls = wave_sum_u32(acc.walls);
-        w.nonfinite = wave_sum_u32(acc.nonfinite);
-        w.pad = 0u;
-        w.area = wave_sum_f64(acc.area);
-        w.ek = wave_sum_f64(acc.ek);
-        if (lane == 0) A.partials[tile] = w;
+        put_partial(acc, A.partials[tile]);
     }
 }
 
@@ -921,11 +1036,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t span_rsrc(const R* base, uint3
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<R*>(base), (short)0, (int)bytes, kRawBufferWord3);
 }
 
-__device__ __forceinline__ double u64_as_double(uint32_t lo, uint32_t hi)
-{
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
 // VEC values of this lane at byte offset voff of the span [base, base+bytes).
 template <int VEC, typename R>
 __device__ __forceinline__ void buf_load(const R* base, uint32_t bytes, uint32_t voff, R (&v)[VEC])
@@ -1036,6 +1146,7 @@ __device__ __forceinline__ void tb_iter(const TBArgs<T, R>& A, const TBLane& L, 
         R left = from_left_lane(cc[VEC - 1]);
         R right = from_right_lane(cc[0]);
         R out_phi[VEC], out_pi[VEC];
+        R nm[VEC][2], np[VEC][2];
         // level 1 row y is inside the tile for i in [T-1, T-1 + s1 - s0)
         const bool diag_row = DIAG && k == 1 && i >= T - 1 && i < T - 1 + (L.s1 - L.s0);
 #pragma unroll
@@ -1045,11 +1156,17 @@ __device__ __forceinline__ void tb_iter(const TBArgs<T, R>& A, const TBLane& L, 
             const R xp = j < VEC - 1 ? cc[j < VEC - 1 ? j + 1 : j] : right;
             kick_drift<2, UNIT>(c, nsum2(xm, xp, cm[j], cp[j]), pp[j], A.k[k - 1], out_pi[j], out_phi[j]);
             if constexpr (DIAG) {
-                if (diag_row && L.soff != kPastRow) {
-                    const R nm[2] = {xm, cm[j]};
-                    const R np[2] = {xp, cp[j]};
-                    site_diag<2>(c, pp[j], nm, np, A.dc, acc);
-                }
+                nm[j][0] = xm;
+                nm[j][1] = cm[j];
+                np[j][0] = xp;
+                np[j][1] = cp[j];
+            }
+        }
+        if constexpr (DIAG) {
+            if (diag_row) {
+                const R(&c)[VEC] = k == 1 ? S.in[U & 3] : S.lv[0][0];
+                const R(&pi)[VEC] = k == 1 ? S.pin[U & 1] : S.pl[0][0];
+                sites_diag<2, VEC>(c, pi, nm, np, L.soff != kPastRow, A.dc, acc);
             }
         }
         if (k < T) {
@@ -1174,9 +1291,7 @@ __device__ __forceinline__ void tb_tile(const TBArgs<T, R>& A, int64_t tile)
     rw.pi = yrow(y0 + d);
 
     DiagAcc acc;
-    acc.links[0] = acc.links[1] = acc.links[2] = 0u;
-    acc.walls = acc.nonfinite = 0u;
-    acc.area = acc.ek = 0.0;
+    zero_diag(acc);
 
     const int32_t last = (L.s1 - L.s0) + 2 * T - 3;
     int32_t i = 0;
@@ -1192,30 +1307,21 @@ __device__ __forceinline__ void tb_tile(const TBArgs<T, R>& A, int64_t tile)
     }
 
     if constexpr (DIAG) {
-        WavePartial w;
-        w.links[0] = wave_sum_u32(acc.links[0]);
-        w.links[1] = wave_sum_u32(acc.links[1]);
-        w.links[2] = 0u;
-        w.walls = wave_sum_u32(acc.walls);
-        w.nonfinite = wave_sum_u32(acc.nonfinite);
-        w.pad = 0u;
-        w.area = wave_sum_f64(acc.area);
-        w.ek = wave_sum_f64(acc.ek);
-        if (lane == 0) A.partials[tile] = w;
+        put_partial(acc, A.partials[tile]);
     }
 }
 
 // Waves per SIMD the register allocation of k_tb2d must leave room for: the
 // float32 eight-step pass with two sites per lane fits 128 VGPRs (four waves)
 // without spilling and is held there.
-constexpr int tb2d_min_waves(int vec, int T, int esize)
+constexpr int tb2d_min_waves(int vec, int T, int esize, bool diag)
 {
-    return (esize == 4 && vec == 2 && T == 8) ? 4 : 1;
+    return (esize == 4 && vec == 2 && T == 8 && !diag) ? 4 : 1;
 }
 
 template <int VEC, int T, bool DIAG, bool UNIT, typename R>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(tb2d_min_waves(VEC, T, (int)sizeof(R))))) void k_tb2d(TBArgs<T, R> A)
+__attribute__((amdgpu_waves_per_eu(tb2d_min_waves(VEC, T, (int)sizeof(R), DIAG)))) void k_tb2d(TBArgs<T, R> A)
 {
     const int64_t tile = uniform64(xcd_remap(blockIdx.x, gridDim.x) * kWavesPerBlock + wave_in_block());
     if (tile >= A.ntiles) return;
@@ -1226,7 +1332,7 @@ __attribute__((amdgpu_waves_per_eu(tb2d_min_waves(VEC, T, (int)sizeof(R))))) voi
 // of the fused adjoint's reverse passes, two per forward pass).
 template <int VEC, int T, bool UNIT, typename R>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(tb2d_min_waves(VEC, T, (int)sizeof(R))))) void k_tb2d_mid(TBArgs<T, R> A)
+__attribute__((amdgpu_waves_per_eu(tb2d_min_waves(VEC, T, (int)sizeof(R), false)))) void k_tb2d_mid(TBArgs<T, R> A)
 {
     const int64_t tile = uniform64(xcd_remap(blockIdx.x, gridDim.x) * kWavesPerBlock + wave_in_block());
     if (tile >= A.ntiles) return;
@@ -1894,10 +2000,11 @@ __device__ __forceinline__ void tb3_iter(const TB3Args<T, R>& A, const TB3Lane<T
                                     A.k[k - 1], out_pi[j], out_phi[j]);
                 if constexpr (DIAG) {
                     if (k == 1 && r >= T && r < T + TY) {
-                        if (diag_plane && r - T < L.yown && L.own_lane) {
-                            const R nm[3] = {xm, cc[r - 1][j], cm[r][j]};
-                            const R np[3] = {xp, cc[r + 1][j], cp[r][j]};
-                            site_diag<3>(c, pp[r][j], nm, np, A.dc, acc);
+                        if (diag_plane && r - T < L.yown) {
+                            const R ca[1] = {c}, pa[1] = {pp[r][j]};
+                            const R nm[1][3] = {{xm, cc[r - 1][j], cm[r][j]}};
+                            const R np[1][3] = {{xp, cc[r + 1][j], cp[r][j]}};
+                            sites_diag<3, 1>(ca, pa, nm, np, L.own_lane, A.dc, acc);
                         }
                     }
                 }
@@ -2012,9 +2119,7 @@ __device__ __forceinline__ void tb3_tile(const TB3Args<T, R>& A, int64_t tile)
     rw.pi = zplane(z0 + 1);
 
     DiagAcc acc;
-    acc.links[0] = acc.links[1] = acc.links[2] = 0u;
-    acc.walls = acc.nonfinite = 0u;
-    acc.area = acc.ek = 0.0;
+    zero_diag(acc);
 
     const int32_t last = (L.s1 - L.s0) + 2 * T - 3;
     int32_t i = 0;
@@ -2030,16 +2135,7 @@ __device__ __forceinline__ void tb3_tile(const TB3Args<T, R>& A, int64_t tile)
     }
 
     if constexpr (DIAG) {
-        WavePartial w;
-        w.links[0] = wave_sum_u32(acc.links[0]);
-        w.links[1] = wave_sum_u32(acc.links[1]);
-        w.links[2] = wave_sum_u32(acc.links[2]);
-        w.walls = wave_sum_u32(acc.walls);
-        w.nonfinite = wave_sum_u32(acc.nonfinite);
-        w.pad = 0u;
-        w.area = wave_sum_f64(acc.area);
-        w.ek = wave_sum_f64(acc.ek);
-        if (lane == 0) A.partials[tile] = w;
+        put_partial(acc, A.partials[tile]);
     }
 }
 
@@ -2183,6 +2279,7 @@ __device__ __forceinline__ void tb3l_iter(const TB3Args<T, RT>& A, const TB3LLan
             const RT left = from_left_lane(cc[r][VEC - 1]);
             const RT right = from_right_lane(cc[r][0]);
             RT out_phi[VEC], out_pi[VEC];
+            RT nm[VEC][3], np[VEC][3];
 #pragma unroll
             for (int j = 0; j < VEC; ++j) {
                 const RT c = cc[r][j];
@@ -2193,12 +2290,17 @@ __device__ __forceinline__ void tb3l_iter(const TB3Args<T, RT>& A, const TB3LLan
                 kick_drift<3, UNIT>(c, nsum3(xm, xp, ym, yp, cm[r][j], cp[r][j]), pp[r][j], A.k[k - 1], out_pi[j],
                                     out_phi[j]);
                 if constexpr (DIAG) {
-                    if (k == 1 && diag_plane && ((L.own_rows >> r) & 1u) && L.own_lane) {
-                        const RT nm[3] = {xm, ym, cm[r][j]};
-                        const RT np[3] = {xp, yp, cp[r][j]};
-                        site_diag<3>(c, pp[r][j], nm, np, A.dc, acc);
-                    }
+                    nm[j][0] = xm;
+                    nm[j][1] = ym;
+                    nm[j][2] = cm[r][j];
+                    np[j][0] = xp;
+                    np[j][1] = yp;
+                    np[j][2] = cp[r][j];
                 }
+            }
+            if constexpr (DIAG) {
+                if (k == 1 && diag_plane && ((L.own_rows >> r) & 1u))
+                    sites_diag<3, VEC>(S.in[U & 3][r], S.pin[U & 1][r], nm, np, L.own_lane, A.dc, acc);
             }
             if (k < T) {
 #pragma unroll
@@ -2328,9 +2430,7 @@ __device__ __forceinline__ void tb3l_tile(const TB3Args<T, RT>& A, int64_t tile,
     __syncthreads();
 
     DiagAcc acc;
-    acc.links[0] = acc.links[1] = acc.links[2] = 0u;
-    acc.walls = acc.nonfinite = 0u;
-    acc.area = acc.ek = 0.0;
+    zero_diag(acc);
 
     const int32_t last = (L.s1 - L.s0) + 2 * T - 3;
     int32_t i = 0;
@@ -2346,16 +2446,7 @@ __device__ __forceinline__ void tb3l_tile(const TB3Args<T, RT>& A, int64_t tile,
     }
 
     if constexpr (DIAG) {
-        WavePartial w;
-        w.links[0] = wave_sum_u32(acc.links[0]);
-        w.links[1] = wave_sum_u32(acc.links[1]);
-        w.links[2] = wave_sum_u32(acc.links[2]);
-        w.walls = wave_sum_u32(acc.walls);
-        w.nonfinite = wave_sum_u32(acc.nonfinite);
-        w.pad = 0u;
-        w.area = wave_sum_f64(acc.area);
-        w.ek = wave_sum_f64(acc.ek);
-        if (lane == 0) A.partials[tile * NW + L.wave] = w;
+        put_partial(acc, A.partials[tile * NW + L.wave]);
     }
 }
 

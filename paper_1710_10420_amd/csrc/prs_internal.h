@@ -102,16 +102,22 @@ constexpr int kMaxPassSteps = 8;   // most leapfrog steps fused into one pass
 hipError_t launch_tb_slab(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
                           const void* pi_in, void* pi_out, const StepCoef64* k, bool diag, WavePartial* partials,
                           const DiagCoef& dc, hipStream_t s);
-hipError_t launch_tb_slab_f32(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
-                              const void* pi_in, void* pi_out, const StepCoef64* k, bool diag,
-                              WavePartial* partials, const DiagCoef& dc, hipStream_t s);
-hipError_t launch_tb_slab_f64(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
-                              const void* pi_in, void* pi_out, const StepCoef64* k, bool diag,
-                              WavePartial* partials, const DiagCoef& dc, hipStream_t s);
 
-// Reduces `count` partials in a fixed order into one record at `rec`.
-hipError_t launch_finalize(const WavePartial* partials, int64_t count, prs_stats* rec,
-                           int64_t step, double eta, double area_scale, hipStream_t s);
+// Reduces each job's `count` partials in a fixed order into its record (a
+// device or pinned host pointer); n <= kFinBatch jobs, one launch.
+struct FinJob {
+    const WavePartial* parts;
+    int64_t count;
+    prs_stats* rec;
+    int64_t step;
+    double eta;
+};
+constexpr int kFinBatch = 16;
+struct FinBatch {
+    FinJob job[kFinBatch];
+    double area_scale;
+};
+hipError_t launch_finalize(const FinJob* jobs, int n, double area_scale, hipStream_t s);
 
 hipError_t launch_fill_uniform(void* phi, int64_t count, uint64_t seed, bool f64, hipStream_t s);
 
@@ -145,16 +151,6 @@ hipError_t launch_tb_all(int T, const Geometry& g, const Tiling& t, const void* 
                          const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s);
 hipError_t launch_tba(int T, const Geometry& g, const Tiling& t, const void* w_in, void* w_out, const void* mu_in,
                       void* mu_out, const void* const* phi, double* gacc, const AdjCoef64* c, hipStream_t s);
-hipError_t launch_tb_all_f32(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* const* phi_lv,
-                             const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s);
-hipError_t launch_tb_all_f64(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* const* phi_lv,
-                             const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s);
-hipError_t launch_tba_f32(int T, const Geometry& g, const Tiling& t, const void* w_in, void* w_out,
-                          const void* mu_in, void* mu_out, const void* const* phi, double* gacc,
-                          const AdjCoef64* c, hipStream_t s);
-hipError_t launch_tba_f64(int T, const Geometry& g, const Tiling& t, const void* w_in, void* w_out,
-                          const void* mu_in, void* mu_out, const void* const* phi, double* gacc,
-                          const AdjCoef64* c, hipStream_t s);
 
 // Reverse passes that recompute their fields (2D): T reverse steps m .. s =
 // m-T+1 from the pass-start state (phi_s = phi^s, pi_s = phi_dot^{s-1/2}),
@@ -169,12 +165,6 @@ bool tb_mid_supported(const Geometry& g, const Tiling& t, int T);
 hipError_t launch_tb_mid(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
                          const void* pi_in, void* pi_out, void* phi_mid, void* pi_mid, const StepCoef64* k,
                          hipStream_t s);
-hipError_t launch_tb_mid_f32(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
-                             const void* pi_in, void* pi_out, void* phi_mid, void* pi_mid, const StepCoef64* k,
-                             hipStream_t s);
-hipError_t launch_tb_mid_f64(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
-                             const void* pi_in, void* pi_out, void* phi_mid, void* pi_mid, const StepCoef64* k,
-                             hipStream_t s);
 bool tbf_supported(const Geometry& g, const Tiling& t, int T);
 int64_t tbf_tiles(const Geometry& g, const Tiling& t, int T);
 int64_t tbf_workgroups(const Geometry& g, const Tiling& t, int T);   // of one launch
@@ -182,12 +172,6 @@ int64_t tb2_workgroups(const Geometry& g, const Tiling& t, int T);   // of one 2
 hipError_t launch_tbf(int T, const Geometry& g, const Tiling& t, const void* phi_s, const void* pi_s,
                       const void* w_in, void* w_out, const void* mu_in, void* mu_out, double* gacc,
                       const StepCoef64* k, const AdjCoef64* c, hipStream_t s);
-hipError_t launch_tbf_f32(int T, const Geometry& g, const Tiling& t, const void* phi_s, const void* pi_s,
-                          const void* w_in, void* w_out, const void* mu_in, void* mu_out, double* gacc,
-                          const StepCoef64* k, const AdjCoef64* c, hipStream_t s);
-hipError_t launch_tbf_f64(int T, const Geometry& g, const Tiling& t, const void* phi_s, const void* pi_s,
-                          const void* w_in, void* w_out, const void* mu_in, void* mu_out, double* gacc,
-                          const StepCoef64* k, const AdjCoef64* c, hipStream_t s);
 
 // mu = dL/dphi^S, w = deta*mu from the final field; FP64 loss partial per block.
 hipError_t launch_adj_seed(const Geometry& g, const void* phi, int64_t count, double kc, double deta, void* mu,
@@ -203,24 +187,40 @@ hipError_t static_scratch(void** ptr, size_t* bytes);
 hipError_t launch_copy16(const void* src, void* dst, int64_t n16, hipStream_t s);
 hipError_t launch_zero_f64(double* v, int64_t count, hipStream_t s);
 
-// Per-precision instantiations behind the dispatchers above (one kernel file
-// each).
+// Per-precision instantiations behind the dispatchers above (float and
+// double; one translation unit each).  halo: slab halo depth, 0 periodic.
+template <typename R>
+hipError_t launch_tb2d(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
+                       const void* pi_in, void* pi_out, const StepCoef64* k, bool diag, WavePartial* partials,
+                       const DiagCoef& dc, int halo, hipStream_t s);
+template <typename R>
+hipError_t launch_tb3d(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
+                       const void* pi_in, void* pi_out, const StepCoef64* k, bool diag, WavePartial* partials,
+                       const DiagCoef& dc, int halo, hipStream_t s);
+template <typename R>
+hipError_t launch_adjoint_p(const Geometry& g, const Tiling& t, const void* w_in, void* w_out, void* mu,
+                            const void* phi_n, double* gacc, const AdjCoef64& c, hipStream_t s);
+template <typename R>
+hipError_t launch_tb_all_p(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* const* phi_lv,
+                           const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s);
+template <typename R>
+hipError_t launch_tba_p(int T, const Geometry& g, const Tiling& t, const void* w_in, void* w_out,
+                        const void* mu_in, void* mu_out, const void* const* phi, double* gacc, const AdjCoef64* c,
+                        hipStream_t s);
+template <typename R>
+hipError_t launch_tb_mid_p(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
+                           const void* pi_in, void* pi_out, void* phi_mid, void* pi_mid, const StepCoef64* k,
+                           hipStream_t s);
+template <typename R>
+hipError_t launch_tbf_p(int T, const Geometry& g, const Tiling& t, const void* phi_s, const void* pi_s,
+                        const void* w_in, void* w_out, const void* mu_in, void* mu_out, double* gacc,
+                        const StepCoef64* k, const AdjCoef64* c, hipStream_t s);
 hipError_t launch_step_f32(const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out, const void* pi,
                            void* pi_out, const StepCoef64& k, bool update, bool diag, WavePartial* partials,
                            const DiagCoef& dc, hipStream_t s);
 hipError_t launch_step_f64(const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out, const void* pi,
                            void* pi_out, const StepCoef64& k, bool update, bool diag, WavePartial* partials,
                            const DiagCoef& dc, hipStream_t s);
-hipError_t launch_tb_f32(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
-                           const void* pi_in, void* pi_out, const StepCoef64* k, bool diag, WavePartial* partials,
-                           const DiagCoef& dc, hipStream_t s);
-hipError_t launch_tb_f64(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
-                           const void* pi_in, void* pi_out, const StepCoef64* k, bool diag, WavePartial* partials,
-                           const DiagCoef& dc, hipStream_t s);
-hipError_t launch_adjoint_f32(const Geometry& g, const Tiling& t, const void* w_in, void* w_out, void* mu,
-                              const void* phi_n, double* gacc, const AdjCoef64& c, hipStream_t s);
-hipError_t launch_adjoint_f64(const Geometry& g, const Tiling& t, const void* w_in, void* w_out, void* mu,
-                              const void* phi_n, double* gacc, const AdjCoef64& c, hipStream_t s);
 hipError_t launch_adj_seed_f32(const void* phi, int64_t count, double kc, double deta, void* mu, void* w,
                                double* partial, int nblocks, hipStream_t s);
 hipError_t launch_adj_seed_f64(const void* phi, int64_t count, double kc, double deta, void* mu, void* w,
