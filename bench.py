@@ -67,7 +67,7 @@ def kernel_digest():
     """Digest of the kernel sources (device code and its launch templates)."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("prs_device.h", "prs_fwd2d.hip", "prs_fwd3d.hip", "prs_adjoint.hip", "prs_kernels.hip",
+    for name in ("prs_device.h", "prs_block2d.h", "prs_fwd2d.hip", "prs_fwd3d.hip", "prs_adjoint.hip", "prs_kernels.hip",
                  "prs_ensemble.hip", "prs_internal.h"):
         with open(os.path.join(ROOT, "paper_1710_10420_amd", "csrc", name), "rb") as f:
             h.update(f.read())
@@ -257,10 +257,18 @@ def forward_leg(prs, torch, w, runs, warmup, tiling=None, steps_per_pass=None, e
     per_launch_bytes = BYTES_PER_SITE_PASS * sites           # algorithmic bytes of one pass
     achieved = per_launch_bytes / avg_launch_s / 1e9 if avg_launch_s else None
     digest = kernel_digest()
-    tr = TRAFFIC_PER_LAUNCH.get((w["key"],) + til + (T,))
+    # 2D: the steps between two diagnostic passes (T steps from each record)
+    # run in block passes of up to 16 steps, which are what is timed; their
+    # average length stands for the steps per launch
+    blocks = len(w["shape"]) == 2 and T > 1
+    nrec = prs.prs_records_in(sim.p, 0, S)
+    steps_launch = (S - nrec * min(T, w["diag_every"])) * runs / k_launches if blocks and k_launches else T
+    tr = TRAFFIC_PER_LAUNCH.get((w["key"], "block") if blocks else (w["key"],) + til + (T,))
     traffic = tr["bytes"] if tr and tr["sources"] == digest else None
-    lane_ops, isa = pass_valu_lane_ops(w["shape"], til, T, isa_counts()) if T > 1 else (None, None)
-    if T == 1:
+    lane_ops, isa = pass_valu_lane_ops(w["shape"], til, T, isa_counts()) if T > 1 and not blocks else (None, None)
+    if blocks:
+        kernel = "k_blk2d (block pass, %.2f fused leapfrog steps per pass on average)" % steps_launch
+    elif T == 1:
         kernel = "k_step (one fused leapfrog step per pass)"
     elif len(w["shape"]) == 3 and til[2] in (8, 16, 32, 64):
         kernel = ("k_tb3l<vec=%d,T=%d,waves=%d> (%d fused leapfrog steps per pass, row halos through LDS)"
@@ -274,16 +282,17 @@ def forward_leg(prs, torch, w, runs, warmup, tiling=None, steps_per_pass=None, e
             "kernel": kernel,
             "algorithmic_bytes_per_launch": per_launch_bytes,
             "algorithmic_bytes_per_site_per_pass": BYTES_PER_SITE_PASS,
-            "site_updates_per_launch": sites * T,
+            "site_updates_per_launch": sites * steps_launch,
             "avg_launch_us": avg_launch_s * 1e6 if avg_launch_s else None,
             "timed_launches": k_launches,
             "launch_timing": "HIP events on the library's stream around each run of consecutive pass-kernel "
                              "launches inside the timed region (prs_set_launch_timing)",
             # the site-update rate of the pass as the bandwidth a single-step
             # pass (16 B per site-update) would need, over the HBM peak
-            "effective_single_step_gbs": (BYTES_PER_UPDATE * sites * T / avg_launch_s / 1e9
+            "effective_single_step_gbs": (BYTES_PER_UPDATE * sites * steps_launch / avg_launch_s / 1e9
                                           if avg_launch_s else None),
-            "effective_single_step_frac": (BYTES_PER_UPDATE * sites * T / avg_launch_s / 1e9 / HBM_PEAK_GBS
+            "effective_single_step_frac": (BYTES_PER_UPDATE * sites * steps_launch / avg_launch_s / 1e9
+                                           / HBM_PEAK_GBS
                                            if avg_launch_s else None),
             "passes_per_run": {"multi_step": multi, "single_step": single}}
     if traffic:

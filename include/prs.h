@@ -124,10 +124,10 @@ int64_t prs_records_in(const prs_params* p, int64_t n0, int64_t nsteps);
 /* Advance nsteps steps (Eqs. 3-6).  The Laplacian, kick and drift of a step
  * run fused in one kernel, and a launch advances up to steps_per_pass steps
  * at once (prs_set_time_blocking: default 2 in 2D, 1 in 3D; the autotuner
- * may choose up to 8 in 2D and 4 in 3D), never with a recorded state inside
- * a pass.  When series is non-NULL the diagnostics (Eqs. 7-8) of every state
- * n with n % diag_every == 0 are computed inside the pass that starts at n
- * (on its input state) and written to series[0 .. *n_written-1]; cap must be
+ * may choose up to 8 in 2D and 4 in 3D; 2D passes without a record up to 16),
+ * never with a recorded state inside a pass.  When series is non-NULL the
+ * diagnostics (Eqs. 7-8) of every state n with n % diag_every == 0 are
+ * computed inside the pass that starts at n (on its input state) and written to series[0 .. *n_written-1]; cap must be
  * at least prs_records_in(...), else PRS_EINVAL.  With series == NULL no
  * diagnostics are computed.  Splitting a call into two consecutive calls
  * gives bit-identical fields and records.  Synchronises the stream when
@@ -213,8 +213,8 @@ prs_status prs_autotune(prs_ctx* ctx, const char* cache_path, int32_t flags, voi
 
 /* Launch timing, for measurement.  With on != 0, prs_step_n brackets every
  * run of consecutive launches of its pass kernel (the steps_per_pass-step
- * pass without diagnostics) with a pair of HIP events on the context's
- * stream, synchronises the stream before returning and adds the runs'
+ * pass without diagnostics; in 2D the block passes) with a pair of HIP
+ * events on the context's stream, synchronises the stream before returning and adds the runs'
  * durations and launch counts to two totals.  prs_get_launch_timing reads
  * the totals (milliseconds and launches; either pointer may be NULL) and
  * clears them when reset != 0.  Off by default; timing adds two event
@@ -235,7 +235,11 @@ prs_status prs_tuned_tiling(const prs_params* p, const char* cache_path, int32_t
 
 /* Temporal blocking: with steps_per_pass = T > 1, prs_step_n advances up to
  * T steps per pass over HBM -- a pass never has a recorded state inside it --
- * so each value is read about once per T steps.  T may be 2, 3, 4, 6 or 8 for
+ * so each value is read about once per T steps.  In 2D the passes that start
+ * at a recorded state (and the adjoint's, slab's and persistent ensemble's)
+ * have T steps and the context's tiling; the steps between them run in block
+ * passes of up to 16 steps, whose shape and length the library chooses by
+ * the lattice's size, for any T > 1.  T may be 2, 3, 4, 6 or 8 for
  * 2D lattices (default 2), and 2, 3 or 4 for 3D lattices (default 1); other
  * values give PRS_EINVAL.  A pass uses T steps only when the tiling has a
  * T-step kernel, and otherwise the longest length that has one:

@@ -179,6 +179,98 @@ std::vector<uint8_t> plan_passes(const Geometry& g, const Tiling& t, int64_t cap
     return plan;
 }
 
+// One launch of a run: `steps` steps, by a block pass (blk) or by a marching
+// multi-step pass or single step of the run's tiling.
+struct Launch {
+    uint8_t steps;
+    bool blk;
+    bool flips() const { return blk || steps > 1; }   // phi_dot moves to the other buffer
+};
+
+// Block shapes of one lattice by step count, chosen on first use.
+struct BlkTable {
+    BlkShape at[kBlkSteps + 1] = {};
+    const BlkShape& get(const Geometry& g, int steps)
+    {
+        if (at[steps].vec == 0) at[steps] = blk_choose(g, steps);
+        return at[steps];
+    }
+};
+
+// The launches of nsteps steps from n0, no launch with a recorded state
+// (n % K == 0, K > 0) strictly inside it and an even number of them moving
+// phi_dot: plan_passes' plan, of which 2D runs with multi-step passes (T > 1)
+// keep the passes that compute a record's diagnostics (`records`: those that
+// start at a recorded state; their length decides the order of a record's
+// sums) and take the steps between them in block passes, which cover up to
+// kBlkSteps steps: each stretch in the number of equal launches estimated
+// fastest.
+std::vector<Launch> plan_launches(const Geometry& g, const Tiling& t, int64_t cap, int64_t n0, int64_t nsteps, int T,
+                                  int64_t K, bool records, BlkTable& table)
+{
+    std::vector<Launch> out;
+    const bool blocks = T > 1 && blk_supported(g);
+    int64_t n = n0, left = 0;      // steps of the current stretch without a record
+    size_t flips = 0;
+    auto add = [&](int64_t steps, bool blk) {
+        out.push_back(Launch{(uint8_t)steps, blk});
+        flips += out.back().flips() ? 1 : 0;
+    };
+    auto stretch = [&]() {
+        // long stretches in launches of the fastest length per step, the
+        // rest split evenly
+        while (left > 4 * kBlkSteps) {
+            int best = kBlkSteps;
+            for (int L = kBlkSteps / 2; L <= kBlkSteps; ++L)
+                if (table.get(g, L).us * best < table.get(g, best).us * L) best = L;
+            add(best, true);
+            left -= best;
+        }
+        if (left == 0) return;
+        int64_t m = 0;
+        double least = 0.0;
+        for (int64_t c = (left + kBlkSteps - 1) / kBlkSteps; c <= left && c <= 8; ++c) {
+            const int lo = (int)(left / c), more = (int)(left % c);
+            const double us = (c - more) * (double)table.get(g, lo).us +
+                              (more > 0 ? more * (double)table.get(g, lo + 1).us : 0.0);
+            if (m == 0 || us < least) {
+                m = c;
+                least = us;
+            }
+        }
+        for (int64_t i = 0; i < m; ++i) add(left / m + (i < left % m ? 1 : 0), true);
+        left = 0;
+    };
+    for (uint8_t L : plan_passes(g, t, cap, n0, nsteps, T, K)) {
+        const bool recorded = K > 0 && n % K == 0;
+        if (!blocks || (recorded && records)) {
+            stretch();
+            add(L, false);
+        } else {
+            if (recorded) stretch();      // no launch across a recorded (checkpointed) state
+            left += L;
+        }
+        n += L;
+    }
+    stretch();
+    if (flips % 2 == 1) {
+        // one too many: halve the last block pass of several steps, or run a
+        // one-step block pass as a single step (without block passes the
+        // plan is even)
+        auto several = [](const Launch& l) { return l.blk && l.steps > 1; };
+        auto it = std::find_if(out.rbegin(), out.rend(), several);
+        if (it != out.rend()) {
+            const Launch l = *it;
+            it->steps = (uint8_t)(l.steps - l.steps / 2);
+            out.insert(it.base(), Launch{(uint8_t)(l.steps / 2), true});
+        } else {
+            it = std::find_if(out.rbegin(), out.rend(), [](const Launch& l) { return l.blk; });
+            if (it != out.rend()) it->blk = false;
+        }
+    }
+    return out;
+}
+
 }  // namespace
 
 struct prs_ctx {
@@ -200,6 +292,7 @@ struct prs_ctx {
     Tiling rec_til;    // tiling and steps per pass of the adjoint's recomputation
     int32_t rec_tblock;   // (0: those of the forward)
     int32_t tblock;    // steps per pass (1: single steps)
+    mutable BlkTable blk;
     hipStream_t stream;
     int64_t step;
     // adjoint bookkeeping between prs_adjoint_forward and _backward
@@ -423,7 +516,8 @@ prs_status prs_step_n(prs_ctx* c, int64_t nsteps, prs_stats* series, int64_t cap
     RecordQueue queue{c->partials, c->partial_total, area_scale(c->p)};
 
     const int T = tb_supported(c->geo) ? c->tblock : 1;
-    const std::vector<uint8_t> plan = plan_passes(c->geo, c->til, c->partial_cap, c->step, nsteps, T, want ? K : 0);
+    const std::vector<Launch> plan = plan_launches(c->geo, c->til, c->partial_cap, c->step, nsteps, T, want ? K : 0,
+                                                   want, c->blk);
 
     void* pi_cur = c->pi;
     void* pi_oth = c->pi_alt;
@@ -432,11 +526,12 @@ prs_status prs_step_n(prs_ctx* c, int64_t nsteps, prs_stats* series, int64_t cap
     // diagnostics) is bracketed by one event pair
     size_t spans = 0;
     bool open = false;
-    for (uint8_t L : plan) {
+    for (const Launch& l : plan) {
+        const int L = l.steps;
         const int64_t n = c->step;
         const bool diag = want && (n % K == 0);
         if (c->lt_on) {
-            const bool dom = !diag && L == T;
+            const bool dom = !diag && (l.blk || L == T);
             if (dom && !open) {
                 if (2 * spans + 2 > c->lt_ev.size()) {
                     for (int j = 0; j < 2; ++j) {
@@ -463,7 +558,14 @@ prs_status prs_step_n(prs_ctx* c, int64_t nsteps, prs_stats* series, int64_t cap
                     "finalize launch");
         }
         const DiagCoef dc = diag_coef(c, n);
-        if (L > 1) {
+        if (l.blk) {
+            StepCoef64 k[kBlkSteps];
+            for (int i = 0; i < L; ++i) k[i] = coef_for(c, n + i);
+            HIP_TRY(launch_blk2d(L, c->blk.get(c->geo, L), c->geo, c->phi[c->cur], c->phi[c->cur ^ 1], pi_cur, pi_oth,
+                                 k, c->stream),
+                    "block pass launch");
+            std::swap(pi_cur, pi_oth);
+        } else if (L > 1) {
             StepCoef64 k[kMaxPassSteps];
             for (int i = 0; i < L; ++i) k[i] = coef_for(c, n + i);
             HIP_TRY(launch_tb(L, c->geo, c->til, c->phi[c->cur], c->phi[c->cur ^ 1], pi_cur, pi_oth, k, diag,
@@ -558,7 +660,8 @@ prs_status prs_plan_passes(const prs_ctx* c, int64_t nsteps, int32_t with_record
     const int T = tb_supported(c->geo) ? c->tblock : 1;
     const int64_t K = (with_records && c->p.diag_every > 0) ? c->p.diag_every : 0;
     int64_t m = 0, n1 = 0;
-    for (uint8_t L : plan_passes(c->geo, c->til, c->partial_cap, c->step, nsteps, T, K)) (L > 1 ? m : n1) += 1;
+    for (const Launch& l : plan_launches(c->geo, c->til, c->partial_cap, c->step, nsteps, T, K, K > 0, c->blk))
+        (l.flips() ? m : n1) += 1;
     if (multi_passes) *multi_passes = m;
     if (single_passes) *single_passes = n1;
     return PRS_OK;
@@ -1007,7 +1110,8 @@ prs_status prs_adjoint_forward(prs_ctx* c, int64_t nsteps, int32_t ckpt_every, v
     const void* phi_in = c->phi[c->cur];
     const void* pi_in = c->pi;
     int64_t k = 0;
-    for (uint8_t Lp : plan_passes(c->geo, c->til, c->partial_cap, 0, nsteps, T, L.K)) {
+    for (const Launch& l : plan_launches(c->geo, c->til, c->partial_cap, 0, nsteps, T, L.K, false, c->blk)) {
+        const int Lp = l.steps;
         const int64_t n = n0 + k;
         const bool ck = (k + Lp) % L.K == 0 && k + Lp < nsteps;   // ends on checkpoint (k+Lp)/K
         void* phi_out;
@@ -1018,10 +1122,15 @@ prs_status prs_adjoint_forward(prs_ctx* c, int64_t nsteps, int32_t ckpt_every, v
             pi_out = at<char>(work, L.ck_pi + L.fb * sg);
         } else {
             phi_out = c->phi[c->cur ^ 1];
-            if (Lp > 1) pi_out = pi_in == c->pi ? c->pi_alt : c->pi;
+            if (l.flips()) pi_out = pi_in == c->pi ? c->pi_alt : c->pi;
             else pi_out = (pi_in == c->pi || pi_in == c->pi_alt) ? const_cast<void*>(pi_in) : c->pi;
         }
-        if (Lp > 1) {
+        if (l.blk) {
+            StepCoef64 kk[kBlkSteps];
+            for (int i = 0; i < Lp; ++i) kk[i] = coef_for(c, n + i);
+            HIP_TRY(launch_blk2d(Lp, c->blk.get(c->geo, Lp), c->geo, phi_in, phi_out, pi_in, pi_out, kk, c->stream),
+                    "block pass launch");
+        } else if (Lp > 1) {
             StepCoef64 kk[kMaxPassSteps];
             for (int i = 0; i < Lp; ++i) kk[i] = coef_for(c, n + i);
             HIP_TRY(launch_tb(Lp, c->geo, c->til, phi_in, phi_out, pi_in, pi_out, kk, false, nullptr, DiagCoef{},
@@ -1341,7 +1450,9 @@ struct prs_batch {
     std::vector<Geometry> geo;
     std::vector<Tiling> til;
     std::vector<int32_t> tblock;        // steps per pass (1: single steps)
-    std::vector<int64_t> npasses;       // per item, including the final record pass
+    std::vector<int64_t> npasses;       // per item, including the final record pass (persistent modes)
+    std::vector<int64_t> nlaunches;     // the same of the stream modes, as last enqueued
+    int ran;                            // what ran last: 0 nothing, 1 a persistent mode, 2 a stream mode
     std::vector<int64_t> rec_off;       // count + 1 record offsets
     std::vector<int64_t> part_cap;      // partial capacity per realisation
     std::vector<size_t> coef_off, pass_off, alt_off, part_off;
@@ -1379,6 +1490,7 @@ namespace {
 
 struct PassEntry {
     int32_t first, steps, rec, alt;
+    bool blk;
 };
 
 struct BatchLayout {
@@ -1470,19 +1582,26 @@ prs_status batch_layout(const prs_batch_item* items, int32_t count, BatchLayout&
 // per pass, no recorded state inside a pass, an even number of multi-step
 // passes so phi_dot ends in the caller's buffer), then the diagnostics-only
 // pass of the final state.
-std::vector<PassEntry> batch_plan(const prs_batch_item& it, const Geometry& g, const Tiling& t, int64_t cap, int T)
+// The persistent modes take marching passes only (table: NULL), the stream
+// modes a single run's launches.
+std::vector<PassEntry> batch_plan(const prs_batch_item& it, const Geometry& g, const Tiling& t, int64_t cap, int T,
+                                  BlkTable* table)
 {
     const int64_t S = it.nsteps, K = it.p.diag_every;
+    std::vector<Launch> plan;
+    if (table) plan = plan_launches(g, t, cap, 0, S, T, K, K > 0, *table);
+    else
+        for (uint8_t L : plan_passes(g, t, cap, 0, S, T, K)) plan.push_back(Launch{L, false});
     std::vector<PassEntry> out;
     int64_t n = 0, rec = 0;
     int alt = 0;
-    for (uint8_t L : plan_passes(g, t, cap, 0, S, T, K)) {
+    for (const Launch& l : plan) {
         const bool r = K > 0 && n % K == 0;
-        out.push_back(PassEntry{(int32_t)n, (int32_t)L, r ? (int32_t)rec++ : -1, alt});
-        if (L > 1) alt ^= 1;
-        n += L;
+        out.push_back(PassEntry{(int32_t)n, (int32_t)l.steps, r ? (int32_t)rec++ : -1, alt, l.blk});
+        if (l.flips()) alt ^= 1;
+        n += l.steps;
     }
-    out.push_back(PassEntry{(int32_t)S, 0, (int32_t)rec, alt});   // final state
+    out.push_back(PassEntry{(int32_t)S, 0, (int32_t)rec, alt, false});   // final state
     return out;
 }
 
@@ -1537,6 +1656,7 @@ struct ItemCursor {
     std::vector<PassEntry> plan;
     size_t next;
     prs_ctx coef;            // parameters for the coefficient schedule
+    BlkTable blk;
     RecordQueue queue;
 };
 
@@ -1544,7 +1664,9 @@ prs_status batch_item_begin(prs_batch* b, int32_t r, ItemCursor& cur, hipStream_
 {
     const prs_batch_item& it = b->items[r];
     cur.item = r;
-    cur.plan = batch_plan(it, b->geo[r], b->til[r], b->part_cap[r], b->tblock[r]);
+    cur.blk = BlkTable{};
+    cur.plan = batch_plan(it, b->geo[r], b->til[r], b->part_cap[r], b->tblock[r], &cur.blk);
+    b->nlaunches[r] = (int64_t)cur.plan.size();
     cur.next = 0;
     cur.queue = RecordQueue{reinterpret_cast<WavePartial*>(static_cast<char*>(b->ws) + b->off_part + b->part_off[r]),
                             2 * b->part_cap[r], area_scale(it.p)};
@@ -1586,7 +1708,12 @@ prs_status batch_item_pass(prs_batch* b, ItemCursor& cur, hipStream_t s)
     const DiagCoef dc = diag_coef(&cur.coef, n);
     void* phi_in = phi[idx & 1];
     void* phi_out = phi[(idx + 1) & 1];
-    if (e.steps > 1) {
+    if (e.blk) {
+        StepCoef64 k[kBlkSteps];
+        for (int i = 0; i < e.steps; ++i) k[i] = coef_for(&cur.coef, n + i);
+        HIP_TRY(launch_blk2d(e.steps, cur.blk.get(g, e.steps), g, phi_in, phi_out, pi_now, pi_next, k, s),
+                "block pass launch");
+    } else if (e.steps > 1) {
         StepCoef64 k[kMaxPassSteps];
         for (int i = 0; i < e.steps; ++i) k[i] = coef_for(&cur.coef, n + i);
         HIP_TRY(launch_tb(e.steps, g, t, phi_in, phi_out, pi_now, pi_next, k, diag, parts, dc, s),
@@ -1689,7 +1816,7 @@ prs_status batch_upload(prs_batch* b, int32_t nseq)
         EnsCoef* dcoef = reinterpret_cast<EnsCoef*>(base + b->off_coef + b->coef_off[r]);
         HIP_TRY(hipMemcpy(dcoef, coef.data(), coef.size() * sizeof(EnsCoef), hipMemcpyHostToDevice),
                 "coefficient upload");
-        const std::vector<PassEntry> plan = batch_plan(it, g, t, b->part_cap[r], b->tblock[r]);
+        const std::vector<PassEntry> plan = batch_plan(it, g, t, b->part_cap[r], b->tblock[r], nullptr);
         std::vector<EnsPass>& ps = passes[(size_t)r];
         ps.resize(plan.size());
         int64_t cum = 0;
@@ -1937,6 +2064,8 @@ prs_status prs_batch_create(const prs_batch_item* items, int32_t count, void* wo
     b->rec_off = L.rec_off;
     b->total_recs = L.rec_off[count];
     b->npasses.assign(count, 0);
+    b->nlaunches.assign(count, 0);
+    b->ran = 0;
     for (int32_t r = 0; r < count; ++r) {
         b->geo.push_back(geometry_of(items[r].p));
         Tiling t = default_tiling(b->geo.back());
@@ -2028,8 +2157,15 @@ prs_status prs_batch_state(const prs_batch* b, int32_t item, void** phi, void** 
 {
     if (!b || item < 0 || item >= b->count) return fail(PRS_EINVAL, "invalid batch or item");
     const prs_batch_item& it = b->items[item];
-    const std::vector<PassEntry> plan = batch_plan(it, b->geo[item], b->til[item], b->part_cap[item], b->tblock[item]);
-    const int64_t np = (int64_t)plan.size();
+    // the run's own count: the modes' plans differ, and settings may have
+    // changed since
+    int64_t np = b->ran == 1 ? b->npasses[item] : b->ran == 2 ? b->nlaunches[item] : 0;
+    if (np == 0) {
+        BlkTable table;
+        np = (int64_t)batch_plan(it, b->geo[item], b->til[item], b->part_cap[item], b->tblock[item],
+                                 persistent_mode(b->mode) ? nullptr : &table)
+                 .size();
+    }
     if (phi) *phi = ((np - 1) & 1) ? it.phi_b : it.phi_a;
     if (dphi) *dphi = it.dphi;
     return PRS_OK;
@@ -2068,6 +2204,7 @@ prs_status prs_batch_run(prs_batch* b, prs_stats* series, int64_t cap)
         b->dirty = false;
     }
     *b->herr = 0;
+    b->ran = persistent ? 1 : 2;
     const bool graph = b->mode == PRS_BATCH_PERSISTENT_GRAPH || b->mode == PRS_BATCH_STREAMS_GRAPH;
     if (graph) {
         if (!b->exec) {

@@ -93,6 +93,25 @@ bool tb_steps_supported(const Geometry& g, int T);
 bool tb_pass_supported(const Geometry& g, const Tiling& t, int T);
 constexpr int kMaxPassSteps = 8;   // most leapfrog steps fused into one pass
 
+// Block passes (2D, prs_block2d.h): `steps` (1 .. kBlkSteps) steps in one
+// launch, each workgroup a block of 64 vec columns by waves * rows rows.
+// Operands as launch_tb's; phi_dot moves to pi_out whatever the step count.
+constexpr int kBlkSteps = 16;
+struct BlkShape {
+    int vec, rows, waves;
+    float us;            // estimated time of the launch
+};
+struct BlkGrid {
+    int64_t tiles_x, blocks;   // blocks: 0 when the shape has no valid middle or too many blocks
+    int32_t halo_lanes;
+};
+BlkGrid blk_grid(const Geometry& g, int vec, int rows, int waves, int steps);
+bool blk_supported(const Geometry& g);
+// The shape estimated fastest for `steps` steps of this lattice.
+BlkShape blk_choose(const Geometry& g, int steps);
+hipError_t launch_blk2d(int steps, const BlkShape& b, const Geometry& g, const void* phi_in, void* phi_out,
+                        const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s);
+
 // A T-step pass over a slab along the last axis (the per-device kernel of a
 // lattice sharded along y in 2D, z in 3D): the fields are stored with T halo
 // rows or planes below and above the g.M interior ones (row or plane z at
@@ -193,6 +212,9 @@ template <typename R>
 hipError_t launch_tb2d(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
                        const void* pi_in, void* pi_out, const StepCoef64* k, bool diag, WavePartial* partials,
                        const DiagCoef& dc, int halo, hipStream_t s);
+template <typename R>
+hipError_t launch_blk2d_p(int steps, const BlkShape& b, const Geometry& g, const void* phi_in, void* phi_out,
+                          const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s);
 template <typename R>
 hipError_t launch_tb3d(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
                        const void* pi_in, void* pi_out, const StepCoef64* k, bool diag, WavePartial* partials,

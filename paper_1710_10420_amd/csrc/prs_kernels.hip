@@ -195,6 +195,78 @@ hipError_t launch_tb(int T, const Geometry& g, const Tiling& t, const void* phi_
     return tb_dispatch(T, g, t, phi_in, phi_out, pi_in, pi_out, k, diag, partials, dc, 0, s);
 }
 
+BlkGrid blk_grid(const Geometry& g, int vec, int rows, int waves, int steps)
+{
+    BlkGrid b{0, 0, (steps + vec - 1) / vec};
+    const int64_t w = (int64_t)(kWave - 2 * b.halo_lanes) * vec, h = (int64_t)waves * rows - 2 * steps;
+    if (steps < 1 || steps > kBlkSteps || w <= 0 || h <= 0 || g.nx % vec != 0) return b;
+    b.tiles_x = (g.nx + w - 1) / w;
+    const int64_t n = b.tiles_x * ((g.M + h - 1) / h);
+    b.blocks = n <= 0x7FFFFFFF ? n : 0;
+    return b;
+}
+
+// Rows and columns are 32-bit in the kernel, a row's bytes a buffer size.
+bool blk_supported(const Geometry& g)
+{
+    return g.ndim == 2 && g.nx <= ((int64_t)1 << 28) && g.M <= ((int64_t)1 << 30) &&
+           blk_grid(g, 1, 2, 8, 4).blocks > 0;
+}
+
+// Time of a block pass on 256 compute units, from launches timed at 128^2 to
+// 8192^2 with 4 to 16 steps (the constants are fitted to them; the shape
+// picked is within 10 % of the fastest of all shapes, mostly the fastest).
+// While every unit holds at most two blocks, all run at once and the fullest
+// unit sets the time: launch and first loads, and per step a constant (the
+// barrier and the exchange) and the unit's sites.  Beyond that the blocks
+// pass through in turn, loads and stores beside other blocks' steps, and the
+// larger of memory and arithmetic rules.
+BlkShape blk_choose(const Geometry& g, int steps)
+{
+    struct Shape {
+        int8_t vec, rows, waves;
+    };
+    static const Shape f32[] = {{1, 2, 8},  {1, 2, 16}, {1, 3, 16}, {1, 4, 16}, {1, 5, 16},  {1, 8, 16},  {1, 12, 16},
+                                {2, 2, 16}, {2, 3, 16}, {2, 4, 16}, {2, 5, 16}, {2, 6, 16},  {2, 8, 16},  {2, 10, 16},
+                                {2, 11, 16}, {2, 12, 16}};
+    static const Shape f64[] = {{1, 2, 8},  {1, 2, 16}, {1, 3, 16}, {1, 4, 16}, {1, 5, 16}, {1, 8, 16},
+                                {1, 12, 16}, {2, 2, 16}, {2, 3, 16}, {2, 4, 16}, {2, 5, 16}};
+    const Shape* list = g.f64 ? f64 : f32;
+    const int n = g.f64 ? (int)(sizeof f64 / sizeof f64[0]) : (int)(sizeof f32 / sizeof f32[0]);
+    const double size = g.f64 ? 8 : 4, sites = (double)g.nx * (double)g.M;
+    const double start = 3.4, step = g.f64 ? 0.109 : 0.085, load = g.f64 ? 0.020 : 0.0095;
+    const double bw = 4 * sites * size > 250e6 ? 5.5e3 : g.f64 ? 6.5e3 : 4.7e3;   // bytes per ns x 1000
+    BlkShape best{0, 0, 0, 0.0f};
+    for (int i = 0; i < n; ++i) {
+        const int v = list[i].vec, r = list[i].rows, w = list[i].waves;
+        const BlkGrid b = blk_grid(g, v, r, w, steps);
+        if (b.blocks < 1) continue;
+        // us per step of 64 sites of a unit: two columns a lane share a DPP
+        // shift and an LDS access
+        const double site = (g.f64 ? 0.0059 : 0.0039) * (v == 1 ? 1.1 : 1.0);
+        const double per = (double)b.blocks / 256.0, held = w == 16 ? 2.0 : 4.0, area = (double)(w * r * v);
+        double t;
+        if (per <= held) {
+            const double m = (double)((b.blocks + 255) / 256);
+            t = start + steps * (step + m * area * site) + load * area * m;
+        } else {
+            const double arith = steps * (step + (per + 0.25 * held) * area * site);
+            const double mem = ((double)b.blocks * area * kWave + sites) * size * 2.0 / (bw * 1e3);
+            t = start + (arith > mem ? arith + 0.2 * mem : mem + 0.2 * arith);
+        }
+        if (best.vec == 0 || t < best.us) best = BlkShape{v, r, w, (float)t};
+    }
+    return best;
+}
+
+hipError_t launch_blk2d(int steps, const BlkShape& b, const Geometry& g, const void* phi_in, void* phi_out,
+                        const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s)
+{
+    if (!blk_supported(g)) return hipErrorInvalidValue;
+    return g.f64 ? launch_blk2d_p<double>(steps, b, g, phi_in, phi_out, pi_in, pi_out, k, s)
+                 : launch_blk2d_p<float>(steps, b, g, phi_in, phi_out, pi_in, pi_out, k, s);
+}
+
 hipError_t launch_tb_slab(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
                           const void* pi_in, void* pi_out, const StepCoef64* k, bool diag, WavePartial* partials,
                           const DiagCoef& dc, hipStream_t s)
