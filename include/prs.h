@@ -239,7 +239,10 @@ prs_status prs_tuned_tiling(const prs_params* p, const char* cache_path, int32_t
  * at a recorded state (and the adjoint's, slab's and persistent ensemble's)
  * have T steps and the context's tiling; the steps between them run in block
  * passes of up to 16 steps, whose shape and length the library chooses by
- * the lattice's size, for any T > 1.  T may be 2, 3, 4, 6 or 8 for
+ * the lattice's size, for any T > 1.  In 3D a context whose tiling and steps
+ * per pass were neither set nor tuned takes the steps between two records
+ * in passes of 2, 3 or 4 steps with tilings the library chooses by the
+ * lattice's size; set, they are used as they are (1: single steps).  T may be 2, 3, 4, 6 or 8 for
  * 2D lattices (default 2), and 2, 3 or 4 for 3D lattices (default 1); other
  * values give PRS_EINVAL.  A pass uses T steps only when the tiling has a
  * T-step kernel, and otherwise the longest length that has one:
@@ -276,7 +279,9 @@ prs_status prs_plan_passes(const prs_ctx* ctx, int64_t nsteps, int32_t with_reco
  * have no reverse pass and run single reverse steps); a pass runs the longest supported
  * length up to the setting, down to single reverse steps.  The default
  * tiling is the forward's at prs_init; the default steps per pass 4 in 2D,
- * 1 in 3D. */
+ * 1 in 3D.  While neither of the two is set or tuned the backward uses a
+ * reverse tiling and pass length chosen by the lattice's size, and so does
+ * the recomputation while the forward's settings are the default ones. */
 prs_status prs_set_adjoint_tiling(prs_ctx* ctx, int32_t vec, int32_t rows, int32_t ty);
 prs_status prs_get_adjoint_tiling(prs_ctx* ctx, int32_t* vec, int32_t* rows, int32_t* ty);
 prs_status prs_set_adjoint_time_blocking(prs_ctx* ctx, int32_t steps_per_pass);

@@ -14,6 +14,7 @@
 #include <cstring>
 #include <cstddef>
 #include <map>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -49,7 +50,6 @@ prs_status hip_fail(hipError_t e, const char* what)
 
 constexpr size_t kAlign = 256;
 constexpr int64_t kRecCap = 1024;   // records buffered before a flush
-constexpr int64_t kMinRows = 8;     // smallest marching tile the workspace allows
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
@@ -108,18 +108,11 @@ prs_status validate(const prs_params* p)
     return PRS_OK;
 }
 
+// The tiling of a run that neither the caller nor the tuner gave one: of the
+// passes of the default length.
 Tiling default_tiling(const Geometry& g)
 {
-    Tiling t;
-    if (g.nx % 4 == 0 && g.nx >= 256) t.vec = 4;
-    else if (g.nx % 2 == 0 && g.nx >= 128) t.vec = 2;
-    else if (g.nx % 4 == 0) t.vec = 4;
-    else if (g.nx % 2 == 0) t.vec = 2;
-    else t.vec = 1;
-    if (g.f64 && t.vec == 4) t.vec = 2;   // 16 bytes per lane at most
-    t.ty = g.ndim == 3 ? 2 : 1;
-    t.rows = g.ndim == 3 ? 32 : 16;
-    return t;
+    return g.ndim == 2 && tb_supported(g) ? auto_tile2(g, 2) : auto_step(g).til;
 }
 
 int64_t partial_capacity(const Geometry& g)
@@ -179,94 +172,154 @@ std::vector<uint8_t> plan_passes(const Geometry& g, const Tiling& t, int64_t cap
     return plan;
 }
 
-// One launch of a run: `steps` steps, by a block pass (blk) or by a marching
-// multi-step pass or single step of the run's tiling.
+// One launch of a run: a marching pass or single step of the run's tiling,
+// or, with `choice`, the launch of `steps` steps that the library chose.
 struct Launch {
     uint8_t steps;
-    bool blk;
-    bool flips() const { return blk || steps > 1; }   // phi_dot moves to the other buffer
+    const PassChoice* choice;
+    bool flips() const { return steps > 1 || (choice && choice->blk); }   // phi_dot moves to the other buffer
 };
 
-// Block shapes of one lattice by step count, chosen on first use.
-struct BlkTable {
-    BlkShape at[kBlkSteps + 1] = {};
-    const BlkShape& get(const Geometry& g, int steps)
+// Launches for the steps between two records: of all splits into the lengths
+// on offer the one estimated fastest, for an even and for an odd number of
+// launches that move phi_dot (their total has to be even).
+class Stretches {
+public:
+    // 2D: block passes of 1 .. kBlkSteps steps; 3D: LDS passes of 2, 3, 4
+    // steps; and single steps.
+    explicit Stretches(const Geometry& g)
     {
-        if (at[steps].vec == 0) at[steps] = blk_choose(g, steps);
-        return at[steps];
+        if (g.ndim == 2) {
+            for (int L = 1; L <= kBlkSteps; ++L) {
+                const BlkShape b = blk_choose(g, L);
+                if (b.vec) add(PassChoice{L, b.us, true, Tiling{b.vec, b.rows, b.waves}});
+            }
+        } else {
+            for (int T = 2; T <= 4; ++T) {
+                const PassChoice c = auto_pass3(g, T);
+                if (c.til.vec) add(c);
+            }
+        }
+        add(auto_step(g));
+        for (int i = 0; i < n_; ++i)
+            if (opt_[i].us * opt_[long_].steps < opt_[long_].us * opt_[i].steps) long_ = i;
+        for (int r = 0; r <= kMax; ++r)
+            for (int p = 0; p < 2; ++p) {
+                cost_[r][p] = r == 0 && p == 0 ? 0.0f : kNever;
+                for (int i = 0; i < n_; ++i) {
+                    const int L = opt_[i].steps, q = p ^ (flips(i) ? 1 : 0);
+                    if (L > r || cost_[r - L][q] >= kNever) continue;
+                    const float t = cost_[r - L][q] + opt_[i].us;
+                    if (t < cost_[r][p]) {
+                        cost_[r][p] = t;
+                        pick_[r][p] = (int8_t)i;
+                    }
+                }
+            }
     }
+    // Time of a stretch of `steps` with parity p; kNever when there is none.
+    float cost(int64_t steps, int p) const
+    {
+        int64_t k;
+        const int r = tail(steps, &k);
+        return (float)k * opt_[long_].us + cost_[r][p ^ (flips(long_) ? (int)(k & 1) : 0)];
+    }
+    void plan(int64_t steps, int p, std::vector<Launch>& out) const
+    {
+        int64_t k;
+        int r = tail(steps, &k);
+        for (int64_t i = 0; i < k; ++i) out.push_back(Launch{(uint8_t)opt_[long_].steps, &opt_[long_]});
+        p ^= flips(long_) ? (int)(k & 1) : 0;
+        while (r > 0) {
+            const int i = pick_[r][p];
+            out.push_back(Launch{(uint8_t)opt_[i].steps, &opt_[i]});
+            r -= opt_[i].steps;
+            p ^= flips(i) ? 1 : 0;
+        }
+    }
+    static constexpr float kNever = 1e30f;
+
+private:
+    static constexpr int kMax = 64;
+    bool flips(int i) const { return opt_[i].blk || opt_[i].steps > 1; }
+    void add(const PassChoice& c) { opt_[n_++] = c; }
+    // Steps left for the table after k launches of the length that is
+    // fastest per step.
+    int tail(int64_t steps, int64_t* k) const
+    {
+        *k = steps > kMax ? (steps - kMax + opt_[long_].steps - 1) / opt_[long_].steps : 0;
+        return (int)(steps - *k * opt_[long_].steps);
+    }
+    PassChoice opt_[kBlkSteps + 1];
+    int n_ = 0, long_ = 0;
+    float cost_[kMax + 1][2];
+    int8_t pick_[kMax + 1][2];
 };
 
 // The launches of nsteps steps from n0, no launch with a recorded state
 // (n % K == 0, K > 0) strictly inside it and an even number of them moving
-// phi_dot: plan_passes' plan, of which 2D runs with multi-step passes (T > 1)
-// keep the passes that compute a record's diagnostics (`records`: those that
-// start at a recorded state; their length decides the order of a record's
-// sums) and take the steps between them in block passes, which cover up to
-// kBlkSteps steps: each stretch in the number of equal launches estimated
-// fastest.
+// phi_dot: plan_passes' plan, of which, given `st`, the passes that compute a
+// record's diagnostics stay (`records`: those that start at a recorded state;
+// their length decides the order of a record's sums) and the steps between
+// them run in the launches of `st`.
 std::vector<Launch> plan_launches(const Geometry& g, const Tiling& t, int64_t cap, int64_t n0, int64_t nsteps, int T,
-                                  int64_t K, bool records, BlkTable& table)
+                                  int64_t K, bool records, const Stretches* st)
 {
     std::vector<Launch> out;
-    const bool blocks = T > 1 && blk_supported(g);
-    int64_t n = n0, left = 0;      // steps of the current stretch without a record
-    size_t flips = 0;
-    auto add = [&](int64_t steps, bool blk) {
-        out.push_back(Launch{(uint8_t)steps, blk});
-        flips += out.back().flips() ? 1 : 0;
+    const std::vector<uint8_t> plan = plan_passes(g, t, cap, n0, nsteps, T, K);
+    if (!st) {
+        for (uint8_t L : plan) out.push_back(Launch{L, nullptr});
+        return out;
+    }
+    struct Part {
+        int64_t steps;
+        bool kept;      // a pass of the plan, else a stretch
+        int p;          // parity of a stretch
     };
+    std::vector<Part> parts;
+    int odd = 0;
+    int64_t n = n0, left = 0;
     auto stretch = [&]() {
-        // long stretches in launches of the fastest length per step, the
-        // rest split evenly
-        while (left > 4 * kBlkSteps) {
-            int best = kBlkSteps;
-            for (int L = kBlkSteps / 2; L <= kBlkSteps; ++L)
-                if (table.get(g, L).us * best < table.get(g, best).us * L) best = L;
-            add(best, true);
-            left -= best;
-        }
         if (left == 0) return;
-        int64_t m = 0;
-        double least = 0.0;
-        for (int64_t c = (left + kBlkSteps - 1) / kBlkSteps; c <= left && c <= 8; ++c) {
-            const int lo = (int)(left / c), more = (int)(left % c);
-            const double us = (c - more) * (double)table.get(g, lo).us +
-                              (more > 0 ? more * (double)table.get(g, lo + 1).us : 0.0);
-            if (m == 0 || us < least) {
-                m = c;
-                least = us;
-            }
-        }
-        for (int64_t i = 0; i < m; ++i) add(left / m + (i < left % m ? 1 : 0), true);
+        const int p = st->cost(left, 1) < st->cost(left, 0) ? 1 : 0;
+        parts.push_back(Part{left, false, p});
+        odd ^= p;
         left = 0;
     };
-    for (uint8_t L : plan_passes(g, t, cap, n0, nsteps, T, K)) {
+    for (uint8_t L : plan) {
         const bool recorded = K > 0 && n % K == 0;
-        if (!blocks || (recorded && records)) {
-            stretch();
-            add(L, false);
+        if (recorded) stretch();          // no launch across a recorded (checkpointed) state
+        if (recorded && records) {
+            parts.push_back(Part{L, true, 0});
+            odd ^= L > 1 ? 1 : 0;
         } else {
-            if (recorded) stretch();      // no launch across a recorded (checkpointed) state
             left += L;
         }
         n += L;
     }
     stretch();
-    if (flips % 2 == 1) {
-        // one too many: halve the last block pass of several steps, or run a
-        // one-step block pass as a single step (without block passes the
-        // plan is even)
-        auto several = [](const Launch& l) { return l.blk && l.steps > 1; };
-        auto it = std::find_if(out.rbegin(), out.rend(), several);
-        if (it != out.rend()) {
-            const Launch l = *it;
-            it->steps = (uint8_t)(l.steps - l.steps / 2);
-            out.insert(it.base(), Launch{(uint8_t)(l.steps / 2), true});
-        } else {
-            it = std::find_if(out.rbegin(), out.rend(), [](const Launch& l) { return l.blk; });
-            if (it != out.rend()) it->blk = false;
+    if (odd) {
+        // the stretch whose other parity costs least (the plan's own launches
+        // are even in number, so there is one)
+        Part* best = nullptr;
+        float least = Stretches::kNever;
+        for (Part& x : parts) {
+            if (x.kept) continue;
+            const float d = st->cost(x.steps, x.p ^ 1) - st->cost(x.steps, x.p);
+            if (d < least) {
+                least = d;
+                best = &x;
+            }
         }
+        if (!best) {
+            for (uint8_t L : plan) out.push_back(Launch{L, nullptr});
+            return out;
+        }
+        best->p ^= 1;
+    }
+    for (const Part& x : parts) {
+        if (x.kept) out.push_back(Launch{(uint8_t)x.steps, nullptr});
+        else st->plan(x.steps, x.p, out);
     }
     return out;
 }
@@ -292,7 +345,9 @@ struct prs_ctx {
     Tiling rec_til;    // tiling and steps per pass of the adjoint's recomputation
     int32_t rec_tblock;   // (0: those of the forward)
     int32_t tblock;    // steps per pass (1: single steps)
-    mutable BlkTable blk;
+    bool own;          // tiling or steps per pass were set (by the caller or the tuner)
+    bool adj_own;      // the same of the reverse sweep
+    mutable std::unique_ptr<Stretches> stretches;   // made on first use
     hipStream_t stream;
     int64_t step;
     // adjoint bookkeeping between prs_adjoint_forward and _backward
@@ -316,6 +371,14 @@ struct prs_ctx {
 };
 
 namespace {
+
+// Stretches serve 2D multi-step runs and 3D runs whose settings are the
+// library's; a tuned or set 3D run keeps its tiling and pass length.
+bool use_stretches(const Geometry& g, int T, bool own)
+{
+    if (!tb_supported(g)) return false;
+    return g.ndim == 2 ? T > 1 && blk_supported(g) : !own;
+}
 
 // a(eta_n)^beta with a(eta) = (eta/eta0)^m: the scale-factor power of the
 // force of Eq. (2) at step n; exactly 1 for the PRS choice beta = 0.
@@ -421,6 +484,34 @@ int64_t partial_entries(int64_t cap)
     return std::max<int64_t>(cap, std::min<int64_t>(kFinBatch * cap, (int64_t)((2u << 20) / sizeof(WavePartial))));
 }
 
+int pass_steps(const prs_ctx* c) { return tb_supported(c->geo) ? c->tblock : 1; }
+
+// The launches of the steps between records, or NULL: passes of the run's
+// tiling and length there too.
+const Stretches* run_stretches(const prs_ctx* c)
+{
+    if (!use_stretches(c->geo, pass_steps(c), c->own)) return nullptr;
+    if (!c->stretches) c->stretches.reset(new (std::nothrow) Stretches(c->geo));
+    return c->stretches.get();
+}
+
+// Enqueues one launch of a run without diagnostics.  `coef(i)` gives the
+// coefficients of its i-th step.
+template <typename Coef>
+hipError_t enqueue(const Launch& l, const Geometry& g, const Tiling& til, const void* phi_in, void* phi_out,
+                   const void* pi_in, void* pi_out, Coef coef, hipStream_t s)
+{
+    static_assert(kBlkSteps >= kMaxPassSteps, "room for a marching pass's coefficients");
+    StepCoef64 k[kBlkSteps];
+    for (int i = 0; i < l.steps; ++i) k[i] = coef(i);
+    const Tiling& t = l.choice ? l.choice->til : til;
+    if (l.choice && l.choice->blk)
+        return launch_blk2d(l.steps, BlkShape{t.vec, t.rows, t.ty, 0.0f}, g, phi_in, phi_out, pi_in, pi_out, k, s);
+    if (l.steps > 1)
+        return launch_tb(l.steps, g, t, phi_in, phi_out, pi_in, pi_out, k, false, nullptr, DiagCoef{}, s);
+    return launch_step(g, t, phi_in, phi_out, pi_in, pi_out, k[0], true, false, nullptr, DiagCoef{}, s);
+}
+
 prs_status flush(prs_ctx* c, int64_t count, prs_stats* dst)
 {
     if (count == 0) return PRS_OK;
@@ -511,13 +602,12 @@ prs_status prs_step_n(prs_ctx* c, int64_t nsteps, prs_stats* series, int64_t cap
         prs_status st = check_stable_until(c->p, c->V0, c->step + nsteps - 1);
         if (st != PRS_OK) return st;
     }
-    const TileCounts tc = tile_counts(c->geo, c->til);
+    const int T = pass_steps(c);
+    const Stretches* between = run_stretches(c);
     const int64_t K = c->p.diag_every;
     RecordQueue queue{c->partials, c->partial_total, area_scale(c->p)};
-
-    const int T = tb_supported(c->geo) ? c->tblock : 1;
     const std::vector<Launch> plan = plan_launches(c->geo, c->til, c->partial_cap, c->step, nsteps, T, want ? K : 0,
-                                                   want, c->blk);
+                                                   want, between);
 
     void* pi_cur = c->pi;
     void* pi_oth = c->pi_alt;
@@ -531,7 +621,7 @@ prs_status prs_step_n(prs_ctx* c, int64_t nsteps, prs_stats* series, int64_t cap
         const int64_t n = c->step;
         const bool diag = want && (n % K == 0);
         if (c->lt_on) {
-            const bool dom = !diag && (l.blk || L == T);
+            const bool dom = !diag && (between ? l.flips() : L == T);
             if (dom && !open) {
                 if (2 * spans + 2 > c->lt_ev.size()) {
                     for (int j = 0; j < 2; ++j) {
@@ -553,30 +643,27 @@ prs_status prs_step_n(prs_ctx* c, int64_t nsteps, prs_stats* series, int64_t cap
         }
         WavePartial* parts = nullptr;
         if (diag) {
-            const int64_t ntiles = L > 1 ? tb_tiles(c->geo, c->til, L) : tc.ntiles;
+            const int64_t ntiles = L > 1 ? tb_tiles(c->geo, c->til, L) : tile_counts(c->geo, c->til).ntiles;
             HIP_TRY(queue.add(ntiles, c->hrec + pending, n, c->p.eta0 + (double)n * c->p.deta, c->stream, &parts),
                     "finalize launch");
         }
-        const DiagCoef dc = diag_coef(c, n);
-        if (l.blk) {
-            StepCoef64 k[kBlkSteps];
-            for (int i = 0; i < L; ++i) k[i] = coef_for(c, n + i);
-            HIP_TRY(launch_blk2d(L, c->blk.get(c->geo, L), c->geo, c->phi[c->cur], c->phi[c->cur ^ 1], pi_cur, pi_oth,
-                                 k, c->stream),
-                    "block pass launch");
-            std::swap(pi_cur, pi_oth);
+        void* pi_out = l.flips() ? pi_oth : pi_cur;
+        if (!diag) {
+            HIP_TRY(enqueue(l, c->geo, c->til, c->phi[c->cur], c->phi[c->cur ^ 1], pi_cur, pi_out,
+                            [&](int i) { return coef_for(c, n + i); }, c->stream),
+                    "pass launch");
         } else if (L > 1) {
             StepCoef64 k[kMaxPassSteps];
             for (int i = 0; i < L; ++i) k[i] = coef_for(c, n + i);
-            HIP_TRY(launch_tb(L, c->geo, c->til, c->phi[c->cur], c->phi[c->cur ^ 1], pi_cur, pi_oth, k, diag,
-                                parts, dc, c->stream),
+            HIP_TRY(launch_tb(L, c->geo, c->til, c->phi[c->cur], c->phi[c->cur ^ 1], pi_cur, pi_out, k, true, parts,
+                              diag_coef(c, n), c->stream),
                     "multi-step kernel launch");
-            std::swap(pi_cur, pi_oth);
         } else {
-            HIP_TRY(launch_step(c->geo, c->til, c->phi[c->cur], c->phi[c->cur ^ 1], pi_cur, pi_cur,
-                                coef_for(c, n), true, diag, parts, dc, c->stream),
+            HIP_TRY(launch_step(c->geo, c->til, c->phi[c->cur], c->phi[c->cur ^ 1], pi_cur, pi_out, coef_for(c, n),
+                                true, true, parts, diag_coef(c, n), c->stream),
                     "step kernel launch");
         }
+        if (l.flips()) std::swap(pi_cur, pi_oth);
         if (diag && ++pending == kRecCap) {
             HIP_TRY(queue.reduce(c->stream), "finalize launch");
             prs_status st = flush(c, pending, series + written);
@@ -650,6 +737,7 @@ prs_status prs_set_time_blocking(prs_ctx* c, int32_t steps_per_pass)
         return fail(PRS_EINVAL, "no %d-step pass kernel for this lattice (2D: 2, 3, 4, 6, 8; "
                     "3D: 2, 3, 4)", steps_per_pass);
     c->tblock = steps_per_pass;
+    c->own = true;
     return PRS_OK;
 }
 
@@ -657,10 +745,10 @@ prs_status prs_plan_passes(const prs_ctx* c, int64_t nsteps, int32_t with_record
                            int64_t* single_passes)
 {
     if (!c || nsteps < 0) return fail(PRS_EINVAL, "invalid arguments");
-    const int T = tb_supported(c->geo) ? c->tblock : 1;
     const int64_t K = (with_records && c->p.diag_every > 0) ? c->p.diag_every : 0;
     int64_t m = 0, n1 = 0;
-    for (const Launch& l : plan_launches(c->geo, c->til, c->partial_cap, c->step, nsteps, T, K, K > 0, c->blk))
+    for (const Launch& l : plan_launches(c->geo, c->til, c->partial_cap, c->step, nsteps, pass_steps(c), K, K > 0,
+                                         run_stretches(c)))
         (l.flips() ? m : n1) += 1;
     if (multi_passes) *multi_passes = m;
     if (single_passes) *single_passes = n1;
@@ -722,6 +810,7 @@ prs_status prs_set_tiling(prs_ctx* c, int32_t vec, int32_t rows, int32_t ty)
         return fail(PRS_EINVAL, "tiling has more wave tiles than the workspace holds (rows >= %lld)",
                     (long long)kMinRows);
     c->til = t;
+    c->own = true;
     return PRS_OK;
 }
 
@@ -735,6 +824,7 @@ prs_status prs_set_adjoint_tiling(prs_ctx* c, int32_t vec, int32_t rows, int32_t
         return fail(PRS_EINVAL, "tiling has more wave tiles than the workspace holds (rows >= %lld)",
                     (long long)kMinRows);
     c->adj_til = t;
+    c->adj_own = true;
     return PRS_OK;
 }
 
@@ -890,6 +980,7 @@ prs_status prs_set_adjoint_time_blocking(prs_ctx* c, int32_t steps_per_pass)
     if (steps_per_pass < 1 || steps_per_pass > kMaxPassSteps)
         return fail(PRS_EINVAL, "steps per pass must be 1 .. %d", kMaxPassSteps);
     c->adj_tblock = steps_per_pass;
+    c->adj_own = true;
     return PRS_OK;
 }
 
@@ -1106,11 +1197,11 @@ prs_status prs_adjoint_forward(prs_ctx* c, int64_t nsteps, int32_t ckpt_every, v
             "checkpoint copy");
     HIP_TRY(hipMemcpyAsync(at<char>(work, L.ck_pi), c->pi, bytes, hipMemcpyDeviceToDevice, c->stream),
             "checkpoint copy");
-    const int T = tb_supported(c->geo) ? c->tblock : 1;
     const void* phi_in = c->phi[c->cur];
     const void* pi_in = c->pi;
     int64_t k = 0;
-    for (const Launch& l : plan_launches(c->geo, c->til, c->partial_cap, 0, nsteps, T, L.K, false, c->blk)) {
+    for (const Launch& l : plan_launches(c->geo, c->til, c->partial_cap, 0, nsteps, pass_steps(c), L.K, false,
+                                         run_stretches(c))) {
         const int Lp = l.steps;
         const int64_t n = n0 + k;
         const bool ck = (k + Lp) % L.K == 0 && k + Lp < nsteps;   // ends on checkpoint (k+Lp)/K
@@ -1125,22 +1216,9 @@ prs_status prs_adjoint_forward(prs_ctx* c, int64_t nsteps, int32_t ckpt_every, v
             if (l.flips()) pi_out = pi_in == c->pi ? c->pi_alt : c->pi;
             else pi_out = (pi_in == c->pi || pi_in == c->pi_alt) ? const_cast<void*>(pi_in) : c->pi;
         }
-        if (l.blk) {
-            StepCoef64 kk[kBlkSteps];
-            for (int i = 0; i < Lp; ++i) kk[i] = coef_for(c, n + i);
-            HIP_TRY(launch_blk2d(Lp, c->blk.get(c->geo, Lp), c->geo, phi_in, phi_out, pi_in, pi_out, kk, c->stream),
-                    "block pass launch");
-        } else if (Lp > 1) {
-            StepCoef64 kk[kMaxPassSteps];
-            for (int i = 0; i < Lp; ++i) kk[i] = coef_for(c, n + i);
-            HIP_TRY(launch_tb(Lp, c->geo, c->til, phi_in, phi_out, pi_in, pi_out, kk, false, nullptr, DiagCoef{},
-                              c->stream),
-                    "multi-step kernel launch");
-        } else {
-            HIP_TRY(launch_step(c->geo, c->til, phi_in, phi_out, pi_in, pi_out, coef_for(c, n), true, false,
-                                nullptr, DiagCoef{}, c->stream),
-                    "step kernel launch");
-        }
+        HIP_TRY(enqueue(l, c->geo, c->til, phi_in, phi_out, pi_in, pi_out, [&](int j) { return coef_for(c, n + j); },
+                        c->stream),
+                "pass launch");
         if (phi_out == c->phi[c->cur ^ 1]) c->cur ^= 1;
         phi_in = phi_out;
         pi_in = pi_out;
@@ -1230,17 +1308,33 @@ prs_status prs_adjoint_backward(prs_ctx* c, void* work, size_t work_bytes, void*
     const int64_t n0 = c->adj_n0;
     const size_t bytes = field_bytes(c->p);
     // the recomputation: its own tuned tiling and pass length, else the forward's
-    const Tiling rt = c->rec_tblock > 0 ? c->rec_til : c->til;
-    const int T = tb_supported(c->geo) ? (c->rec_tblock > 0 ? c->rec_tblock : c->tblock) : 1;
-    const int TA = tb_supported(c->geo) ? c->adj_tblock : 1;
+    Tiling rt = c->rec_tblock > 0 ? c->rec_til : c->til;
+    int T = tb_supported(c->geo) ? (c->rec_tblock > 0 ? c->rec_tblock : c->tblock) : 1;
+    Tiling at_til = c->adj_til;
+    int TA = tb_supported(c->geo) ? c->adj_tblock : 1;
+    // what neither the caller nor the tuner set is chosen by the lattice's size
+    if (tb_supported(c->geo) && !c->adj_own) at_til = auto_adj_tile(c->geo, &TA);
+    if (tb_supported(c->geo) && !c->own && c->rec_tblock == 0) {
+        if (c->geo.ndim == 2) {
+            T = kMaxPassSteps;
+            rt = auto_tile2(c->geo, T);
+        } else {
+            const PassChoice pc = auto_pass3(c->geo, 4);
+            if (pc.til.vec) {
+                T = 4;
+                rt = pc.til;
+                rt.rows = std::max<int>(rt.rows, (int)kMinRows);
+            }
+        }
+    }
     // The fused scheme (2D): per segment the recomputation keeps only the
     // states at the starts of the reverse passes (TF steps apart, the last
     // pass may be shorter), and each reverse pass recomputes its fields from
     // its pass-start state.  Else every step's field is recomputed and stored.
     const int TF = std::min(TA, 4);
     const bool fused = c->adj_scheme == PRS_ADJ_FUSED && c->geo.ndim == 2 && tb_supported(c->geo) && TF >= 2 &&
-                       tbf_supported(c->geo, c->adj_til, TF) &&
-                       tbf_tiles(c->geo, c->adj_til, TF) <= c->partial_cap &&
+                       tbf_supported(c->geo, at_til, TF) &&
+                       tbf_tiles(c->geo, at_til, TF) <= c->partial_cap &&
                        tb_pass_supported(c->geo, rt, TF);
     double* gacc = at<double>(work, L.gacc);
     HIP_TRY(launch_zero_f64(gacc, c->partial_cap, c->stream), "zero launch");
@@ -1341,12 +1435,12 @@ prs_status prs_adjoint_backward(prs_ctx* c, void* work, size_t work_bytes, void*
                     AdjCoef64 cc[kMaxPassSteps];
                     for (int i = 0; i + 1 < Lq; ++i) kk[i] = coef_for(c, st + i);
                     for (int k = 1; k <= Lq; ++k) cc[k - 1] = adj_coef(c, st + Lq - k, st + Lq - k == n0);
-                    HIP_TRY(launch_tbf(Lq, c->geo, c->adj_til, pass_start(sg, q, false), pass_start(sg, q, true),
+                    HIP_TRY(launch_tbf(Lq, c->geo, at_til, pass_start(sg, q, false), pass_start(sg, q, true),
                                        wcur, wnxt, mu, mu_oth, gacc, kk, cc, c->stream),
                             "adjoint launch");
                     std::swap(mu, mu_oth);
                 } else {
-                    HIP_TRY(launch_adjoint(c->geo, c->adj_til, wcur, wnxt, mu, pass_start(sg, q, false), gacc,
+                    HIP_TRY(launch_adjoint(c->geo, at_til, wcur, wnxt, mu, pass_start(sg, q, false), gacc,
                                            adj_coef(c, st, st == n0), c->stream),
                             "adjoint launch");
                 }
@@ -1357,7 +1451,7 @@ prs_status prs_adjoint_backward(prs_ctx* c, void* work, size_t work_bytes, void*
         char* ckphi = at<char>(work, L.ck_phi + L.fb * sg);
         auto phi_at = [&](int64_t j) -> const void* { return j == 0 ? ckphi : seg_at(sg, j); };   // phi^{ns+j}
         for (int64_t k = len - 1; k >= 0;) {
-            const int Lp = adj_pass_len(c->geo, c->adj_til, c->partial_cap, TA, k + 1, true);
+            const int Lp = adj_pass_len(c->geo, at_til, c->partial_cap, TA, k + 1, true);
             if (Lp > 1) {
                 const void* phis[kMaxPassSteps];
                 AdjCoef64 cc[kMaxPassSteps];
@@ -1365,11 +1459,11 @@ prs_status prs_adjoint_backward(prs_ctx* c, void* work, size_t work_bytes, void*
                     phis[i] = phi_at(k - i);
                     cc[i] = adj_coef(c, ns + k - i, ns + k - i == n0);
                 }
-                HIP_TRY(launch_tba(Lp, c->geo, c->adj_til, wcur, wnxt, mu, mu_oth, phis, gacc, cc, c->stream),
+                HIP_TRY(launch_tba(Lp, c->geo, at_til, wcur, wnxt, mu, mu_oth, phis, gacc, cc, c->stream),
                         "adjoint launch");
                 std::swap(mu, mu_oth);
             } else {
-                HIP_TRY(launch_adjoint(c->geo, c->adj_til, wcur, wnxt, mu, phi_at(k), gacc,
+                HIP_TRY(launch_adjoint(c->geo, at_til, wcur, wnxt, mu, phi_at(k), gacc,
                                        adj_coef(c, ns + k, ns + k == n0), c->stream),
                         "adjoint launch");
             }
@@ -1450,6 +1544,8 @@ struct prs_batch {
     std::vector<Geometry> geo;
     std::vector<Tiling> til;
     std::vector<int32_t> tblock;        // steps per pass (1: single steps)
+    std::vector<uint8_t> own;           // tiling or steps per pass were set
+    std::vector<std::unique_ptr<Stretches>> stretches;   // made on first use
     std::vector<int64_t> npasses;       // per item, including the final record pass (persistent modes)
     std::vector<int64_t> nlaunches;     // the same of the stream modes, as last enqueued
     int ran;                            // what ran last: 0 nothing, 1 a persistent mode, 2 a stream mode
@@ -1490,7 +1586,7 @@ namespace {
 
 struct PassEntry {
     int32_t first, steps, rec, alt;
-    bool blk;
+    Launch launch;
 };
 
 struct BatchLayout {
@@ -1582,26 +1678,23 @@ prs_status batch_layout(const prs_batch_item* items, int32_t count, BatchLayout&
 // per pass, no recorded state inside a pass, an even number of multi-step
 // passes so phi_dot ends in the caller's buffer), then the diagnostics-only
 // pass of the final state.
-// The persistent modes take marching passes only (table: NULL), the stream
+// The persistent modes take marching passes only (st: NULL), the stream
 // modes a single run's launches.
 std::vector<PassEntry> batch_plan(const prs_batch_item& it, const Geometry& g, const Tiling& t, int64_t cap, int T,
-                                  BlkTable* table)
+                                  const Stretches* st)
 {
     const int64_t S = it.nsteps, K = it.p.diag_every;
-    std::vector<Launch> plan;
-    if (table) plan = plan_launches(g, t, cap, 0, S, T, K, K > 0, *table);
-    else
-        for (uint8_t L : plan_passes(g, t, cap, 0, S, T, K)) plan.push_back(Launch{L, false});
+    const std::vector<Launch> plan = plan_launches(g, t, cap, 0, S, T, K, K > 0, st);
     std::vector<PassEntry> out;
     int64_t n = 0, rec = 0;
     int alt = 0;
     for (const Launch& l : plan) {
         const bool r = K > 0 && n % K == 0;
-        out.push_back(PassEntry{(int32_t)n, (int32_t)l.steps, r ? (int32_t)rec++ : -1, alt, l.blk});
+        out.push_back(PassEntry{(int32_t)n, (int32_t)l.steps, r ? (int32_t)rec++ : -1, alt, l});
         if (l.flips()) alt ^= 1;
         n += l.steps;
     }
-    out.push_back(PassEntry{(int32_t)S, 0, (int32_t)rec, alt, false});   // final state
+    out.push_back(PassEntry{(int32_t)S, 0, (int32_t)rec, alt, Launch{0, nullptr}});   // final state
     return out;
 }
 
@@ -1656,16 +1749,21 @@ struct ItemCursor {
     std::vector<PassEntry> plan;
     size_t next;
     prs_ctx coef;            // parameters for the coefficient schedule
-    BlkTable blk;
     RecordQueue queue;
 };
+
+const Stretches* batch_stretches(prs_batch* b, int32_t r)
+{
+    if (!use_stretches(b->geo[r], b->tblock[r], b->own[r])) return nullptr;
+    if (!b->stretches[r]) b->stretches[r].reset(new (std::nothrow) Stretches(b->geo[r]));
+    return b->stretches[r].get();
+}
 
 prs_status batch_item_begin(prs_batch* b, int32_t r, ItemCursor& cur, hipStream_t s)
 {
     const prs_batch_item& it = b->items[r];
     cur.item = r;
-    cur.blk = BlkTable{};
-    cur.plan = batch_plan(it, b->geo[r], b->til[r], b->part_cap[r], b->tblock[r], &cur.blk);
+    cur.plan = batch_plan(it, b->geo[r], b->til[r], b->part_cap[r], b->tblock[r], batch_stretches(b, r));
     b->nlaunches[r] = (int64_t)cur.plan.size();
     cur.next = 0;
     cur.queue = RecordQueue{reinterpret_cast<WavePartial*>(static_cast<char*>(b->ws) + b->off_part + b->part_off[r]),
@@ -1708,24 +1806,23 @@ prs_status batch_item_pass(prs_batch* b, ItemCursor& cur, hipStream_t s)
     const DiagCoef dc = diag_coef(&cur.coef, n);
     void* phi_in = phi[idx & 1];
     void* phi_out = phi[(idx + 1) & 1];
-    if (e.blk) {
-        StepCoef64 k[kBlkSteps];
-        for (int i = 0; i < e.steps; ++i) k[i] = coef_for(&cur.coef, n + i);
-        HIP_TRY(launch_blk2d(e.steps, cur.blk.get(g, e.steps), g, phi_in, phi_out, pi_now, pi_next, k, s),
-                "block pass launch");
-    } else if (e.steps > 1) {
-        StepCoef64 k[kMaxPassSteps];
-        for (int i = 0; i < e.steps; ++i) k[i] = coef_for(&cur.coef, n + i);
-        HIP_TRY(launch_tb(e.steps, g, t, phi_in, phi_out, pi_now, pi_next, k, diag, parts, dc, s),
-                "multi-step kernel launch");
-    } else if (e.steps == 1) {
-        HIP_TRY(launch_step(g, t, phi_in, phi_out, pi_now, pi_now, coef_for(&cur.coef, n), true, diag, parts, dc,
-                            s),
-                "step kernel launch");
-    } else {
+    void* pi_out = e.launch.flips() ? pi_next : pi_now;
+    if (e.steps == 0) {
         HIP_TRY(launch_step(g, t, phi_in, nullptr, pi_now, nullptr, coef_for(&cur.coef, n), false, true, parts, dc,
                             s),
                 "diagnostics kernel launch");
+    } else if (!diag) {
+        HIP_TRY(enqueue(e.launch, g, t, phi_in, phi_out, pi_now, pi_out,
+                        [&](int i) { return coef_for(&cur.coef, n + i); }, s),
+                "pass launch");
+    } else if (e.steps > 1) {
+        StepCoef64 k[kMaxPassSteps];
+        for (int i = 0; i < e.steps; ++i) k[i] = coef_for(&cur.coef, n + i);
+        HIP_TRY(launch_tb(e.steps, g, t, phi_in, phi_out, pi_now, pi_out, k, true, parts, dc, s),
+                "multi-step kernel launch");
+    } else {
+        HIP_TRY(launch_step(g, t, phi_in, phi_out, pi_now, pi_out, coef_for(&cur.coef, n), true, true, parts, dc, s),
+                "step kernel launch");
     }
     // the final state's record is the plan's last entry
     if (cur.next == cur.plan.size()) HIP_TRY(cur.queue.reduce(s), "finalize launch");
@@ -2065,6 +2162,8 @@ prs_status prs_batch_create(const prs_batch_item* items, int32_t count, void* wo
     b->total_recs = L.rec_off[count];
     b->npasses.assign(count, 0);
     b->nlaunches.assign(count, 0);
+    b->own.assign(count, 0);
+    b->stretches.resize(count);
     b->ran = 0;
     for (int32_t r = 0; r < count; ++r) {
         b->geo.push_back(geometry_of(items[r].p));
@@ -2102,6 +2201,7 @@ prs_status prs_batch_set_tiling(prs_batch* b, int32_t item, int32_t vec, int32_t
     if (item_tiles_max(b->geo[item], t, std::max(2, b->tblock[item])) > b->part_cap[item])
         return fail(PRS_EINVAL, "tiling has more wave tiles than the workspace holds");
     b->til[item] = t;
+    b->own[item] = 1;
     batch_release_graph(b);
     b->dirty = true;
     return PRS_OK;
@@ -2121,6 +2221,7 @@ prs_status prs_batch_set_time_blocking(prs_batch* b, int32_t item, int32_t steps
     if (item_tiles_max(b->geo[item], b->til[item], std::max(2, steps_per_pass)) > b->part_cap[item])
         return fail(PRS_EINVAL, "steps per pass need more wave tiles than the workspace holds");
     b->tblock[item] = steps_per_pass;
+    b->own[item] = 1;
     batch_release_graph(b);
     b->dirty = true;
     return PRS_OK;
@@ -2161,10 +2262,11 @@ prs_status prs_batch_state(const prs_batch* b, int32_t item, void** phi, void** 
     // changed since
     int64_t np = b->ran == 1 ? b->npasses[item] : b->ran == 2 ? b->nlaunches[item] : 0;
     if (np == 0) {
-        BlkTable table;
-        np = (int64_t)batch_plan(it, b->geo[item], b->til[item], b->part_cap[item], b->tblock[item],
-                                 persistent_mode(b->mode) ? nullptr : &table)
-                 .size();
+        const bool streams = !persistent_mode(b->mode);
+        std::unique_ptr<Stretches> st;
+        if (streams && use_stretches(b->geo[item], b->tblock[item], b->own[item]))
+            st.reset(new (std::nothrow) Stretches(b->geo[item]));
+        np = (int64_t)batch_plan(it, b->geo[item], b->til[item], b->part_cap[item], b->tblock[item], st.get()).size();
     }
     if (phi) *phi = ((np - 1) & 1) ? it.phi_b : it.phi_a;
     if (dphi) *dphi = it.dphi;
@@ -2284,7 +2386,8 @@ prs_status prs_batch_autotune(prs_batch* b, double* best_ms)
             const Geometry& h = b->geo[q];
             const Tiling& u = b->til[q];
             if (h.ndim == g.ndim && h.f64 == g.f64 && h.nx == g.nx && h.Q == g.Q && h.M == g.M && u.vec == t.vec &&
-                u.rows == t.rows && u.ty == t.ty && b->tblock[q] == b->tblock[r]) {
+                u.rows == t.rows && u.ty == t.ty && b->tblock[q] == b->tblock[r] &&
+                b->own[q] == b->own[r]) {
                 G.items.push_back(r);
                 G.work += work;
                 placed = true;
@@ -2307,10 +2410,11 @@ prs_status prs_batch_autotune(prs_batch* b, double* best_ms)
             if (persistent && !ens_supported(g, t, T)) return false;
             return item_tiles_max(g, t, std::max(2, T)) <= b->part_cap[q];
         };
-        auto apply = [&](const Tiling& t, int T) {
+        auto apply = [&](const Tiling& t, int T, uint8_t own) {
             for (int32_t r : G.items) {
                 b->til[r] = t;
                 b->tblock[r] = T;
+                b->own[r] = own;
             }
             batch_release_graph(b);
             b->dirty = true;
@@ -2318,6 +2422,7 @@ prs_status prs_batch_autotune(prs_batch* b, double* best_ms)
         for (;;) {
             const Tiling cur = b->til[q];
             const int T = b->tblock[q];
+            const uint8_t own = b->own[q];
             // candidates: the marching tile doubled (up to the tuner's
             // longest, 128, and not past the lattice); in 3D, when the
             // current tiling is a workgroup-stacked one, the other
@@ -2339,11 +2444,11 @@ prs_status prs_batch_autotune(prs_batch* b, double* best_ms)
             double round_best = 1e300;
             size_t pick = cand.size();
             for (size_t c = 0; c < cand.size(); ++c) {
-                apply(cand[c].first, cand[c].second);
+                apply(cand[c].first, cand[c].second, 1);
                 double ms = 0.0;
                 st = time_runs(&ms);
                 if (st != PRS_OK) {
-                    apply(cur, T);
+                    apply(cur, T, own);
                     return st;
                 }
                 if (ms < round_best) {
@@ -2353,11 +2458,11 @@ prs_status prs_batch_autotune(prs_batch* b, double* best_ms)
             }
             // a change must gain more than the runs' spread to be kept
             if (pick < cand.size() && round_best < best * 0.98) {
-                apply(cand[pick].first, cand[pick].second);
+                apply(cand[pick].first, cand[pick].second, 1);
                 best = round_best;
                 continue;
             }
-            apply(cur, T);
+            apply(cur, T, own);
             break;
         }
     }
@@ -2754,6 +2859,7 @@ prs_status autotune_adjoint(prs_ctx* c, const char* cache_path, int32_t flags, v
     if (e != hipSuccess) return hip_fail(e, "adjoint autotune");
     c->adj_til = best;
     c->adj_tblock = best_T;
+    c->adj_own = true;
     if (best_us) *best_us = best_t * 1e3;
     if (cache_path && cache_path[0]) {
         cache[key] = TuneEntry{best.vec, best.rows, best.ty, best_T, best_t * 1e3};
@@ -2896,6 +3002,7 @@ prs_status prs_autotune(prs_ctx* c, const char* cache_path, int32_t flags, void*
     if (result != PRS_OK) return result;
     c->til = best;
     c->tblock = best_T;
+    c->own = true;
     if (best_us) *best_us = best_t * 1e3;
     if (cache_path && cache_path[0]) {
         cache[key] = TuneEntry{best.vec, best.rows, best.ty, best_T, best_t * 1e3};

@@ -1661,7 +1661,7 @@ __device__ __forceinline__ R row_nsum(const R* cc, R left, R right, int j, R ym,
 
 template <int VEC, int T, bool UNIT, bool CHECK, int U, typename R>
 __device__ __forceinline__ void tbf_iter(const TBFArgs<T, R>& A, const TBLane& L, int32_t i, int32_t last,
-                                         int32_t n_out, TBFRows& rw, TBFState<VEC, T, R>& S, R (&g32)[T])
+                                         int32_t n_out, TBFRows& rw, TBFState<VEC, T, R>& S, double (&gs)[T])
 {
     constexpr int R0 = tbf_ring0(T);
     // prefetch for the next iteration: phi^s row y+1, phi_dot row y, w_in row
@@ -1747,7 +1747,8 @@ __device__ __forceinline__ void tbf_iter(const TBFArgs<T, R>& A, const TBLane& L
             const R pq = adj_site_pq<UNIT>(cc[e], row_nsum<VEC>(cc, left, right, e, cm[e], cp[e]), mp[e], ph[e],
                                            A.a[k - 1], A.b[k - 1], A.cw[k - 1], A.F[k - 1], A.kc, A.inv_dx2,
                                            out_w[e], out_mu[e]);
-            if (own_row) g32[k - 1] = fmar(cc[e], pq, g32[k - 1]);
+            const R term = cc[e] * pq;                 // w phi (kc phi^2 - 1), as k_adjoint rounds it
+            if (own_row) gs[k - 1] += (double)term;
         }
         if (k < T) {
 #pragma unroll
@@ -1766,15 +1767,14 @@ __device__ __forceinline__ void tbf_iter(const TBFArgs<T, R>& A, const TBLane& L
 }
 
 // Iterations i .. i+U-1 (U the level-0 ring length, so ring slots are
-// compile-time); false once the last iteration has run.  The group's
-// dL/dV0 partials are then added to the per-level doubles of owned lanes.
+// compile-time); false once the last iteration has run.
 template <int VEC, int T, bool UNIT, bool CHECK, typename R, int... Us>
 __device__ __forceinline__ bool tbf_group_u(const TBFArgs<T, R>& A, const TBLane& L, int32_t i, int32_t last,
-                                            int32_t n_out, TBFRows& rw, TBFState<VEC, T, R>& S, R (&g32)[T],
+                                            int32_t n_out, TBFRows& rw, TBFState<VEC, T, R>& S, double (&gs)[T],
                                             std::integer_sequence<int, Us...>)
 {
     bool more = true;
-    ((more = more && (i + Us <= last) ? (tbf_iter<VEC, T, UNIT, CHECK, Us>(A, L, i + Us, last, n_out, rw, S, g32),
+    ((more = more && (i + Us <= last) ? (tbf_iter<VEC, T, UNIT, CHECK, Us>(A, L, i + Us, last, n_out, rw, S, gs),
                                          true)
                                       : false),
      ...);
@@ -1847,41 +1847,28 @@ __global__ __launch_bounds__(kBlock) void k_tbf2d(TBFArgs<T, R> A)
     rw.w = wrap_row(y0 - T + 3, L.ny);
     rw.mu = wrap_row(y0 - T + 2, L.ny);
 
-    R g32[T];
-    double gs[T];
+    double gs[T];      // dL/dV0 sums per level
 #pragma unroll
-    for (int k = 0; k < T; ++k) {
-        g32[k] = R(0);
-        gs[k] = 0.0;
-    }
-    const bool own_lane = L.soff != kPastRow;
-    auto flush = [&]() {
-#pragma unroll
-        for (int k = 0; k < T; ++k) {
-            gs[k] += own_lane ? (double)g32[k] : 0.0;
-            g32[k] = R(0);
-        }
-    };
+    for (int k = 0; k < T; ++k) gs[k] = 0.0;
 
     const int32_t last = n_out + 4 * T - 5;
     int32_t i = 0;
     bool more = true;
 #pragma unroll
     for (int w = 0; w < WARM; ++w) {
-        if (more) more = tbf_group_u<VEC, T, UNIT, true>(A, L, i, last, n_out, rw, S, g32,
+        if (more) more = tbf_group_u<VEC, T, UNIT, true>(A, L, i, last, n_out, rw, S, gs,
                                                          std::make_integer_sequence<int, R0>{});
         i += R0;
     }
-    flush();
     while (more) {
-        more = tbf_group_u<VEC, T, UNIT, false>(A, L, i, last, n_out, rw, S, g32,
+        more = tbf_group_u<VEC, T, UNIT, false>(A, L, i, last, n_out, rw, S, gs,
                                                 std::make_integer_sequence<int, R0>{});
         i += R0;
-        flush();
     }
+    const bool own_lane = L.soff != kPastRow;
     double gsum = 0.0;
 #pragma unroll
-    for (int k = 0; k < T; ++k) gsum += A.gscale[k] * wave_sum_f64(gs[k]);
+    for (int k = 0; k < T; ++k) gsum += A.gscale[k] * wave_sum_f64(own_lane ? gs[k] : 0.0);
     if (lane == 0) A.gacc[tile] += gsum;
 }
 

@@ -96,6 +96,7 @@ constexpr int kMaxPassSteps = 8;   // most leapfrog steps fused into one pass
 // Block passes (2D, prs_block2d.h): `steps` (1 .. kBlkSteps) steps in one
 // launch, each workgroup a block of 64 vec columns by waves * rows rows.
 // Operands as launch_tb's; phi_dot moves to pi_out whatever the step count.
+constexpr int64_t kMinRows = 8;    // fewest rows (planes) per tile the partial buffers hold for every tiling
 constexpr int kBlkSteps = 16;
 struct BlkShape {
     int vec, rows, waves;
@@ -111,6 +112,20 @@ bool blk_supported(const Geometry& g);
 BlkShape blk_choose(const Geometry& g, int steps);
 hipError_t launch_blk2d(int steps, const BlkShape& b, const Geometry& g, const void* phi_in, void* phi_out,
                         const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s);
+
+// Settings the library chooses by the lattice's size where neither the caller
+// nor the tuner has (estimates fitted to timed launches; results do not
+// depend on them).
+struct PassChoice {
+    int steps;
+    float us;      // estimated time of the launch
+    bool blk;      // a 2D block pass
+    Tiling til;    // else the marching pass's (single step's) tiling
+};
+Tiling auto_tile2(const Geometry& g, int T);             // 2D marching passes of T steps
+PassChoice auto_step(const Geometry& g);                 // single steps
+PassChoice auto_pass3(const Geometry& g, int T);         // 3D passes of T = 2, 3, 4 steps
+Tiling auto_adj_tile(const Geometry& g, int* T);         // reverse passes (2D fused, 3D stored)
 
 // A T-step pass over a slab along the last axis (the per-device kernel of a
 // lattice sharded along y in 2D, z in 3D): the fields are stored with T halo

@@ -2,6 +2,7 @@
 // templates are in prs_device.h), the record reduction and the host-side
 // dispatch by precision (the batched ensemble's kernel is in prs_ensemble.hip).
 
+#include <cmath>
 #include <mutex>
 
 #include "prs_device.h"
@@ -257,6 +258,132 @@ BlkShape blk_choose(const Geometry& g, int steps)
         if (best.vec == 0 || t < best.us) best = BlkShape{v, r, w, (float)t};
     }
     return best;
+}
+
+// 2D marching passes need about three wave tiles per SIMD (1024 SIMDs) to
+// hide a wave's chain of levels: the shortest tiles with one site per lane
+// while that makes no more, else two sites per lane and the height that
+// does.  Eight steps at 256^2: 9.1 us with one site and 8 rows, 14.4 us with
+// four and 8; at 2048^2 21 us with two sites and 13 rows, 24 with 16.
+Tiling auto_tile2(const Geometry& g, int T)
+{
+    constexpr int64_t kTiles = 3072;
+    Tiling t{1, (int)kMinRows, 1};
+    if (g.nx % 2 != 0 || tb_tiles(g, t, T) <= kTiles) return t;
+    if (!g.f64 || T <= 4) t.vec = 2;
+    while (t.rows < 64 && tb_tiles(g, t, T) > kTiles) ++t.rows;
+    return t;
+}
+
+// 16 bytes a lane where the row allows them, and in 3D short tiles on
+// lattices that would not fill the device (128^3: 9 us a step with 8 planes;
+// 200 x 120 x 90 11 us against 34 with 32 planes).  Two rows a wave only where
+// the fields outgrow the last-level cache: 512^3 431 us against 461 and
+// 1024^3 3.59 ms against 3.65, but 384^3 238 us against 212 with one row.
+PassChoice auto_step(const Geometry& g)
+{
+    const double sites = (double)g.nx * (double)g.Q * (double)g.M, bytes = 4 * sites * (g.f64 ? 8 : 4);
+    PassChoice c{1, 0.0f, false, Tiling{1, sites < 8e6 ? 8 : 32, g.ndim == 3 && sites > 1e8 ? 2 : 1}};
+    if (g.nx % 4 == 0 && !g.f64) c.til.vec = 4;
+    else if (g.nx % 2 == 0) c.til.vec = 2;
+    if (g.ndim == 2 && sites < 8e6) c.til = auto_tile2(g, 2);
+    c.us = (float)(4.5 + bytes / (bytes < 300e6 ? 7.0e6 : 4.9e6));
+    return c;
+}
+
+// The 3D LDS pass: per shape the time of a round of workgroups (iterations,
+// each a constant and the resident workgroups' rows and levels) times the
+// rounds, or of the memory traffic where that is longer.  Within 7 % of the
+// fastest measured shape from 64^3 to 400^3; above the last-level cache two
+// sites per lane, whose rows are longer, run 20 % faster than one.
+PassChoice auto_pass3(const Geometry& g, int T)
+{
+    struct Shape {
+        int8_t vec, ty, T;
+        uint8_t regs;
+    };
+    static const Shape f32[] = {
+        {1, 8, 2, 33},  {1, 16, 2, 56},  {1, 32, 2, 33},  {1, 64, 2, 56},  {2, 16, 2, 126}, {2, 32, 2, 66},
+        {1, 8, 3, 42},  {1, 16, 3, 84},  {1, 32, 3, 42},  {1, 64, 3, 84},  {2, 16, 3, 176}, {2, 32, 3, 97},
+        {1, 8, 4, 62},  {1, 16, 4, 113}, {1, 32, 4, 62},  {1, 64, 4, 113}, {2, 16, 4, 219}, {2, 32, 4, 127}};
+    static const Shape f64[] = {{1, 8, 2, 68},  {1, 8, 3, 93},   {1, 8, 4, 118},
+                                {1, 16, 2, 128}, {1, 16, 3, 179}, {1, 16, 4, 220}};
+    const Shape* list = g.f64 ? f64 : f32;
+    const int n = g.f64 ? (int)(sizeof f64 / sizeof f64[0]) : (int)(sizeof f32 / sizeof f32[0]);
+    const double size = g.f64 ? 8 : 4, sites = (double)g.nx * (double)g.Q * (double)g.M;
+    const bool cached = 4 * sites * size < 300e6;
+    const double site = g.f64 ? 0.0060 : 0.00353, bw = cached ? 8.8e3 : 5.5e3;
+    PassChoice best{T, 0.0f, false, Tiling{0, 0, 0}};
+    for (int i = 0; i < n; ++i) {
+        const Shape& h = list[i];
+        const Tiling probe{h.vec, 32, h.ty};
+        if (h.T != T || !tb_pass_supported(g, probe, T)) continue;
+        if (!cached && !g.f64 && h.vec == 1 && g.nx % 2 == 0) continue;
+        const int nw = tb3l_waves(h.ty), r = tb3l_rows_per_wave(h.ty);
+        const int64_t w = tb_owned_width_d(h.vec, T), y = tb3l_own_rows(nw, r, T);
+        const int64_t cols = ((g.nx + w - 1) / w) * ((g.Q + y - 1) / y);
+        const int waves = h.regs <= 64 ? 8 : h.regs <= 72 ? 7 : h.regs <= 80 ? 6 : h.regs <= 96 ? 5 : h.regs <= 128 ? 4 : 2;
+        const int held = std::max(1, 4 * waves / nw);
+        const double area = (double)(nw * r * h.vec);
+        auto time = [&](int64_t rows) {
+            const int64_t wgs = cols * ((g.M + rows - 1) / rows);
+            const double iters = (double)(rows + 2 * T - 2);
+            auto iter = [&](double m) { return 0.18 + m * area * (T + 1) * site; };
+            double t;
+            if (wgs <= 256 * (int64_t)held) {
+                t = 4.46 + iters * iter((double)((wgs + 255) / 256));
+            } else {
+                const double rounds = (double)wgs / (256.0 * held), full = std::floor(rounds), rest = rounds - full;
+                t = 4.46 + iters * (full * iter(held) + (rest > 0 ? iter(std::max(1.0, std::ceil(rest * held))) : 0.0));
+            }
+            const double read = (double)wgs * kWave * area * (2.0 * (double)rows + 4.0 * T - 2.0) * size;
+            const double mem = (0.75 * read + 2.5 * sites * size) / (bw * 1e3);
+            return mem > t ? mem + 0.15 * t : t + 0.15 * mem;
+        };
+        // heights: the ones that give one to four whole rounds, and two
+        // plain ones
+        for (int k = 0; k < 6; ++k) {
+            int64_t rows = k == 4 ? 16 : 32;
+            if (k < 4) {
+                const int64_t tz = 256 * (int64_t)held * (k + 1) / cols;
+                if (tz < 1) continue;
+                rows = std::min<int64_t>(64, std::max<int64_t>(4, (g.M + tz - 1) / tz));
+            }
+            const double t = time(rows);
+            if (best.til.vec == 0 || t < best.us) {
+                best.us = (float)t;
+                best.til = Tiling{h.vec, (int)rows, h.ty};
+            }
+        }
+    }
+    return best;
+}
+
+// Reverse passes.  2D (fused, four steps): the shortest tiles with one site
+// per lane while they make at most two per SIMD; else two sites per lane and
+// one tile per SIMD if those are short, or two (the tuner's choice from
+// 128^2 to 3000 x 2000, the single steps of four sites per lane took 24
+// against 9 us a step at 2048^2).  3D (stored): three steps of one site per
+// lane, 16 planes (the tuner's choice at 128^3 and 256^3).
+Tiling auto_adj_tile(const Geometry& g, int* T)
+{
+    if (g.ndim == 3) {
+        *T = g.f64 ? 2 : 3;
+        return Tiling{1, g.M < 96 ? 8 : 16, 2};
+    }
+    *T = 4;
+    Tiling t{1, (int)kMinRows, 1};
+    if (g.f64 || g.nx % 2 != 0) {
+        while (t.rows < 64 && tbf_tiles(g, t, 4) > 2048) ++t.rows;
+        return t;
+    }
+    if (tbf_tiles(g, t, 4) <= 2048) return t;
+    t.vec = 2;
+    while (t.rows <= 12 && tbf_tiles(g, t, 4) > 1024) ++t.rows;
+    if (t.rows <= 12) return t;
+    t.rows = (int)kMinRows;
+    while (t.rows < 64 && tbf_tiles(g, t, 4) > 2048) ++t.rows;
+    return t;
 }
 
 hipError_t launch_blk2d(int steps, const BlkShape& b, const Geometry& g, const void* phi_in, void* phi_out,
