@@ -185,9 +185,13 @@ struct Launch {
 // launches that move phi_dot (their total has to be even).
 class Stretches {
 public:
-    // 2D: block passes of 1 .. kBlkSteps steps; 3D: LDS passes of 2, 3, 4
-    // steps; and single steps.
-    explicit Stretches(const Geometry& g)
+    // 2D: block passes of 1 .. kBlkSteps steps; 3D: LDS passes of 2 ..
+    // kDeepSteps steps; and single steps.  `own`: the tiling and length T of
+    // a 3D run that the caller or the tuner set.  Its passes stand as the
+    // fastest of their length, whatever the estimate says (the tuner measured
+    // them), so only longer passes, and shorter ones for the remainder, can
+    // take their place.
+    explicit Stretches(const Geometry& g, const Tiling* own = nullptr, int own_T = 1)
     {
         if (g.ndim == 2) {
             for (int L = 1; L <= kBlkSteps; ++L) {
@@ -195,8 +199,13 @@ public:
                 if (b.vec) add(PassChoice{L, b.us, true, Tiling{b.vec, b.rows, b.waves}});
             }
         } else {
-            for (int T = 2; T <= 4; ++T) {
-                const PassChoice c = auto_pass3(g, T);
+            for (int T = 2; T <= kDeepSteps; ++T) {
+                PassChoice c = auto_pass3(g, T);
+                if (own && T == own_T) {
+                    const float us = c.til.vec ? c.us : 1e30f;
+                    c = own_pass3(g, *own, T);
+                    c.us = 0.97f * std::min(c.us, us);
+                }
                 if (c.til.vec) add(c);
             }
         }
@@ -372,12 +381,20 @@ struct prs_ctx {
 
 namespace {
 
-// Stretches serve 2D multi-step runs and 3D runs whose settings are the
-// library's; a tuned or set 3D run keeps its tiling and pass length.
-bool use_stretches(const Geometry& g, int T, bool own)
+// Stretches serve 2D multi-step runs, and 3D runs whose settings are the
+// library's or an LDS pass; other 3D runs keep the tiling and pass length that
+// the caller or the tuner set.
+bool use_stretches(const Geometry& g, const Tiling& t, int T, bool own)
 {
     if (!tb_supported(g)) return false;
-    return g.ndim == 2 ? T > 1 && blk_supported(g) : !own;
+    if (g.ndim == 2) return T > 1 && blk_supported(g);
+    return !own || (T > 1 && own_pass3(g, t, T).til.vec != 0);
+}
+
+Stretches* make_stretches(const Geometry& g, const Tiling& t, int T, bool own)
+{
+    if (!use_stretches(g, t, T, own)) return nullptr;
+    return new (std::nothrow) Stretches(g, g.ndim == 3 && own ? &t : nullptr, T);
 }
 
 // a(eta_n)^beta with a(eta) = (eta/eta0)^m: the scale-factor power of the
@@ -490,8 +507,7 @@ int pass_steps(const prs_ctx* c) { return tb_supported(c->geo) ? c->tblock : 1; 
 // tiling and length there too.
 const Stretches* run_stretches(const prs_ctx* c)
 {
-    if (!use_stretches(c->geo, pass_steps(c), c->own)) return nullptr;
-    if (!c->stretches) c->stretches.reset(new (std::nothrow) Stretches(c->geo));
+    if (!c->stretches) c->stretches.reset(make_stretches(c->geo, c->til, pass_steps(c), c->own));
     return c->stretches.get();
 }
 
@@ -507,6 +523,8 @@ hipError_t enqueue(const Launch& l, const Geometry& g, const Tiling& til, const 
     const Tiling& t = l.choice ? l.choice->til : til;
     if (l.choice && l.choice->blk)
         return launch_blk2d(l.steps, BlkShape{t.vec, t.rows, t.ty, 0.0f}, g, phi_in, phi_out, pi_in, pi_out, k, s);
+    if (l.choice && g.ndim == 3 && l.steps == kDeepSteps)
+        return launch_tb3_deep(g, t, phi_in, phi_out, pi_in, pi_out, k, s);
     if (l.steps > 1)
         return launch_tb(l.steps, g, t, phi_in, phi_out, pi_in, pi_out, k, false, nullptr, DiagCoef{}, s);
     return launch_step(g, t, phi_in, phi_out, pi_in, pi_out, k[0], true, false, nullptr, DiagCoef{}, s);
@@ -738,6 +756,7 @@ prs_status prs_set_time_blocking(prs_ctx* c, int32_t steps_per_pass)
                     "3D: 2, 3, 4)", steps_per_pass);
     c->tblock = steps_per_pass;
     c->own = true;
+    c->stretches.reset();
     return PRS_OK;
 }
 
@@ -811,6 +830,7 @@ prs_status prs_set_tiling(prs_ctx* c, int32_t vec, int32_t rows, int32_t ty)
                     (long long)kMinRows);
     c->til = t;
     c->own = true;
+    c->stretches.reset();
     return PRS_OK;
 }
 
@@ -1754,8 +1774,7 @@ struct ItemCursor {
 
 const Stretches* batch_stretches(prs_batch* b, int32_t r)
 {
-    if (!use_stretches(b->geo[r], b->tblock[r], b->own[r])) return nullptr;
-    if (!b->stretches[r]) b->stretches[r].reset(new (std::nothrow) Stretches(b->geo[r]));
+    if (!b->stretches[r]) b->stretches[r].reset(make_stretches(b->geo[r], b->til[r], b->tblock[r], b->own[r] != 0));
     return b->stretches[r].get();
 }
 
@@ -2202,6 +2221,7 @@ prs_status prs_batch_set_tiling(prs_batch* b, int32_t item, int32_t vec, int32_t
         return fail(PRS_EINVAL, "tiling has more wave tiles than the workspace holds");
     b->til[item] = t;
     b->own[item] = 1;
+    b->stretches[item].reset();
     batch_release_graph(b);
     b->dirty = true;
     return PRS_OK;
@@ -2222,6 +2242,7 @@ prs_status prs_batch_set_time_blocking(prs_batch* b, int32_t item, int32_t steps
         return fail(PRS_EINVAL, "steps per pass need more wave tiles than the workspace holds");
     b->tblock[item] = steps_per_pass;
     b->own[item] = 1;
+    b->stretches[item].reset();
     batch_release_graph(b);
     b->dirty = true;
     return PRS_OK;
@@ -2264,8 +2285,7 @@ prs_status prs_batch_state(const prs_batch* b, int32_t item, void** phi, void** 
     if (np == 0) {
         const bool streams = !persistent_mode(b->mode);
         std::unique_ptr<Stretches> st;
-        if (streams && use_stretches(b->geo[item], b->tblock[item], b->own[item]))
-            st.reset(new (std::nothrow) Stretches(b->geo[item]));
+        if (streams) st.reset(make_stretches(b->geo[item], b->til[item], b->tblock[item], b->own[item] != 0));
         np = (int64_t)batch_plan(it, b->geo[item], b->til[item], b->part_cap[item], b->tblock[item], st.get()).size();
     }
     if (phi) *phi = ((np - 1) & 1) ? it.phi_b : it.phi_a;
@@ -2415,6 +2435,7 @@ prs_status prs_batch_autotune(prs_batch* b, double* best_ms)
                 b->til[r] = t;
                 b->tblock[r] = T;
                 b->own[r] = own;
+                b->stretches[r].reset();
             }
             batch_release_graph(b);
             b->dirty = true;
@@ -2574,13 +2595,14 @@ int device_compute_units()
 // has only a few waves per SIMD, a partial last round leaves the units that
 // got one workgroup fewer idle while it runs.
 template <typename Usable, typename Workgroups>
-void add_balanced_rows(std::vector<Tiling>& have, int kmax, int ncu, Usable usable, Workgroups workgroups)
+void add_balanced_rows(std::vector<Tiling>& have, int kmax, int ncu, Usable usable, Workgroups workgroups,
+                       int ty = 1)
 {
     if (ncu <= 0) return;
     for (int vec : {1, 2, 4})
         for (int k = 1; k <= kmax; ++k)
             for (int r = (int)kMinRows; r <= 128; ++r) {
-                const Tiling t{vec, r, 1};
+                const Tiling t{vec, r, ty};
                 if (!usable(t)) break;
                 if (workgroups(t) <= (int64_t)k * ncu) {
                     bool seen = false;
@@ -2953,9 +2975,10 @@ prs_status prs_autotune(prs_ctx* c, const char* cache_path, int32_t flags, void*
     for (int T = 1; T <= max_T; ++T) {
         if (T > 1 && !tb_steps_supported(c->geo, T)) continue;
         per = T;
-        // 2D multi-step passes also try the heights that give a whole number
-        // of workgroup rounds, up to four per compute unit (lattices whose
-        // pass fills the units many times over get none)
+        // multi-step passes (in 3D the LDS pass) also try the heights that
+        // give a whole number of workgroup rounds, up to four per compute
+        // unit (lattices whose pass fills the units many times over get none;
+        // at 256^3 26 planes a tile take 54 us a pass, 32 planes 60)
         std::vector<Tiling> tcand = cand;
         if (c->geo.ndim == 2 && T > 1)
             add_balanced_rows(
@@ -2964,6 +2987,11 @@ prs_status prs_autotune(prs_ctx* c, const char* cache_path, int32_t flags, void*
                     return tb_pass_supported(c->geo, t, T) && (!batch_set || ens_supported(c->geo, t, T));
                 },
                 [&](const Tiling& t) { return tb2_workgroups(c->geo, t, T); });
+        if (c->geo.ndim == 3 && T > 1 && !batch_set)
+            for (int ty : {8, 16, 32, 64})
+                add_balanced_rows(
+                    tcand, 4, ncu, [&](const Tiling& t) { return tb_pass_supported(c->geo, t, T); },
+                    [&](const Tiling& t) { return tb_tiles(c->geo, t, T) / (ty >= 32 ? 16 : 8); }, ty);
         for (const Tiling& t : tcand) {
             if (e != hipSuccess) break;
             if (T > 1 && !tb_pass_supported(c->geo, t, T)) continue;
@@ -3003,6 +3031,7 @@ prs_status prs_autotune(prs_ctx* c, const char* cache_path, int32_t flags, void*
     c->til = best;
     c->tblock = best_T;
     c->own = true;
+    c->stretches.reset();
     if (best_us) *best_us = best_t * 1e3;
     if (cache_path && cache_path[0]) {
         cache[key] = TuneEntry{best.vec, best.rows, best.ty, best_T, best_t * 1e3};

@@ -236,6 +236,38 @@ __device__ __forceinline__ double from_right_lane(double v)
     return __builtin_bit_cast(double, ((uint64_t)h << 32) | l);
 }
 
+// The same shifts with the wave as a ring (lane 0 receives lane 63's value,
+// lane 63 lane 0's): a row of exactly one wave's sites needs no halo lanes.
+__device__ __forceinline__ float from_left_ring(float v)
+{
+    const int b = __builtin_bit_cast(int, v);
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(b, 0x13C, 0xF, 0xF, true));
+}
+
+__device__ __forceinline__ float from_right_ring(float v)
+{
+    const int b = __builtin_bit_cast(int, v);
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(b, 0x134, 0xF, 0xF, true));
+}
+
+__device__ __forceinline__ double from_left_ring(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const int lo = (int)(uint32_t)b, hi = (int)(uint32_t)(b >> 32);
+    const uint32_t l = (uint32_t)__builtin_amdgcn_mov_dpp(lo, 0x13C, 0xF, 0xF, true);
+    const uint32_t h = (uint32_t)__builtin_amdgcn_mov_dpp(hi, 0x13C, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)h << 32) | l);
+}
+
+__device__ __forceinline__ double from_right_ring(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const int lo = (int)(uint32_t)b, hi = (int)(uint32_t)(b >> 32);
+    const uint32_t l = (uint32_t)__builtin_amdgcn_mov_dpp(lo, 0x134, 0xF, 0xF, true);
+    const uint32_t h = (uint32_t)__builtin_amdgcn_mov_dpp(hi, 0x134, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)h << 32) | l);
+}
+
 __device__ __forceinline__ double u64_as_double(uint32_t lo, uint32_t hi)
 {
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
@@ -966,6 +998,19 @@ __host__ __device__ __forceinline__ int64_t tb_owned_width_d(int vec, int T)
 {
     const int H = (T + vec - 1) / vec;
     return (int64_t)(kWave - 2 * H) * vec;
+}
+
+// The 3D LDS pass: a row of exactly the wave's sites is one tile without
+// halo lanes (128^3, two sites a lane: 14.9 us for four steps, 21.4 in two
+// tiles with halos).
+__host__ __device__ __forceinline__ int tb3l_halo(int64_t nx, int vec, int T)
+{
+    return nx == (int64_t)kWave * vec ? 0 : (T + vec - 1) / vec;
+}
+
+__host__ __device__ __forceinline__ int64_t tb3l_width(int64_t nx, int vec, int T)
+{
+    return (int64_t)(kWave - 2 * tb3l_halo(nx, vec, T)) * vec;
 }
 
 template <int VEC, int T, typename R>
@@ -1897,6 +1942,7 @@ struct TB3Args {
     int64_t nx, ny, nz;
     int64_t tiles_x, tiles_y, ntiles;
     int64_t rows;               // planes per tile along z
+    int32_t hx;                 // the LDS pass: halo lanes on each side of a wave's rows (tb3l_halo)
     int32_t zhalo = 0;          // 0: periodic in z; T: a z-slab stored with T halo planes below and above
     StepCoefT<R> k[T];
     DiagCoef dc;
@@ -2210,8 +2256,16 @@ __device__ __forceinline__ void tb3l_put(RT* p, const RT (&v)[VEC])
 }
 
 // Iteration i of the z-march (level k computes plane s0 - T - k + 2 + i, as
-// in k_tb3d).
-template <int VEC, int T, int R, int NW, bool DIAG, bool UNIT, bool CHECK, int U, bool ALL, typename RT>
+// in k_tb3d).  FLAT is the march of the longest passes: every level runs in
+// every iteration, the first and last ones included, on planes that feed
+// nothing stored, and the scheduler keeps the levels apart.  Without the
+// warm-up's conditional levels and the exits between iterations a level's
+// ring holds two planes across an iteration, not four and both phi_dot
+// planes: five levels of eight sites take 219 registers and spill none,
+// where the other march spills (1024^3: 4.53 ms for five steps, 6.3 spilled,
+// and 4.4 ms for four).  Small tiles pay for the idle levels (128^3 25 us a
+// pass for 19), so lengths up to four keep the other march.
+template <int VEC, int T, int R, int NW, bool DIAG, bool UNIT, bool CHECK, int U, bool ALL, bool FLAT, typename RT>
 __device__ __forceinline__ void tb3l_iter(const TB3Args<T, RT>& A, const TB3LLane<R>& L, RT* lds, int32_t i,
                                           int32_t last, TBRows& rw, TB3LState<VEC, T, R, RT>& S, DiagAcc& acc)
 {
@@ -2224,6 +2278,7 @@ __device__ __forceinline__ void tb3l_iter(const TB3Args<T, RT>& A, const TB3LLan
     // the boundary rows of the phi^n plane level 1 computes next iteration
     tb3l_put<VEC>(tb3l_slot<VEC, NW>(lds, 0, U & 1, L.wave, 0), S.in[(U + 1) & 3][0]);
     tb3l_put<VEC>(tb3l_slot<VEC, NW>(lds, 0, U & 1, L.wave, 1), S.in[(U + 1) & 3][R - 1]);
+    if constexpr (FLAT) __builtin_amdgcn_sched_barrier(0);
     const int wb = L.wave > 0 ? L.wave - 1 : 0;
     const int wa = L.wave < NW - 1 ? L.wave + 1 : NW - 1;
 #pragma unroll
@@ -2259,12 +2314,13 @@ __device__ __forceinline__ void tb3l_iter(const TB3Args<T, RT>& A, const TB3LLan
         }
         const bool diag_plane = DIAG && k == 1 && i >= T - 1 && i < T - 1 + (L.s1 - L.s0);
         const int32_t zout = L.s0 + i - (2 * T - 2);
-        const uint32_t sb = (!CHECK || i >= 2 * T - 2) ? L.plane_bytes : 0u;
-        const size_t obase = (size_t)(uint32_t)((CHECK && i < 2 * T - 2 ? L.s0 : zout) + L.zoff) * L.plane;
+        const bool stored = FLAT ? zout >= L.s0 && zout < L.s1 : !CHECK || i >= 2 * T - 2;
+        const uint32_t sb = stored ? L.plane_bytes : 0u;
+        const size_t obase = (size_t)(uint32_t)((stored ? zout : L.s0) + L.zoff) * L.plane;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const RT left = from_left_lane(cc[r][VEC - 1]);
-            const RT right = from_right_lane(cc[r][0]);
+            const RT left = from_left_ring(cc[r][VEC - 1]);
+            const RT right = from_right_ring(cc[r][0]);
             RT out_phi[VEC], out_pi[VEC];
             RT nm[VEC][3], np[VEC][3];
 #pragma unroll
@@ -2306,11 +2362,13 @@ __device__ __forceinline__ void tb3l_iter(const TB3Args<T, RT>& A, const TB3LLan
                 buf_store<VEC>(A.phi_out + obase, sb, L.srow[r], out_phi);
                 buf_store<VEC>(A.pi_out + obase, sb, L.srow[r], out_pi);
             }
+            if constexpr (FLAT) __builtin_amdgcn_sched_barrier(0);
         }
         if (k < T) {
             tb3l_put<VEC>(tb3l_slot<VEC, NW>(lds, k, U & 1, L.wave, 0), S.lv[k < T ? k : 0][U & 3][0]);
             tb3l_put<VEC>(tb3l_slot<VEC, NW>(lds, k, U & 1, L.wave, 1), S.lv[k < T ? k : 0][U & 3][R - 1]);
         }
+        if constexpr (FLAT) __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
 }
@@ -2319,14 +2377,28 @@ template <int VEC, int T, int R, int NW, bool DIAG, bool UNIT, bool CHECK, bool 
 __device__ __forceinline__ bool tb3l_group(const TB3Args<T, RT>& A, const TB3LLane<R>& L, RT* lds, int32_t i,
                                            int32_t last, TBRows& rw, TB3LState<VEC, T, R, RT>& S, DiagAcc& acc)
 {
-    tb3l_iter<VEC, T, R, NW, DIAG, UNIT, CHECK, 0, ALL>(A, L, lds, i, last, rw, S, acc);
+    tb3l_iter<VEC, T, R, NW, DIAG, UNIT, CHECK, 0, ALL, false>(A, L, lds, i, last, rw, S, acc);
     if (i + 1 > last) return false;
-    tb3l_iter<VEC, T, R, NW, DIAG, UNIT, CHECK, 1, ALL>(A, L, lds, i + 1, last, rw, S, acc);
+    tb3l_iter<VEC, T, R, NW, DIAG, UNIT, CHECK, 1, ALL, false>(A, L, lds, i + 1, last, rw, S, acc);
     if (i + 2 > last) return false;
-    tb3l_iter<VEC, T, R, NW, DIAG, UNIT, CHECK, 2, ALL>(A, L, lds, i + 2, last, rw, S, acc);
+    tb3l_iter<VEC, T, R, NW, DIAG, UNIT, CHECK, 2, ALL, false>(A, L, lds, i + 2, last, rw, S, acc);
     if (i + 3 > last) return false;
-    tb3l_iter<VEC, T, R, NW, DIAG, UNIT, CHECK, 3, ALL>(A, L, lds, i + 3, last, rw, S, acc);
+    tb3l_iter<VEC, T, R, NW, DIAG, UNIT, CHECK, 3, ALL, false>(A, L, lds, i + 3, last, rw, S, acc);
     return i + 4 <= last;
+}
+
+// The whole flat march, in groups of four iterations (the last may run past
+// `last`, loading and storing nothing).
+template <int VEC, int T, int R, int NW, bool UNIT, typename RT>
+__device__ __forceinline__ void tb3l_flat(const TB3Args<T, RT>& A, const TB3LLane<R>& L, RT* lds, int32_t last,
+                                          TBRows& rw, TB3LState<VEC, T, R, RT>& S, DiagAcc& acc)
+{
+    for (int32_t i = 0; i <= last; i += 4) {
+        tb3l_iter<VEC, T, R, NW, false, UNIT, false, 0, false, true>(A, L, lds, i, last, rw, S, acc);
+        tb3l_iter<VEC, T, R, NW, false, UNIT, false, 1, false, true>(A, L, lds, i + 1, last, rw, S, acc);
+        tb3l_iter<VEC, T, R, NW, false, UNIT, false, 2, false, true>(A, L, lds, i + 2, last, rw, S, acc);
+        tb3l_iter<VEC, T, R, NW, false, UNIT, false, 3, false, true>(A, L, lds, i + 3, last, rw, S, acc);
+    }
 }
 
 // Rows a workgroup of the LDS pass stores along y.
@@ -2345,8 +2417,8 @@ constexpr int tb3l_min_waves(int vec, int T, int R, int NW, int esize, bool diag
 template <int VEC, int T, int R, int NW, bool DIAG, bool UNIT, bool ALL, typename RT>
 __device__ __forceinline__ void tb3l_tile(const TB3Args<T, RT>& A, int64_t tile, RT* lds)
 {
-    constexpr int H = (T + VEC - 1) / VEC;
-    constexpr int W = (kWave - 2 * H) * VEC;
+    const int H = A.hx;
+    const int W = (kWave - 2 * H) * VEC;
     constexpr int YOWN = tb3l_own_rows(NW, R, T);
     constexpr int WARM = (2 * T - 2 + 3) / 4;
     const int lane = threadIdx.x & (kWave - 1);
@@ -2420,16 +2492,21 @@ __device__ __forceinline__ void tb3l_tile(const TB3Args<T, RT>& A, int64_t tile,
     zero_diag(acc);
 
     const int32_t last = (L.s1 - L.s0) + 2 * T - 3;
-    int32_t i = 0;
-    bool more = true;
+    if constexpr (T > 4) {
+        static_assert(!DIAG && !ALL, "plain passes only");
+        tb3l_flat<VEC, T, R, NW, UNIT>(A, L, lds, last, rw, S, acc);
+    } else {
+        int32_t i = 0;
+        bool more = true;
 #pragma unroll
-    for (int w = 0; w < WARM; ++w) {
-        if (more) more = tb3l_group<VEC, T, R, NW, DIAG, UNIT, true, ALL>(A, L, lds, i, last, rw, S, acc);
-        i += 4;
-    }
-    while (more) {
-        more = tb3l_group<VEC, T, R, NW, DIAG, UNIT, false, ALL>(A, L, lds, i, last, rw, S, acc);
-        i += 4;
+        for (int w = 0; w < WARM; ++w) {
+            if (more) more = tb3l_group<VEC, T, R, NW, DIAG, UNIT, true, ALL>(A, L, lds, i, last, rw, S, acc);
+            i += 4;
+        }
+        while (more) {
+            more = tb3l_group<VEC, T, R, NW, DIAG, UNIT, false, ALL>(A, L, lds, i, last, rw, S, acc);
+            i += 4;
+        }
     }
 
     if constexpr (DIAG) {
@@ -3242,7 +3319,8 @@ hipError_t launch_tb3l_t(const Geometry& g, const Tiling& t, const void* phi_in,
     A.nx = g.nx;
     A.ny = g.Q;
     A.nz = g.M;
-    const int64_t W = tb_owned_width_d(VEC, T);
+    const int64_t W = tb3l_width(g.nx, VEC, T);
+    A.hx = tb3l_halo(g.nx, VEC, T);
     constexpr int YOWN = tb3l_own_rows(NW, RW, T);
     A.tiles_x = (g.nx + W - 1) / W;
     A.tiles_y = (g.Q + YOWN - 1) / YOWN;
@@ -3252,16 +3330,19 @@ hipError_t launch_tb3l_t(const Geometry& g, const Tiling& t, const void* phi_in,
     A.dc = dc;
     const unsigned blocks = (unsigned)A.ntiles;
     const bool unit = A.k[0].inv_dx2 == R(1) && A.k[0].kc == R(1);
-    if (phi_lv) {
-        if (unit) hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, true, true, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
-        else hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, false, true, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
-    } else if (diag) {
-        hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, true, false, false, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
-    } else if (unit) {
-        hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, true, false, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
-    } else {
-        hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, false, false, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
+    if constexpr (T <= 4) {
+        if (phi_lv) {
+            if (unit) hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, true, true, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
+            else hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, false, true, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
+            return hipGetLastError();
+        }
+        if (diag) {
+            hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, true, false, false, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
+            return hipGetLastError();
+        }
     }
+    if (unit) hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, true, false, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
+    else hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, false, false, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
     return hipGetLastError();
 }
 

@@ -135,6 +135,7 @@ __device__ __forceinline__ void ens_tb3(CDesc& d, CPass& ps, int64_t p, int64_t 
     A.tiles_y = ps.tiles_q;
     A.ntiles = ps.ntiles;
     A.rows = d.rows;
+    A.hx = tb3l_halo(d.nx, 1, T);
     A.zhalo = 0;
 #pragma unroll
     for (int i = 0; i < T; ++i) A.k[i] = ens_coef(d, ps.first + i);
@@ -455,7 +456,7 @@ bool ens_supported(const Geometry& g, const Tiling& t, int T)
 void ens_pass_grid(const Geometry& g, const Tiling& t, int L, EnsPass& ps)
 {
     if (L > 1 && g.ndim == 3) {
-        const int64_t W = tb_owned_width_d(1, L);
+        const int64_t W = tb3l_width(g.nx, 1, L);
         const int64_t yown = tb3l_own_rows(kEnsWaves, t.ty / 4, L);
         const int64_t tx = (g.nx + W - 1) / W, tq = (g.Q + yown - 1) / yown;
         ps.tiles_x = (int32_t)tx;

@@ -98,6 +98,7 @@ constexpr int kMaxPassSteps = 8;   // most leapfrog steps fused into one pass
 // Operands as launch_tb's; phi_dot moves to pi_out whatever the step count.
 constexpr int64_t kMinRows = 8;    // fewest rows (planes) per tile the partial buffers hold for every tiling
 constexpr int kBlkSteps = 16;
+constexpr int kDeepSteps = 5;    // the longest 3D pass
 struct BlkShape {
     int vec, rows, waves;
     float us;            // estimated time of the launch
@@ -124,7 +125,8 @@ struct PassChoice {
 };
 Tiling auto_tile2(const Geometry& g, int T);             // 2D marching passes of T steps
 PassChoice auto_step(const Geometry& g);                 // single steps
-PassChoice auto_pass3(const Geometry& g, int T);         // 3D passes of T = 2, 3, 4 steps
+PassChoice auto_pass3(const Geometry& g, int T);         // 3D passes of T = 2 .. kDeepSteps steps
+PassChoice own_pass3(const Geometry& g, const Tiling& t, int T);
 Tiling auto_adj_tile(const Geometry& g, int* T);         // reverse passes (2D fused, 3D stored)
 
 // A T-step pass over a slab along the last axis (the per-device kernel of a
@@ -136,6 +138,9 @@ Tiling auto_adj_tile(const Geometry& g, int* T);         // reverse passes (2D f
 hipError_t launch_tb_slab(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
                           const void* pi_in, void* pi_out, const StepCoef64* k, bool diag, WavePartial* partials,
                           const DiagCoef& dc, hipStream_t s);
+
+hipError_t launch_tb3_deep(const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out, const void* pi_in,
+                           void* pi_out, const StepCoef64* k, hipStream_t s);
 
 // Reduces each job's `count` partials in a fixed order into its record (a
 // device or pinned host pointer); n <= kFinBatch jobs, one launch.
@@ -230,6 +235,10 @@ hipError_t launch_tb2d(int T, const Geometry& g, const Tiling& t, const void* ph
 template <typename R>
 hipError_t launch_blk2d_p(int steps, const BlkShape& b, const Geometry& g, const void* phi_in, void* phi_out,
                           const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s);
+template <typename R>
+hipError_t launch_tb3_deep_p(const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
+                             const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s);
+
 template <typename R>
 hipError_t launch_tb3d(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
                        const void* pi_in, void* pi_out, const StepCoef64* k, bool diag, WavePartial* partials,

@@ -196,6 +196,16 @@ hipError_t launch_tb(int T, const Geometry& g, const Tiling& t, const void* phi_
     return tb_dispatch(T, g, t, phi_in, phi_out, pi_in, pi_out, k, diag, partials, dc, 0, s);
 }
 
+// Five steps, the longest LDS pass: a launch of the library's own choice
+// (auto_pass3), not a pass length that a caller may set.
+hipError_t launch_tb3_deep(const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out, const void* pi_in,
+                           void* pi_out, const StepCoef64* k, hipStream_t s)
+{
+    if (g.ndim != 3 || !tb_pass_supported(g, t, 4)) return hipErrorInvalidValue;
+    return g.f64 ? launch_tb3_deep_p<double>(g, t, phi_in, phi_out, pi_in, pi_out, k, s)
+                 : launch_tb3_deep_p<float>(g, t, phi_in, phi_out, pi_in, pi_out, k, s);
+}
+
 BlkGrid blk_grid(const Geometry& g, int vec, int rows, int waves, int steps)
 {
     BlkGrid b{0, 0, (steps + vec - 1) / vec};
@@ -291,65 +301,94 @@ PassChoice auto_step(const Geometry& g)
     return c;
 }
 
-// The 3D LDS pass: per shape the time of a round of workgroups (iterations,
-// each a constant and the resident workgroups' rows and levels) times the
-// rounds, or of the memory traffic where that is longer.  Within 7 % of the
-// fastest measured shape from 64^3 to 400^3; above the last-level cache two
-// sites per lane, whose rows are longer, run 20 % faster than one.
+// The shapes of the 3D LDS pass and the registers a wave of each takes.
+struct Pass3Shape {
+    int8_t vec, ty, T;
+    uint8_t regs;
+};
+
+const Pass3Shape* pass3_shapes(bool f64, int* n)
+{
+    static const Pass3Shape f32[] = {
+        {1, 8, 2, 33},  {1, 16, 2, 56},  {1, 32, 2, 33},  {1, 64, 2, 56},  {2, 8, 2, 72},
+        {2, 16, 2, 126}, {2, 32, 2, 66}, {1, 8, 3, 42},   {1, 16, 3, 84},  {1, 32, 3, 42},
+        {1, 64, 3, 84},  {2, 8, 3, 97},  {2, 16, 3, 176}, {2, 32, 3, 97},  {1, 8, 4, 62},
+        {1, 16, 4, 113}, {1, 32, 4, 62}, {1, 64, 4, 113}, {2, 8, 4, 127},  {2, 16, 4, 219},
+        {2, 32, 4, 127}, {2, 16, 5, 219}};
+    static const Pass3Shape f64s[] = {{1, 8, 2, 68},   {1, 8, 3, 93},   {1, 8, 4, 118}, {1, 16, 2, 128},
+                                      {1, 16, 3, 179}, {1, 16, 4, 220}, {1, 16, 5, 219}};
+    *n = f64 ? (int)(sizeof f64s / sizeof f64s[0]) : (int)(sizeof f32 / sizeof f32[0]);
+    return f64 ? f64s : f32;
+}
+
+// Estimated time of an LDS pass: the time of a round of workgroups
+// (iterations, each a constant and the resident workgroups' rows and levels)
+// times the rounds, or of the memory traffic where that is longer.
+struct Pass3Time {
+    Pass3Time(const Geometry& lattice, const Pass3Shape& h) : g(lattice), T(h.T)
+    {
+        size = g.f64 ? 8 : 4;
+        sites = (double)g.nx * (double)g.Q * (double)g.M;
+        cached = 4 * sites * size < 300e6;
+        const int nw = tb3l_waves(h.ty), r = tb3l_rows_per_wave(h.ty);
+        const int64_t w = tb3l_width(g.nx, h.vec, T), y = tb3l_own_rows(nw, r, T);
+        cols = ((g.nx + w - 1) / w) * ((g.Q + y - 1) / y);
+        const int waves = h.regs <= 64 ? 8 : h.regs <= 72 ? 7 : h.regs <= 80 ? 6 : h.regs <= 96 ? 5 : h.regs <= 128 ? 4 : 2;
+        held = std::max(1, 4 * waves / nw);
+        area = (double)(nw * r * h.vec);
+    }
+    double us(int64_t rows) const
+    {
+        const double site = g.f64 ? 0.0060 : 0.00353, bw = cached ? 8.8e3 : 5.5e3;
+        const int64_t wgs = cols * ((g.M + rows - 1) / rows);
+        const double iters = (double)(rows + 2 * T - 2);
+        auto iter = [&](double m) { return 0.18 + m * area * (T + 1) * site; };
+        double t;
+        if (wgs <= 256 * (int64_t)held) {
+            t = 4.46 + iters * iter((double)((wgs + 255) / 256));
+        } else {
+            const double rounds = (double)wgs / (256.0 * held), full = std::floor(rounds), rest = rounds - full;
+            t = 4.46 + iters * (full * iter(held) + (rest > 0 ? iter(std::max(1.0, std::ceil(rest * held))) : 0.0));
+        }
+        const double read = (double)wgs * kWave * area * (2.0 * (double)rows + 4.0 * T - 2.0) * size;
+        const double mem = (0.75 * read + 2.5 * sites * size) / (bw * 1e3);
+        return mem > t ? mem + 0.15 * t : t + 0.15 * mem;
+    }
+    const Geometry& g;
+    int T, held;
+    bool cached;
+    int64_t cols;
+    double size, sites, area;
+};
+
+// The estimated fastest LDS pass of T steps.  Within 7 % of the fastest
+// measured shape from 64^3 to 400^3; above the last-level cache two sites per
+// lane, whose rows are longer, run 20 % faster than one, and only there are
+// there passes of five steps (512^3 123 us a step against 144 with four, but
+// 256^3 20 against 15: the five-step march has no room for more than two
+// waves per SIMD).
 PassChoice auto_pass3(const Geometry& g, int T)
 {
-    struct Shape {
-        int8_t vec, ty, T;
-        uint8_t regs;
-    };
-    static const Shape f32[] = {
-        {1, 8, 2, 33},  {1, 16, 2, 56},  {1, 32, 2, 33},  {1, 64, 2, 56},  {2, 16, 2, 126}, {2, 32, 2, 66},
-        {1, 8, 3, 42},  {1, 16, 3, 84},  {1, 32, 3, 42},  {1, 64, 3, 84},  {2, 16, 3, 176}, {2, 32, 3, 97},
-        {1, 8, 4, 62},  {1, 16, 4, 113}, {1, 32, 4, 62},  {1, 64, 4, 113}, {2, 16, 4, 219}, {2, 32, 4, 127}};
-    static const Shape f64[] = {{1, 8, 2, 68},  {1, 8, 3, 93},   {1, 8, 4, 118},
-                                {1, 16, 2, 128}, {1, 16, 3, 179}, {1, 16, 4, 220}};
-    const Shape* list = g.f64 ? f64 : f32;
-    const int n = g.f64 ? (int)(sizeof f64 / sizeof f64[0]) : (int)(sizeof f32 / sizeof f32[0]);
-    const double size = g.f64 ? 8 : 4, sites = (double)g.nx * (double)g.Q * (double)g.M;
-    const bool cached = 4 * sites * size < 300e6;
-    const double site = g.f64 ? 0.0060 : 0.00353, bw = cached ? 8.8e3 : 5.5e3;
+    int n;
+    const Pass3Shape* list = pass3_shapes(g.f64, &n);
     PassChoice best{T, 0.0f, false, Tiling{0, 0, 0}};
     for (int i = 0; i < n; ++i) {
-        const Shape& h = list[i];
-        const Tiling probe{h.vec, 32, h.ty};
-        if (h.T != T || !tb_pass_supported(g, probe, T)) continue;
-        if (!cached && !g.f64 && h.vec == 1 && g.nx % 2 == 0) continue;
-        const int nw = tb3l_waves(h.ty), r = tb3l_rows_per_wave(h.ty);
-        const int64_t w = tb_owned_width_d(h.vec, T), y = tb3l_own_rows(nw, r, T);
-        const int64_t cols = ((g.nx + w - 1) / w) * ((g.Q + y - 1) / y);
-        const int waves = h.regs <= 64 ? 8 : h.regs <= 72 ? 7 : h.regs <= 80 ? 6 : h.regs <= 96 ? 5 : h.regs <= 128 ? 4 : 2;
-        const int held = std::max(1, 4 * waves / nw);
-        const double area = (double)(nw * r * h.vec);
-        auto time = [&](int64_t rows) {
-            const int64_t wgs = cols * ((g.M + rows - 1) / rows);
-            const double iters = (double)(rows + 2 * T - 2);
-            auto iter = [&](double m) { return 0.18 + m * area * (T + 1) * site; };
-            double t;
-            if (wgs <= 256 * (int64_t)held) {
-                t = 4.46 + iters * iter((double)((wgs + 255) / 256));
-            } else {
-                const double rounds = (double)wgs / (256.0 * held), full = std::floor(rounds), rest = rounds - full;
-                t = 4.46 + iters * (full * iter(held) + (rest > 0 ? iter(std::max(1.0, std::ceil(rest * held))) : 0.0));
-            }
-            const double read = (double)wgs * kWave * area * (2.0 * (double)rows + 4.0 * T - 2.0) * size;
-            const double mem = (0.75 * read + 2.5 * sites * size) / (bw * 1e3);
-            return mem > t ? mem + 0.15 * t : t + 0.15 * mem;
-        };
-        // heights: the ones that give one to four whole rounds, and two
-        // plain ones
-        for (int k = 0; k < 6; ++k) {
-            int64_t rows = k == 4 ? 16 : 32;
+        const Pass3Shape& h = list[i];
+        if (h.T != T || !tb_pass_supported(g, Tiling{h.vec, 32, h.ty}, std::min(T, 4))) continue;
+        const Pass3Time p(g, h);
+        if (p.cached ? T > 4 : !g.f64 && h.vec == 1 && g.nx % 2 == 0) continue;
+        // heights: the ones that give one to four whole rounds, and two or
+        // three plain ones
+        for (int k = 0; k < 7; ++k) {
+            int64_t rows = k == 4 ? 16 : k == 5 ? 32 : 64;
             if (k < 4) {
-                const int64_t tz = 256 * (int64_t)held * (k + 1) / cols;
+                const int64_t tz = 256 * (int64_t)p.held * (k + 1) / p.cols;
                 if (tz < 1) continue;
                 rows = std::min<int64_t>(64, std::max<int64_t>(4, (g.M + tz - 1) / tz));
+            } else if (k == 6 && p.cached) {
+                continue;
             }
-            const double t = time(rows);
+            const double t = p.us(rows);
             if (best.til.vec == 0 || t < best.us) {
                 best.us = (float)t;
                 best.til = Tiling{h.vec, (int)rows, h.ty};
@@ -357,6 +396,19 @@ PassChoice auto_pass3(const Geometry& g, int T)
         }
     }
     return best;
+}
+
+// A pass of T steps in a tiling that the caller or the tuner chose, vec 0
+// when it is none of the LDS pass.
+PassChoice own_pass3(const Geometry& g, const Tiling& t, int T)
+{
+    int n;
+    const Pass3Shape* list = pass3_shapes(g.f64, &n);
+    if (tb3l_tiling(t.ty) && tb_pass_supported(g, t, T))
+        for (int i = 0; i < n; ++i)
+            if (list[i].T == T && list[i].vec == t.vec && list[i].ty == t.ty)
+                return PassChoice{T, (float)Pass3Time(g, list[i]).us(t.rows), false, t};
+    return PassChoice{T, 0.0f, false, Tiling{0, 0, 0}};
 }
 
 // Reverse passes.  2D (fused, four steps): the shortest tiles with one site
@@ -613,11 +665,12 @@ bool tb_pass_supported(const Geometry& g, const Tiling& t, int T)
 
 int64_t tb_tiles(const Geometry& g, const Tiling& t, int T)
 {
-    const int64_t W = tb_owned_width(t.vec, T);
+    int64_t W = tb_owned_width(t.vec, T);
     const int64_t planes = (g.M + t.rows - 1) / t.rows;
     if (g.ndim == 3 && tb3l_tiling(t.ty)) {
         // one partial per wave of every workgroup
         const int nw = tb3l_waves(t.ty);
+        W = tb3l_width(g.nx, t.vec, T);
         const int64_t yown = tb3l_own_rows(nw, tb3l_rows_per_wave(t.ty), T);
         return ((g.nx + W - 1) / W) * ((g.Q + yown - 1) / yown) * planes * nw;
     }
