@@ -67,7 +67,8 @@ def kernel_digest():
     """Digest of the kernel sources (device code and its launch templates)."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("prs_device.h", "prs_block2d.h", "prs_fwd2d.hip", "prs_fwd3d.hip", "prs_adjoint.hip", "prs_kernels.hip",
+    for name in ("prs_device.h", "prs_block2d.h", "prs_fwd2d.hip", "prs_fwd3d.hip", "prs_adjoint.hip",
+                 "prs_adjoint3d.hip", "prs_kernels.hip",
                  "prs_ensemble.hip", "prs_internal.h"):
         with open(os.path.join(ROOT, "paper_1710_10420_amd", "csrc", name), "rb") as f:
             h.update(f.read())

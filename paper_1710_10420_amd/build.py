@@ -28,6 +28,8 @@ SOURCES = [("prs_fwd3d.hip", "prs_fwd3d_f32", ["-DPRS_REAL=float"]),
            ("prs_fwd2d.hip", "prs_fwd2d_f64", ["-DPRS_REAL=double"]),
            ("prs_fwd3d.hip", "prs_fwd3d_f64", ["-DPRS_REAL=double"]),
            ("prs_adjoint.hip", "prs_adjoint_f64", ["-DPRS_REAL=double"]),
+           ("prs_adjoint3d.hip", "prs_adjoint3d_f32", ["-DPRS_REAL=float"]),
+           ("prs_adjoint3d.hip", "prs_adjoint3d_f64", ["-DPRS_REAL=double"]),
            ("prs_ensemble.hip", "prs_ensemble", []),
            ("prs_kernels.hip", "prs_kernels", []),
            ("prs_kernels_f64.hip", "prs_kernels_f64", []),

@@ -1082,28 +1082,32 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t span_rsrc(const R* base, uint3
 }
 
 // VEC values of this lane at byte offset voff of the span [base, base+bytes).
-template <int VEC, typename R>
+// Cache policy of fields that stream once through a working set that the
+// last-level cache could hold without them (the adjoint's stored fields).
+constexpr int kStream = 2;      // nontemporal
+
+template <int VEC, int AUX = 0, typename R>
 __device__ __forceinline__ void buf_load(const R* base, uint32_t bytes, uint32_t voff, R (&v)[VEC])
 {
     static_assert(VEC * sizeof(R) <= 16, "at most 16 bytes per lane and access");
     const __amdgpu_buffer_rsrc_t r = span_rsrc(base, bytes);
     if constexpr (sizeof(R) == 8 && VEC == 2) {
-        const auto t = __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0);
+        const auto t = __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, AUX);
         v[0] = u64_as_double(t[0], t[1]);
         v[1] = u64_as_double(t[2], t[3]);
     } else if constexpr (sizeof(R) == 8) {
-        const auto t = __builtin_amdgcn_raw_buffer_load_b64(r, voff, 0, 0);
+        const auto t = __builtin_amdgcn_raw_buffer_load_b64(r, voff, 0, AUX);
         v[0] = u64_as_double(t[0], t[1]);
     } else if constexpr (VEC == 4) {
-        const auto t = __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0);
+        const auto t = __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, AUX);
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] = __uint_as_float(t[j]);
     } else if constexpr (VEC == 2) {
-        const auto t = __builtin_amdgcn_raw_buffer_load_b64(r, voff, 0, 0);
+        const auto t = __builtin_amdgcn_raw_buffer_load_b64(r, voff, 0, AUX);
         v[0] = __uint_as_float(t[0]);
         v[1] = __uint_as_float(t[1]);
     } else {
-        v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, 0, 0));
+        v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, 0, AUX));
     }
 }
 
@@ -1114,7 +1118,7 @@ __device__ __forceinline__ void buf_load(const R* base, uint32_t bytes, uint32_t
 #define PRS_STORE_AUX 0
 #endif
 
-template <int VEC, typename R>
+template <int VEC, int AUX = PRS_STORE_AUX, typename R>
 __device__ __forceinline__ void buf_store(R* base, uint32_t bytes, uint32_t soff, const R (&v)[VEC])
 {
     static_assert(VEC * sizeof(R) <= 16, "at most 16 bytes per lane and access");
@@ -1132,11 +1136,11 @@ __device__ __forceinline__ void buf_store(R* base, uint32_t bytes, uint32_t soff
         }
     }
     if constexpr (W == 4) {
-        __builtin_amdgcn_raw_buffer_store_b128(t, r, soff, 0, PRS_STORE_AUX);
+        __builtin_amdgcn_raw_buffer_store_b128(t, r, soff, 0, AUX);
     } else if constexpr (W == 2) {
-        __builtin_amdgcn_raw_buffer_store_b64(t, r, soff, 0, PRS_STORE_AUX);
+        __builtin_amdgcn_raw_buffer_store_b64(t, r, soff, 0, AUX);
     } else {
-        __builtin_amdgcn_raw_buffer_store_b32(t[0], r, soff, 0, PRS_STORE_AUX);
+        __builtin_amdgcn_raw_buffer_store_b32(t[0], r, soff, 0, AUX);
     }
 }
 
@@ -2230,13 +2234,13 @@ struct TB3LLane {
 };
 
 // Rows R of one plane of field f at plane p for this wave.
-template <int VEC, int R, typename RT>
+template <int VEC, int R, int AUX = 0, typename RT>
 __device__ __forceinline__ void tb3l_load(const RT* f, int32_t p, const TB3LLane<R>& L, uint32_t bytes,
                                           RT (&v)[R][VEC])
 {
     const RT* base = f + (size_t)(uint32_t)p * L.plane;
 #pragma unroll
-    for (int r = 0; r < R; ++r) buf_load<VEC>(base, bytes, L.lrow[r], v[r]);
+    for (int r = 0; r < R; ++r) buf_load<VEC, AUX>(base, bytes, L.lrow[r], v[r]);
 }
 
 // LDS slot of (level k, plane parity, wave w, side 0 first row / 1 last row)
@@ -2265,7 +2269,7 @@ __device__ __forceinline__ void tb3l_put(RT* p, const RT (&v)[VEC])
 // where the other march spills (1024^3: 4.53 ms for five steps, 6.3 spilled,
 // and 4.4 ms for four).  Small tiles pay for the idle levels (128^3 25 us a
 // pass for 19), so lengths up to four keep the other march.
-template <int VEC, int T, int R, int NW, bool DIAG, bool UNIT, bool CHECK, int U, bool ALL, bool FLAT, typename RT>
+template <int VEC, int T, int R, int NW, bool DIAG, bool UNIT, bool CHECK, int U, int ALL, bool FLAT, typename RT>
 __device__ __forceinline__ void tb3l_iter(const TB3Args<T, RT>& A, const TB3LLane<R>& L, RT* lds, int32_t i,
                                           int32_t last, TBRows& rw, TB3LState<VEC, T, R, RT>& S, DiagAcc& acc)
 {
@@ -2356,10 +2360,10 @@ __device__ __forceinline__ void tb3l_iter(const TB3Args<T, RT>& A, const TB3LLan
                     const int32_t e = i - (T + k - 2);
                     const bool in = e >= 0 && e < L.s1 - L.s0;
                     const size_t lb = (size_t)(uint32_t)((in ? L.s0 + e : L.s0) + L.zoff) * L.plane;
-                    buf_store<VEC>(A.phi_lv[k < T ? k - 1 : 0] + lb, in ? L.plane_bytes : 0u, L.srow[r], out_phi);
+                    buf_store<VEC, ALL == 2 ? kStream : 0>(A.phi_lv[k < T ? k - 1 : 0] + lb, in ? L.plane_bytes : 0u, L.srow[r], out_phi);
                 }
             } else {
-                buf_store<VEC>(A.phi_out + obase, sb, L.srow[r], out_phi);
+                buf_store<VEC, ALL == 2 ? kStream : PRS_STORE_AUX>(A.phi_out + obase, sb, L.srow[r], out_phi);
                 buf_store<VEC>(A.pi_out + obase, sb, L.srow[r], out_pi);
             }
             if constexpr (FLAT) __builtin_amdgcn_sched_barrier(0);
@@ -2373,7 +2377,7 @@ __device__ __forceinline__ void tb3l_iter(const TB3Args<T, RT>& A, const TB3LLan
     __syncthreads();
 }
 
-template <int VEC, int T, int R, int NW, bool DIAG, bool UNIT, bool CHECK, bool ALL, typename RT>
+template <int VEC, int T, int R, int NW, bool DIAG, bool UNIT, bool CHECK, int ALL, typename RT>
 __device__ __forceinline__ bool tb3l_group(const TB3Args<T, RT>& A, const TB3LLane<R>& L, RT* lds, int32_t i,
                                            int32_t last, TBRows& rw, TB3LState<VEC, T, R, RT>& S, DiagAcc& acc)
 {
@@ -2414,7 +2418,7 @@ constexpr int tb3l_min_waves(int vec, int T, int R, int NW, int esize, bool diag
 }
 
 // One workgroup's tile of the LDS pass; all its waves run the same march.
-template <int VEC, int T, int R, int NW, bool DIAG, bool UNIT, bool ALL, typename RT>
+template <int VEC, int T, int R, int NW, bool DIAG, bool UNIT, int ALL, typename RT>
 __device__ __forceinline__ void tb3l_tile(const TB3Args<T, RT>& A, int64_t tile, RT* lds)
 {
     const int H = A.hx;
@@ -2514,7 +2518,7 @@ __device__ __forceinline__ void tb3l_tile(const TB3Args<T, RT>& A, int64_t tile,
     }
 }
 
-template <int VEC, int T, int R, int NW, bool DIAG, bool UNIT, bool ALL, typename RT>
+template <int VEC, int T, int R, int NW, bool DIAG, bool UNIT, int ALL, typename RT>
 __global__ __launch_bounds__(NW * kWave)
 __attribute__((amdgpu_waves_per_eu(tb3l_min_waves(VEC, T, R, NW, (int)sizeof(RT), DIAG)))) void k_tb3l(TB3Args<T, RT> A)
 {
@@ -2542,6 +2546,7 @@ struct TBA3Args {
     int64_t nx, ny, nz;
     int64_t tiles_x, tiles_y, ntiles;
     int64_t rows;
+    int32_t hx;                 // the LDS pass: halo lanes on each side of a wave's rows
     R a[T], b[T], cw[T], F[T];
     R kc, inv_dx2;
     double gscale[T];
@@ -2737,6 +2742,238 @@ __global__ __launch_bounds__(kBlock) void k_tba3d(TBA3Args<T, R> A)
 #pragma unroll
     for (int k = 0; k < T; ++k) gsum += A.gscale[k] * wave_sum_f64(gs[k]);
     if (lane == 0) A.gacc[tile] += gsum;
+}
+
+// ------------- reverse sweep, T steps per pass (3D) with LDS-shared halos ---
+//
+// The reverse pass on the workgroup of k_tb3l: NW waves of R rows stacked
+// along y, w the stencil field whose boundary rows pass between the waves
+// through LDS, mu and each level's phi^{m-k+1} plane pointwise.  Bound by its
+// traffic of 4 + T fields a pass at large lattices and by the chain of an
+// iteration at small ones.  Sharing the rows makes three and four steps a
+// pass cheap: at 256^3 40 us a step (four steps), where k_tba3d takes 48
+// (three steps, each row of a plane read by two to three waves).  NT: phi is read nontemporally
+// (streams_fields).
+
+template <int VEC, int T, int R, typename RT>
+struct TBA3LState {
+    RT in[4][R][VEC];           // w planes, ring over the march
+    RT mi[2][R][VEC];           // mu planes
+    RT lv[T][4][R][VEC];        // level k w planes (k = 1 .. T-1)
+    RT ml[T][2][R][VEC];        // level k mu planes
+    RT ph[T][2][R][VEC];        // phi plane of each level, one iteration ahead
+};
+
+template <int VEC, int T, int R, int NW, bool UNIT, bool CHECK, int U, bool NT, typename RT>
+__device__ __forceinline__ void tba3l_iter(const TBA3Args<T, RT>& A, const TB3LLane<R>& L, RT* lds, int32_t i,
+                                           int32_t last, TBRows& rw, int32_t (&prow)[T],
+                                           TBA3LState<VEC, T, R, RT>& S, double (&gs)[T])
+{
+    const uint32_t nb = i < last ? L.plane_bytes : 0u;
+    tb3l_load<VEC, R>(A.w_in, rw.phi, L, nb, S.in[(U + 2) & 3]);
+    tb3l_load<VEC, R>(A.mu_in, rw.pi, L, nb, S.mi[(U + 1) & 1]);
+    rw.phi = next_row(rw.phi, L.nz);
+    rw.pi = next_row(rw.pi, L.nz);
+#pragma unroll
+    for (int k = 0; k < T; ++k) {
+        tb3l_load<VEC, R, NT ? kStream : 0>(A.phi[k], prow[k], L, nb, S.ph[k][(U + 1) & 1]);
+        prow[k] = next_row(prow[k], L.nz);
+    }
+    tb3l_put<VEC>(tb3l_slot<VEC, NW>(lds, 0, U & 1, L.wave, 0), S.in[(U + 1) & 3][0]);
+    tb3l_put<VEC>(tb3l_slot<VEC, NW>(lds, 0, U & 1, L.wave, 1), S.in[(U + 1) & 3][R - 1]);
+    const int wb = L.wave > 0 ? L.wave - 1 : 0;
+    const int wa = L.wave < NW - 1 ? L.wave + 1 : NW - 1;
+#pragma unroll
+    for (int k = 1; k <= T; ++k) {
+        if (CHECK && i < 2 * (k - 1)) continue;
+        const RT(*cm)[VEC];
+        const RT(*cc)[VEC];
+        const RT(*cp)[VEC];
+        const RT(*mp)[VEC];
+        if (k == 1) {
+            cm = S.in[(U + 3) & 3];
+            cc = S.in[U & 3];
+            cp = S.in[(U + 1) & 3];
+            mp = S.mi[U & 1];
+        } else {
+            cm = S.lv[k - 1][(U + 2) & 3];
+            cc = S.lv[k - 1][(U + 3) & 3];
+            cp = S.lv[k - 1][U & 3];
+            mp = S.ml[k - 1][(U + 1) & 1];
+        }
+        const RT(*ph)[VEC] = S.ph[k - 1][U & 1];
+        RT yb[VEC], ya[VEC];
+        {
+            const RT* pb = tb3l_slot<VEC, NW>(lds, k - 1, (U + 1) & 1, wb, L.wave > 0 ? 1 : 0);
+            const RT* pa = tb3l_slot<VEC, NW>(lds, k - 1, (U + 1) & 1, wa, L.wave < NW - 1 ? 0 : 1);
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) {
+                yb[j] = pb[j];
+                ya[j] = pa[j];
+            }
+        }
+        const int32_t e = i - (T + k - 2);
+        const bool own_plane = e >= 0 && e < L.s1 - L.s0;
+        const int32_t zout = L.s0 + i - (2 * T - 2);
+        const bool stored = !CHECK || i >= 2 * T - 2;
+        const uint32_t sb = stored ? L.plane_bytes : 0u;
+        const size_t obase = (size_t)(uint32_t)(stored ? zout : L.s0) * L.plane;
+        double g = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const RT left = from_left_ring(cc[r][VEC - 1]);
+            const RT right = from_right_ring(cc[r][0]);
+            RT out_w[VEC], out_mu[VEC];
+            double gr = 0.0;
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) {
+                const RT xm = j > 0 ? cc[r][j > 0 ? j - 1 : 0] : left;
+                const RT xp = j < VEC - 1 ? cc[r][j < VEC - 1 ? j + 1 : j] : right;
+                const RT ym = r > 0 ? cc[r > 0 ? r - 1 : 0][j] : yb[j];
+                const RT yp = r < R - 1 ? cc[r < R - 1 ? r + 1 : r][j] : ya[j];
+                const RT gp = adj_site<3, UNIT>(cc[r][j], nsum3(xm, xp, ym, yp, cm[r][j], cp[r][j]), mp[r][j], ph[r][j],
+                                                A.a[k - 1], A.b[k - 1], A.cw[k - 1], A.F[k - 1], A.kc, A.inv_dx2,
+                                                out_w[j], out_mu[j]);
+                gr += (double)gp;
+            }
+            // owned rows only (a wave-uniform factor: no per-lane select)
+            g = fma(gr, (L.own_rows >> r) & 1u ? 1.0 : 0.0, g);
+            if (k < T) {
+#pragma unroll
+                for (int j = 0; j < VEC; ++j) {
+                    S.lv[k < T ? k : 0][U & 3][r][j] = out_w[j];
+                    S.ml[k < T ? k : 0][U & 1][r][j] = out_mu[j];
+                }
+            } else {
+                buf_store<VEC>(A.w_out + obase, sb, L.srow[r], out_w);
+                buf_store<VEC>(A.mu_out + obase, sb, L.srow[r], out_mu);
+            }
+        }
+        if (own_plane) gs[k - 1] = fma(g, L.own_lane ? 1.0 : 0.0, gs[k - 1]);
+        if (k < T) {
+            tb3l_put<VEC>(tb3l_slot<VEC, NW>(lds, k, U & 1, L.wave, 0), S.lv[k < T ? k : 0][U & 3][0]);
+            tb3l_put<VEC>(tb3l_slot<VEC, NW>(lds, k, U & 1, L.wave, 1), S.lv[k < T ? k : 0][U & 3][R - 1]);
+        }
+    }
+    __syncthreads();
+}
+
+template <int VEC, int T, int R, int NW, bool UNIT, bool CHECK, bool NT, typename RT>
+__device__ __forceinline__ bool tba3l_group(const TBA3Args<T, RT>& A, const TB3LLane<R>& L, RT* lds, int32_t i,
+                                            int32_t last, TBRows& rw, int32_t (&prow)[T],
+                                            TBA3LState<VEC, T, R, RT>& S, double (&gs)[T])
+{
+    tba3l_iter<VEC, T, R, NW, UNIT, CHECK, 0, NT>(A, L, lds, i, last, rw, prow, S, gs);
+    if (i + 1 > last) return false;
+    tba3l_iter<VEC, T, R, NW, UNIT, CHECK, 1, NT>(A, L, lds, i + 1, last, rw, prow, S, gs);
+    if (i + 2 > last) return false;
+    tba3l_iter<VEC, T, R, NW, UNIT, CHECK, 2, NT>(A, L, lds, i + 2, last, rw, prow, S, gs);
+    if (i + 3 > last) return false;
+    tba3l_iter<VEC, T, R, NW, UNIT, CHECK, 3, NT>(A, L, lds, i + 3, last, rw, prow, S, gs);
+    return i + 4 <= last;
+}
+
+template <int VEC, int T, int R, int NW, bool UNIT, bool NT, typename RT>
+__global__ __launch_bounds__(NW * kWave)
+__attribute__((amdgpu_waves_per_eu(NW == 16 ? 4 : 2))) void k_tba3l(TBA3Args<T, RT> A)
+{
+    constexpr int YOWN = tb3l_own_rows(NW, R, T);
+    constexpr int WARM = (2 * T - 2 + 3) / 4;
+    __shared__ RT lds[T * 2 * NW * 2 * kWave * VEC];
+    const int64_t tile = uniform64(xcd_remap(blockIdx.x, gridDim.x));
+    if (tile >= A.ntiles) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t tl = __builtin_amdgcn_readfirstlane((uint32_t)tile);
+    const uint32_t tx = tl % (uint32_t)A.tiles_x;
+    const uint32_t rest = tl / (uint32_t)A.tiles_x;
+    const uint32_t tyi = rest % (uint32_t)A.tiles_y;
+    const uint32_t tz = rest / (uint32_t)A.tiles_y;
+    const int32_t nx = (int32_t)A.nx, ny = (int32_t)A.ny;
+    const int H = A.hx;
+    const int W = (kWave - 2 * H) * VEC;
+    TB3LLane<R> L;
+    L.wave = wave_in_block();
+    L.nz = L.zwrap = (int32_t)A.nz;
+    L.zoff = 0;
+    L.plane = (uint64_t)A.nx * (uint64_t)A.ny;
+    L.plane_bytes = (uint32_t)(L.plane * sizeof(RT));
+    const int32_t x0 = (int32_t)(tx * (uint32_t)W) + (lane - H) * VEC;
+    const uint32_t xw = (uint32_t)wrap_row(x0, nx);
+    L.own_lane = lane >= H && lane < kWave - H && x0 < nx;
+    const int32_t y0 = (int32_t)tyi * YOWN;
+    L.own_rows = 0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int32_t wr = L.wave * R + r - T;
+        L.lrow[r] = ((uint32_t)wrap_row(y0 + wr, ny) * (uint32_t)nx + xw) * (uint32_t)sizeof(RT);
+        const bool own = wr >= 0 && wr < YOWN && y0 + wr < ny;
+        L.own_rows |= own ? (1u << r) : 0u;
+        L.srow[r] = (own && L.own_lane) ? L.lrow[r] : kPastRow;
+    }
+    const int32_t rows = (int32_t)A.rows;
+    L.s0 = (int32_t)tz * rows;
+    L.s1 = L.s0 + rows < L.nz ? L.s0 + rows : L.nz;
+
+    TBA3LState<VEC, T, R, RT> S;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) {
+                S.in[a][r][j] = RT(0);
+#pragma unroll
+                for (int k = 0; k < T; ++k) S.lv[k][a][r][j] = RT(0);
+            }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) {
+                S.mi[a][r][j] = RT(0);
+#pragma unroll
+                for (int k = 0; k < T; ++k) S.ml[k][a][r][j] = S.ph[k][a][r][j] = RT(0);
+            }
+
+    const int32_t z0 = L.s0 - T + 1;
+    tb3l_load<VEC, R>(A.w_in, wrap_row(z0 - 1, L.nz), L, L.plane_bytes, S.in[3]);
+    tb3l_load<VEC, R>(A.w_in, wrap_row(z0, L.nz), L, L.plane_bytes, S.in[0]);
+    tb3l_load<VEC, R>(A.w_in, wrap_row(z0 + 1, L.nz), L, L.plane_bytes, S.in[1]);
+    tb3l_load<VEC, R>(A.mu_in, wrap_row(z0, L.nz), L, L.plane_bytes, S.mi[0]);
+    int32_t prow[T];
+#pragma unroll
+    for (int k = 0; k < T; ++k) {
+        tb3l_load<VEC, R, NT ? kStream : 0>(A.phi[k], wrap_row(z0 - k, L.nz), L, L.plane_bytes, S.ph[k][0]);
+        prow[k] = wrap_row(z0 - k + 1, L.nz);
+    }
+    TBRows rw;
+    rw.phi = wrap_row(z0 + 2, L.nz);
+    rw.pi = wrap_row(z0 + 1, L.nz);
+    // level 1 of iteration 0 reads the boundary rows of plane z0 (parity 1)
+    tb3l_put<VEC>(tb3l_slot<VEC, NW>(lds, 0, 1, L.wave, 0), S.in[0][0]);
+    tb3l_put<VEC>(tb3l_slot<VEC, NW>(lds, 0, 1, L.wave, 1), S.in[0][R - 1]);
+    __syncthreads();
+    double gs[T];
+#pragma unroll
+    for (int k = 0; k < T; ++k) gs[k] = 0.0;
+
+    const int32_t last = (L.s1 - L.s0) + 2 * T - 3;
+    int32_t i = 0;
+    bool more = true;
+#pragma unroll
+    for (int w = 0; w < WARM; ++w) {
+        if (more) more = tba3l_group<VEC, T, R, NW, UNIT, true, NT>(A, L, lds, i, last, rw, prow, S, gs);
+        i += 4;
+    }
+    while (more) {
+        more = tba3l_group<VEC, T, R, NW, UNIT, false, NT>(A, L, lds, i, last, rw, prow, S, gs);
+        i += 4;
+    }
+    double gsum = 0.0;
+#pragma unroll
+    for (int k = 0; k < T; ++k) gsum += A.gscale[k] * wave_sum_f64(gs[k]);
+    if (lane == 0) A.gacc[tile * NW + L.wave] += gsum;
 }
 
 // ------------------------------------------------------ launch templates --
@@ -3303,7 +3540,20 @@ constexpr bool tb3l_combo_ok(int vec, int T, int rows_per_wave, int nw = 8)
 __host__ __device__ __forceinline__ int tb3l_waves(int ty) { return ty >= 32 ? 16 : 8; }
 __host__ __device__ __forceinline__ int tb3l_rows_per_wave(int ty) { return ty >= 32 ? ty / 16 : ty / 4; }
 
-template <typename R, int VEC, int T, int RW, int NW>
+// The adjoint's passes go round four fields (w, mu and their outputs; phi,
+// phi_dot and theirs).  Where those take a good part of the 256 MB last-level
+// cache, the stored fields that stream beside them are written and read
+// nontemporally: recomputation of four steps 91 -> 67 us at 224^3 and 142 ->
+// 125 at 256^3, reverse pass of three 129 -> 114; below, the cache keeps some
+// of them for the reverse sweep (192^3 41 us against 45 nontemporal).
+bool streams_fields(const Geometry& g)
+{
+    return 4.0 * (double)g.nx * (double)g.Q * (double)g.M * (g.f64 ? 8 : 4) > 150e6;
+}
+
+// LV: the recomputation, which stores every step's field (phi_lv), else the
+// plain and diagnostic passes.
+template <typename R, int VEC, int T, int RW, int NW, bool LV>
 hipError_t launch_tb3l_t(const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out, const void* pi_in,
                          void* pi_out, void* const* phi_lv, const StepCoef64* k, bool diag, WavePartial* partials,
                          const DiagCoef& dc, hipStream_t s, int zhalo = 0)
@@ -3330,25 +3580,28 @@ hipError_t launch_tb3l_t(const Geometry& g, const Tiling& t, const void* phi_in,
     A.dc = dc;
     const unsigned blocks = (unsigned)A.ntiles;
     const bool unit = A.k[0].inv_dx2 == R(1) && A.k[0].kc == R(1);
-    if constexpr (T <= 4) {
-        if (phi_lv) {
-            if (unit) hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, true, true, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
-            else hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, false, true, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
-            return hipGetLastError();
+    const dim3 grid(blocks), block(NW * kWave);
+    if constexpr (LV) {
+        if (unit && T > 2 && streams_fields(g))
+            hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, true, (T > 2 ? 2 : 1), R>), grid, block, 0, s, A);
+        else if (unit) hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, true, 1, R>), grid, block, 0, s, A);
+        else hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, false, 1, R>), grid, block, 0, s, A);
+    } else {
+        if constexpr (T <= 4) {
+            if (diag) {
+                hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, true, false, 0, R>), grid, block, 0, s, A);
+                return hipGetLastError();
+            }
         }
-        if (diag) {
-            hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, true, false, false, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
-            return hipGetLastError();
-        }
+        if (unit) hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, true, 0, R>), grid, block, 0, s, A);
+        else hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, false, 0, R>), grid, block, 0, s, A);
     }
-    if (unit) hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, true, false, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
-    else hipLaunchKernelGGL((k_tb3l<VEC, T, RW, NW, false, false, false, R>), dim3(blocks), dim3(NW * kWave), 0, s, A);
     return hipGetLastError();
 }
 
 // phi_lv non-NULL: the recomputation storing every step's field (phi_out is
 // then phi_lv[T-1]).
-template <typename R>
+template <typename R, bool LV>
 hipError_t launch_tb3l_r(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out,
                          const void* pi_in, void* pi_out, void* const* phi_lv, const StepCoef64* k, bool diag,
                          WavePartial* partials, const DiagCoef& dc, hipStream_t s, int zhalo = 0)
@@ -3358,7 +3611,7 @@ hipError_t launch_tb3l_r(int T, const Geometry& g, const Tiling& t, const void* 
 #define PRS_TB3L(V, TT, RR, WW)                                                                                 \
     if (t.vec == V && T == TT && RW == RR && NW == WW) {                                                         \
         if constexpr (tb3l_combo_ok<R>(V, TT, RR, WW))                                                           \
-            return launch_tb3l_t<R, V, TT, RR, WW>(g, t, phi_in, phi_out, pi_in, pi_out, phi_lv, k, diag, partials, \
+            return launch_tb3l_t<R, V, TT, RR, WW, LV>(g, t, phi_in, phi_out, pi_in, pi_out, phi_lv, k, diag, partials, \
                                                    dc, s, zhalo);                                                \
     }
     PRS_TB3L(1, 2, 2, 8)
@@ -3435,7 +3688,7 @@ hipError_t launch_tb3d_r(int T, const Geometry& g, const Tiling& t, const void* 
                          const DiagCoef& dc, hipStream_t s, int zhalo = 0)
 {
     if (tb3l_tiling(t.ty))
-        return launch_tb3l_r<R>(T, g, t, phi_in, phi_out, pi_in, pi_out, nullptr, k, diag, partials, dc, s, zhalo);
+        return launch_tb3l_r<R, false>(T, g, t, phi_in, phi_out, pi_in, pi_out, nullptr, k, diag, partials, dc, s, zhalo);
     const int TY = tb3_rows(t.ty);
     if (!tb3_combo_ok<R>(t.vec, T, TY)) return hipErrorInvalidValue;
 #define PRS_TB3(V, TT, YY)                                                                                   \
@@ -3451,6 +3704,82 @@ hipError_t launch_tb3d_r(int T, const Geometry& g, const Tiling& t, const void* 
     PRS_TB3(1, 3, 8)
     PRS_TB3(2, 3, 4)
 #undef PRS_TB3
+    return hipErrorInvalidValue;
+}
+
+// The LDS reverse pass (k_tba3l): eight-wave workgroups, T = 2, 3, 4 where the
+// rings fit 256 registers.
+template <typename R>
+constexpr bool tba3l_combo_ok(int vec, int T, int rows_per_wave, int nw)
+{
+    if (nw != 8 || T < 2 || T > 4 || (rows_per_wave != 2 && rows_per_wave != 4)) return false;
+    const int words = vec * rows_per_wave * (int)sizeof(R) / 4;     // a plane's registers
+    return (sizeof(R) == 8 ? vec == 1 : vec <= 2) && (words <= 4 || T <= 3);
+}
+
+template <typename R, int VEC, int T, int RW>
+hipError_t launch_tba3l_t(const Geometry& g, const Tiling& t, const void* w_in, void* w_out, const void* mu_in,
+                          void* mu_out, const void* const* phi, double* gacc, const AdjCoef64* c, hipStream_t s)
+{
+    constexpr int NW = 8;
+    TBA3Args<T, R> A;
+    A.w_in = static_cast<const R*>(w_in);
+    A.w_out = static_cast<R*>(w_out);
+    A.mu_in = static_cast<const R*>(mu_in);
+    A.mu_out = static_cast<R*>(mu_out);
+    for (int i = 0; i < T; ++i) {
+        A.phi[i] = static_cast<const R*>(phi[i]);
+        A.a[i] = (R)c[i].a;
+        A.b[i] = (R)c[i].b;
+        A.cw[i] = (R)c[i].cw;
+        A.F[i] = (R)c[i].F;
+        A.gscale[i] = c[i].gscale;
+    }
+    A.kc = (R)c[0].kc;
+    A.inv_dx2 = (R)c[0].inv_dx2;
+    A.gacc = gacc;
+    A.nx = g.nx;
+    A.ny = g.Q;
+    A.nz = g.M;
+    const int64_t W = tb3l_width(g.nx, VEC, T);
+    A.hx = tb3l_halo(g.nx, VEC, T);
+    constexpr int YOWN = tb3l_own_rows(NW, RW, T);
+    A.tiles_x = (g.nx + W - 1) / W;
+    A.tiles_y = (g.Q + YOWN - 1) / YOWN;
+    A.ntiles = A.tiles_x * A.tiles_y * ((g.M + t.rows - 1) / t.rows);   // workgroups
+    A.rows = t.rows;
+    const dim3 grid((unsigned)A.ntiles), block(NW * kWave);
+    const bool unit = A.inv_dx2 == R(1) && A.kc == R(1);
+    if (unit && streams_fields(g)) hipLaunchKernelGGL((k_tba3l<VEC, T, RW, NW, true, true, R>), grid, block, 0, s, A);
+    else if (unit) hipLaunchKernelGGL((k_tba3l<VEC, T, RW, NW, true, false, R>), grid, block, 0, s, A);
+    else hipLaunchKernelGGL((k_tba3l<VEC, T, RW, NW, false, false, R>), grid, block, 0, s, A);
+    return hipGetLastError();
+}
+
+template <typename R>
+hipError_t launch_tba3l_r(int T, const Geometry& g, const Tiling& t, const void* w_in, void* w_out,
+                          const void* mu_in, void* mu_out, const void* const* phi, double* gacc, const AdjCoef64* c,
+                          hipStream_t s)
+{
+    const int RW = tb3l_rows_per_wave(t.ty);
+    if (!tb3l_tiling(t.ty) || !tba3l_combo_ok<R>(t.vec, T, RW, tb3l_waves(t.ty))) return hipErrorInvalidValue;
+#define PRS_TBA3L(V, TT, RR)                                                                              \
+    if (t.vec == V && T == TT && RW == RR) {                                                              \
+        if constexpr (tba3l_combo_ok<R>(V, TT, RR, 8))                                                    \
+            return launch_tba3l_t<R, V, TT, RR>(g, t, w_in, w_out, mu_in, mu_out, phi, gacc, c, s);       \
+    }
+    PRS_TBA3L(1, 2, 2)
+    PRS_TBA3L(1, 3, 2)
+    PRS_TBA3L(1, 4, 2)
+    PRS_TBA3L(1, 2, 4)
+    PRS_TBA3L(1, 3, 4)
+    PRS_TBA3L(1, 4, 4)
+    PRS_TBA3L(2, 2, 2)
+    PRS_TBA3L(2, 3, 2)
+    PRS_TBA3L(2, 4, 2)
+    PRS_TBA3L(2, 2, 4)
+    PRS_TBA3L(2, 3, 4)
+#undef PRS_TBA3L
     return hipErrorInvalidValue;
 }
 
@@ -3534,7 +3863,7 @@ hipError_t launch_tb3_all_r(int T, const Geometry& g, const Tiling& t, const voi
                             const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s)
 {
     if (tb3l_tiling(t.ty))
-        return launch_tb3l_r<R>(T, g, t, phi_in, phi_lv[T - 1], pi_in, pi_out, phi_lv, k, false, nullptr, DiagCoef{},
+        return launch_tb3l_r<R, true>(T, g, t, phi_in, phi_lv[T - 1], pi_in, pi_out, phi_lv, k, false, nullptr, DiagCoef{},
                                 s);
     const int TY = tb3_rows(t.ty);
     if (!tb3_combo_ok<R>(t.vec, T, TY)) return hipErrorInvalidValue;

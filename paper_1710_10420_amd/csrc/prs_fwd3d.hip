@@ -30,7 +30,7 @@ hipError_t launch_tb3_deep_p(const Geometry& g, const Tiling& t, const void* phi
 {
     constexpr int VEC = sizeof(R) == 4 ? 2 : 1;     // 512 bytes a wave and row
     if (t.vec != VEC || tb3l_waves(t.ty) != 8 || tb3l_rows_per_wave(t.ty) != 4) return hipErrorInvalidValue;
-    return launch_tb3l_t<R, VEC, kDeepSteps, 4, 8>(g, t, phi_in, phi_out, pi_in, pi_out, nullptr, k, false, nullptr,
+    return launch_tb3l_t<R, VEC, kDeepSteps, 4, 8, false>(g, t, phi_in, phi_out, pi_in, pi_out, nullptr, k, false, nullptr,
                                                    DiagCoef{}, s);
 }
 

@@ -250,6 +250,11 @@ template <typename R>
 hipError_t launch_tb_all_p(int T, const Geometry& g, const Tiling& t, const void* phi_in, void* const* phi_lv,
                            const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s);
 template <typename R>
+hipError_t launch_tba3l_p(int T, const Geometry& g, const Tiling& t, const void* w_in, void* w_out,
+                          const void* mu_in, void* mu_out, const void* const* phi, double* gacc, const AdjCoef64* c,
+                          hipStream_t s);
+
+template <typename R>
 hipError_t launch_tba_p(int T, const Geometry& g, const Tiling& t, const void* w_in, void* w_out,
                         const void* mu_in, void* mu_out, const void* const* phi, double* gacc, const AdjCoef64* c,
                         hipStream_t s);

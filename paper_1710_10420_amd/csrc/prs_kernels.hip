@@ -323,9 +323,10 @@ const Pass3Shape* pass3_shapes(bool f64, int* n)
 
 // Estimated time of an LDS pass: the time of a round of workgroups
 // (iterations, each a constant and the resident workgroups' rows and levels)
-// times the rounds, or of the memory traffic where that is longer.
+// times the rounds, or of the memory traffic where that is longer.  reverse:
+// the adjoint's pass, which reads T fields besides w and mu.
 struct Pass3Time {
-    Pass3Time(const Geometry& lattice, const Pass3Shape& h) : g(lattice), T(h.T)
+    Pass3Time(const Geometry& lattice, const Pass3Shape& h, bool rev = false) : g(lattice), T(h.T), reverse(rev)
     {
         size = g.f64 ? 8 : 4;
         sites = (double)g.nx * (double)g.Q * (double)g.M;
@@ -333,13 +334,14 @@ struct Pass3Time {
         const int nw = tb3l_waves(h.ty), r = tb3l_rows_per_wave(h.ty);
         const int64_t w = tb3l_width(g.nx, h.vec, T), y = tb3l_own_rows(nw, r, T);
         cols = ((g.nx + w - 1) / w) * ((g.Q + y - 1) / y);
-        const int waves = h.regs <= 64 ? 8 : h.regs <= 72 ? 7 : h.regs <= 80 ? 6 : h.regs <= 96 ? 5 : h.regs <= 128 ? 4 : 2;
+        const int waves = h.regs <= 64 ? 8 : h.regs <= 72 ? 7 : h.regs <= 80 ? 6 : h.regs <= 96 ? 5 : h.regs <= 128 ? 4 : h.regs <= 168 ? 3 : 2;
         held = std::max(1, 4 * waves / nw);
         area = (double)(nw * r * h.vec);
     }
     double us(int64_t rows) const
     {
-        const double site = g.f64 ? 0.0060 : 0.00353, bw = cached ? 8.8e3 : 5.5e3;
+        const double site = (g.f64 ? 0.0060 : 0.00353) * (reverse ? 1.7 : 1.0);
+        const double bw = cached && !reverse ? 8.8e3 : 5.5e3;
         const int64_t wgs = cols * ((g.M + rows - 1) / rows);
         const double iters = (double)(rows + 2 * T - 2);
         auto iter = [&](double m) { return 0.18 + m * area * (T + 1) * site; };
@@ -350,12 +352,32 @@ struct Pass3Time {
             const double rounds = (double)wgs / (256.0 * held), full = std::floor(rounds), rest = rounds - full;
             t = 4.46 + iters * (full * iter(held) + (rest > 0 ? iter(std::max(1.0, std::ceil(rest * held))) : 0.0));
         }
-        const double read = (double)wgs * kWave * area * (2.0 * (double)rows + 4.0 * T - 2.0) * size;
+        const double planes = reverse ? (2.0 + T) * (double)rows + 4.0 * T - 2.0 : 2.0 * (double)rows + 4.0 * T - 2.0;
+        const double read = (double)wgs * kWave * area * planes * size;
         const double mem = (0.75 * read + 2.5 * sites * size) / (bw * 1e3);
         return mem > t ? mem + 0.15 * t : t + 0.15 * mem;
     }
+    // The fastest of the heights that give one to four whole rounds and two
+    // or three plain ones.
+    int64_t best_rows(int64_t least) const
+    {
+        int64_t best = 32;
+        for (int k = 0; k < 6; ++k) {
+            int64_t rows = k == 4 ? 16 : 64;
+            if (k < 4) {
+                const int64_t tz = 256 * (int64_t)held * (k + 1) / cols;
+                if (tz < 1) continue;
+                rows = std::min<int64_t>(64, std::max<int64_t>(least, (g.M + tz - 1) / tz));
+            } else if (k == 5 && cached) {
+                continue;
+            }
+            if (us(rows) < us(best)) best = rows;
+        }
+        return best;
+    }
     const Geometry& g;
     int T, held;
+    bool reverse;
     bool cached;
     int64_t cols;
     double size, sites, area;
@@ -377,22 +399,11 @@ PassChoice auto_pass3(const Geometry& g, int T)
         if (h.T != T || !tb_pass_supported(g, Tiling{h.vec, 32, h.ty}, std::min(T, 4))) continue;
         const Pass3Time p(g, h);
         if (p.cached ? T > 4 : !g.f64 && h.vec == 1 && g.nx % 2 == 0) continue;
-        // heights: the ones that give one to four whole rounds, and two or
-        // three plain ones
-        for (int k = 0; k < 7; ++k) {
-            int64_t rows = k == 4 ? 16 : k == 5 ? 32 : 64;
-            if (k < 4) {
-                const int64_t tz = 256 * (int64_t)p.held * (k + 1) / p.cols;
-                if (tz < 1) continue;
-                rows = std::min<int64_t>(64, std::max<int64_t>(4, (g.M + tz - 1) / tz));
-            } else if (k == 6 && p.cached) {
-                continue;
-            }
-            const double t = p.us(rows);
-            if (best.til.vec == 0 || t < best.us) {
-                best.us = (float)t;
-                best.til = Tiling{h.vec, (int)rows, h.ty};
-            }
+        const int64_t rows = p.best_rows(4);
+        const double t = p.us(rows);
+        if (best.til.vec == 0 || t < best.us) {
+            best.us = (float)t;
+            best.til = Tiling{h.vec, (int)rows, h.ty};
         }
     }
     return best;
@@ -411,17 +422,37 @@ PassChoice own_pass3(const Geometry& g, const Tiling& t, int T)
     return PassChoice{T, 0.0f, false, Tiling{0, 0, 0}};
 }
 
-// Reverse passes.  2D (fused, four steps): the shortest tiles with one site
+// Reverse passes.  3D (stored): the LDS reverse pass that the estimate ranks
+// first.  2D (fused, four steps): the shortest tiles with one site
 // per lane while they make at most two per SIMD; else two sites per lane and
 // one tile per SIMD if those are short, or two (the tuner's choice from
 // 128^2 to 3000 x 2000, the single steps of four sites per lane took 24
-// against 9 us a step at 2048^2).  3D (stored): three steps of one site per
-// lane, 16 planes (the tuner's choice at 128^3 and 256^3).
+// against 9 us a step at 2048^2).
 Tiling auto_adj_tile(const Geometry& g, int* T)
 {
     if (g.ndim == 3) {
-        *T = g.f64 ? 2 : 3;
-        return Tiling{1, g.M < 96 ? 8 : 16, 2};
+        static const Pass3Shape f32[] = {{1, 8, 2, 60},  {1, 8, 3, 82},   {1, 8, 4, 100},  {1, 16, 2, 112},
+                                         {1, 16, 3, 144}, {1, 16, 4, 180}, {2, 8, 2, 112},  {2, 8, 3, 144},
+                                         {2, 8, 4, 182}, {2, 16, 2, 180}, {2, 16, 3, 250}};
+        static const Pass3Shape f64s[] = {{1, 8, 2, 112}, {1, 8, 3, 144}, {1, 8, 4, 182}, {1, 16, 2, 180}, {1, 16, 3, 250}};
+        Tiling best{1, g.M < 96 ? 8 : 16, 2};
+        double least = 0.0;
+        *T = 2;
+        const Pass3Shape* list = g.f64 ? f64s : f32;
+        const int n = g.f64 ? (int)(sizeof f64s / sizeof f64s[0]) : (int)(sizeof f32 / sizeof f32[0]);
+        for (int i = 0; i < n; ++i) {
+            const Pass3Shape& h = list[i];
+            if (!tba_supported(g, Tiling{h.vec, (int)kMinRows, h.ty}, h.T)) continue;
+            const Pass3Time p(g, h, true);
+            const int64_t rows = p.best_rows(kMinRows);
+            const double us = p.us(rows) / h.T;
+            if (least == 0.0 || us < least) {
+                least = us;
+                *T = h.T;
+                best = Tiling{h.vec, (int)rows, h.ty};
+            }
+        }
+        return best;
     }
     *T = 4;
     Tiling t{1, (int)kMinRows, 1};
@@ -472,7 +503,10 @@ hipError_t launch_adj_seed(const Geometry& g, const void* phi, int64_t count, do
 bool tba_supported(const Geometry& g, const Tiling& t, int T)
 {
     if (!tb_supported(g) || !tiling_supported(g, t)) return false;
-    if (g.ndim == 3 && tb3l_tiling(t.ty)) return false;
+    if (g.ndim == 3 && tb3l_tiling(t.ty)) {
+        const int rw = tb3l_rows_per_wave(t.ty), nw = tb3l_waves(t.ty);
+        return g.f64 ? tba3l_combo_ok<double>(t.vec, T, rw, nw) : tba3l_combo_ok<float>(t.vec, T, rw, nw);
+    }
     if (g.ndim == 3) {
         const int TY = tb3_rows(t.ty);
         return g.f64 ? tba3_combo_ok<double>(t.vec, T, TY) : tba3_combo_ok<float>(t.vec, T, TY);
@@ -500,6 +534,9 @@ hipError_t launch_tba(int T, const Geometry& g, const Tiling& t, const void* w_i
                       void* mu_out, const void* const* phi, double* gacc, const AdjCoef64* c, hipStream_t s)
 {
     if (!tba_supported(g, t, T)) return hipErrorInvalidValue;
+    if (g.ndim == 3 && tb3l_tiling(t.ty))
+        return g.f64 ? launch_tba3l_p<double>(T, g, t, w_in, w_out, mu_in, mu_out, phi, gacc, c, s)
+                     : launch_tba3l_p<float>(T, g, t, w_in, w_out, mu_in, mu_out, phi, gacc, c, s);
     return g.f64 ? launch_tba_p<double>(T, g, t, w_in, w_out, mu_in, mu_out, phi, gacc, c, s)
                  : launch_tba_p<float>(T, g, t, w_in, w_out, mu_in, mu_out, phi, gacc, c, s);
 }

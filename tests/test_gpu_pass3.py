@@ -63,3 +63,55 @@ def test_five_step_passes(shape, f64, beta):
     one.step_n(21)
     many.step_n(21)
     _same(one, many, (shape, "set"))
+
+
+def _gradients(shape, f64, nsteps, K, settings):
+    from tests.gpu_util import torch_mod
+    torch, prs = torch_mod(), gpu_prs()
+    p = prs.make_params(shape, deta=0.1, W0=10.0, precision=prs.PRS_F64 if f64 else prs.PRS_F32)
+    nb = prs.prs_adjoint_workspace_bytes(p, nsteps, K)
+    sim = prs.Sim(p, seed=11)
+    if settings is None:
+        sim.set_time_blocking(1)
+        prs.prs_set_adjoint_time_blocking(sim.ctx, 1)
+    elif settings:
+        vec, rows, ty, T = settings
+        prs.prs_set_adjoint_tiling(sim.ctx, vec, rows, ty)
+        prs.prs_set_adjoint_time_blocking(sim.ctx, T)
+    work = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    g, gd = torch.empty_like(sim.phi_a), torch.empty_like(sim.phi_a)
+    loss = prs.prs_adjoint_forward(sim.ctx, nsteps, K, work.data_ptr(), nb)
+    gw = prs.prs_adjoint_backward(sim.ctx, work.data_ptr(), nb, g.data_ptr(), gd.data_ptr())
+    return loss, gw, host(g).copy(), host(gd).copy()
+
+
+def _same_gradients(got, want, terms):
+    assert got[0] == want[0]
+    np.testing.assert_array_equal(got[2], want[2])
+    np.testing.assert_array_equal(got[3], want[3])
+    # the same FP64 terms of either sign, summed in another order
+    assert abs(got[1] - want[1]) <= 1e-12 * max(abs(want[1]), 1e-3 * np.sqrt(terms))
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("shape", [(64, 9, 8), (128, 37, 21), (37, 30, 50), (202, 20, 33), (1, 2, 3)])
+def test_reverse_lds_passes(shape, f64):
+    say("reverse", shape, f64)
+    nsteps, K = 22, 9
+    want = _gradients(shape, f64, nsteps, K, None)
+    for ty in (8, 16):
+        for vec in (1, 2):
+            if shape[0] % vec:
+                continue
+            for T, rows in ((2, 8), (3, 16), (4, 8)):
+                got = _gradients(shape, f64, nsteps, K, (vec, rows, ty, T))
+                _same_gradients(got, want, nsteps * want[2].size)
+
+
+# w, mu and their outputs beyond 150 MB: the stored fields go past the cache
+@pytest.mark.parametrize("shape,f64", [((250, 190, 201), False), ((128, 1000, 75), False), ((131, 190, 200), True)])
+def test_streamed_adjoint_fields(shape, f64):
+    say("streamed", shape, f64)
+    nsteps, K = 13, 7
+    want = _gradients(shape, f64, nsteps, K, None)
+    _same_gradients(_gradients(shape, f64, nsteps, K, ()), want, nsteps * want[2].size)
