@@ -83,13 +83,20 @@ hipError_t launch_tb(int T, const Geometry& g, const Tiling& t, const void* phi_
 int64_t tb_tiles(const Geometry& g, const Tiling& t, int T);
 // Multi-step passes exist for 2D lattices whose rows are shorter than 2^28
 // sites and for 3D lattices whose planes are shorter than 2^31 bytes (their
-// accesses use 32-bit byte offsets within a row or a plane).
+// accesses use 32-bit byte offsets within a row or a plane), of at most
+// kMaxMarch rows (2D) or planes (3D): those are 32-bit numbers in the passes,
+// which also form the number of a tile's last one plus its halo.
+constexpr int64_t kMaxMarch = ((int64_t)1 << 31) - ((int64_t)1 << 14);
 bool tb_supported(const Geometry& g);
+// Most wave tiles of a launch: a launch holds fewer than 2^32 work-items (one
+// of more runs the remainder only and reports nothing), and a workgroup up to
+// three waves without a tile.
+constexpr int64_t kMaxWaveTiles = ((int64_t)1 << 32) / 64 - 4;
 // Steps per multi-step pass with a kernel for some tiling: 2D 2, 3, 4, 6, 8;
 // 3D 2 and, in float32, 3.
 bool tb_steps_supported(const Geometry& g, int T);
 // ... and for this tiling (2D float64: 6 and 8 with vec 1 only; 3D: vec 1
-// or 2, and only some row counts).
+// or 2, and only some row counts; at most kMaxWaveTiles tiles).
 bool tb_pass_supported(const Geometry& g, const Tiling& t, int T);
 constexpr int kMaxPassSteps = 8;   // most leapfrog steps fused into one pass
 

@@ -172,7 +172,7 @@ hipError_t launch_step(const Geometry& g, const Tiling& t, const void* phi_in, v
                        void* pi_out, const StepCoef64& k, bool update, bool diag, WavePartial* partials,
                        const DiagCoef& dc, hipStream_t s)
 {
-    if (!tiling_supported(g, t)) return hipErrorInvalidValue;
+    if (!tiling_supported(g, t) || tile_counts(g, t).ntiles > kMaxWaveTiles) return hipErrorInvalidValue;
     return g.f64 ? launch_step_f64(g, t, phi_in, phi_out, pi, pi_out, k, update, diag, partials, dc, s)
                  : launch_step_f32(g, t, phi_in, phi_out, pi, pi_out, k, update, diag, partials, dc, s);
 }
@@ -201,7 +201,8 @@ hipError_t launch_tb(int T, const Geometry& g, const Tiling& t, const void* phi_
 hipError_t launch_tb3_deep(const Geometry& g, const Tiling& t, const void* phi_in, void* phi_out, const void* pi_in,
                            void* pi_out, const StepCoef64* k, hipStream_t s)
 {
-    if (g.ndim != 3 || !tb_pass_supported(g, t, 4)) return hipErrorInvalidValue;
+    if (g.ndim != 3 || !tb_pass_supported(g, t, 4) || tb_tiles(g, t, kDeepSteps) > kMaxWaveTiles)
+        return hipErrorInvalidValue;
     return g.f64 ? launch_tb3_deep_p<double>(g, t, phi_in, phi_out, pi_in, pi_out, k, s)
                  : launch_tb3_deep_p<float>(g, t, phi_in, phi_out, pi_in, pi_out, k, s);
 }
@@ -213,16 +214,18 @@ BlkGrid blk_grid(const Geometry& g, int vec, int rows, int waves, int steps)
     if (steps < 1 || steps > kBlkSteps || w <= 0 || h <= 0 || g.nx % vec != 0) return b;
     b.tiles_x = (g.nx + w - 1) / w;
     const int64_t n = b.tiles_x * ((g.M + h - 1) / h);
-    b.blocks = n <= 0x7FFFFFFF ? n : 0;
+    b.blocks = n * waves <= kMaxWaveTiles ? n : 0;
     return b;
 }
 
 // Rows and columns are 32-bit in the kernel, a row's bytes a buffer size.
-bool blk_supported(const Geometry& g)
+static bool blk_range(const Geometry& g)
 {
-    return g.ndim == 2 && g.nx <= ((int64_t)1 << 28) && g.M <= ((int64_t)1 << 30) &&
-           blk_grid(g, 1, 2, 8, 4).blocks > 0;
+    return g.ndim == 2 && g.nx <= ((int64_t)1 << 28) && g.M <= ((int64_t)1 << 30);
 }
+
+// A single step has the fewest blocks.
+bool blk_supported(const Geometry& g) { return blk_range(g) && blk_choose(g, 1).vec != 0; }
 
 // Time of a block pass on 256 compute units, from launches timed at 128^2 to
 // 8192^2 with 4 to 16 steps (the constants are fitted to them; the shape
@@ -270,6 +273,16 @@ BlkShape blk_choose(const Geometry& g, int steps)
     return best;
 }
 
+// Rows doubled until a launch holds the wave tiles of single steps and, for
+// T > 1, of T-step passes.
+static Tiling fit_launch(const Geometry& g, Tiling t, int T)
+{
+    while (t.rows < 2048 &&
+           (tile_counts(g, t).ntiles > kMaxWaveTiles || (T > 1 && tb_tiles(g, t, T) > kMaxWaveTiles)))
+        t.rows *= 2;
+    return t;
+}
+
 // 2D marching passes need about three wave tiles per SIMD (1024 SIMDs) to
 // hide a wave's chain of levels: the shortest tiles with one site per lane
 // while that makes no more, else two sites per lane and the height that
@@ -279,10 +292,10 @@ Tiling auto_tile2(const Geometry& g, int T)
 {
     constexpr int64_t kTiles = 3072;
     Tiling t{1, (int)kMinRows, 1};
-    if (g.nx % 2 != 0 || tb_tiles(g, t, T) <= kTiles) return t;
+    if (g.nx % 2 != 0 || tb_tiles(g, t, T) <= kTiles) return fit_launch(g, t, T);
     if (!g.f64 || T <= 4) t.vec = 2;
     while (t.rows < 64 && tb_tiles(g, t, T) > kTiles) ++t.rows;
-    return t;
+    return fit_launch(g, t, T);
 }
 
 // 16 bytes a lane where the row allows them, and in 3D short tiles on
@@ -297,6 +310,7 @@ PassChoice auto_step(const Geometry& g)
     if (g.nx % 4 == 0 && !g.f64) c.til.vec = 4;
     else if (g.nx % 2 == 0) c.til.vec = 2;
     if (g.ndim == 2 && sites < 8e6) c.til = auto_tile2(g, 2);
+    c.til = fit_launch(g, c.til, 1);
     c.us = (float)(4.5 + bytes / (bytes < 300e6 ? 7.0e6 : 4.9e6));
     return c;
 }
@@ -399,11 +413,12 @@ PassChoice auto_pass3(const Geometry& g, int T)
         if (h.T != T || !tb_pass_supported(g, Tiling{h.vec, 32, h.ty}, std::min(T, 4))) continue;
         const Pass3Time p(g, h);
         if (p.cached ? T > 4 : !g.f64 && h.vec == 1 && g.nx % 2 == 0) continue;
-        const int64_t rows = p.best_rows(4);
-        const double t = p.us(rows);
+        const Tiling til{h.vec, (int)p.best_rows(4), h.ty};
+        if (tb_tiles(g, til, T) > kMaxWaveTiles) continue;
+        const double t = p.us(til.rows);
         if (best.til.vec == 0 || t < best.us) {
             best.us = (float)t;
-            best.til = Tiling{h.vec, (int)rows, h.ty};
+            best.til = til;
         }
     }
     return best;
@@ -442,14 +457,15 @@ Tiling auto_adj_tile(const Geometry& g, int* T)
         const int n = g.f64 ? (int)(sizeof f64s / sizeof f64s[0]) : (int)(sizeof f32 / sizeof f32[0]);
         for (int i = 0; i < n; ++i) {
             const Pass3Shape& h = list[i];
-            if (!tba_supported(g, Tiling{h.vec, (int)kMinRows, h.ty}, h.T)) continue;
+            if (!tiling_supported(g, Tiling{h.vec, (int)kMinRows, h.ty})) continue;
             const Pass3Time p(g, h, true);
-            const int64_t rows = p.best_rows(kMinRows);
-            const double us = p.us(rows) / h.T;
+            const Tiling til{h.vec, (int)p.best_rows(kMinRows), h.ty};
+            if (!tba_supported(g, til, h.T)) continue;
+            const double us = p.us(til.rows) / h.T;
             if (least == 0.0 || us < least) {
                 least = us;
                 *T = h.T;
-                best = Tiling{h.vec, (int)rows, h.ty};
+                best = til;
             }
         }
         return best;
@@ -472,7 +488,7 @@ Tiling auto_adj_tile(const Geometry& g, int* T)
 hipError_t launch_blk2d(int steps, const BlkShape& b, const Geometry& g, const void* phi_in, void* phi_out,
                         const void* pi_in, void* pi_out, const StepCoef64* k, hipStream_t s)
 {
-    if (!blk_supported(g)) return hipErrorInvalidValue;
+    if (!blk_range(g)) return hipErrorInvalidValue;
     return g.f64 ? launch_blk2d_p<double>(steps, b, g, phi_in, phi_out, pi_in, pi_out, k, s)
                  : launch_blk2d_p<float>(steps, b, g, phi_in, phi_out, pi_in, pi_out, k, s);
 }
@@ -488,7 +504,7 @@ hipError_t launch_tb_slab(int T, const Geometry& g, const Tiling& t, const void*
 hipError_t launch_adjoint(const Geometry& g, const Tiling& t, const void* w_in, void* w_out, void* mu,
                           const void* phi_n, double* gacc, const AdjCoef64& c, hipStream_t s)
 {
-    if (!tiling_supported(g, t)) return hipErrorInvalidValue;
+    if (!tiling_supported(g, t) || tile_counts(g, t).ntiles > kMaxWaveTiles) return hipErrorInvalidValue;
     return g.f64 ? launch_adjoint_p<double>(g, t, w_in, w_out, mu, phi_n, gacc, c, s)
                  : launch_adjoint_p<float>(g, t, w_in, w_out, mu, phi_n, gacc, c, s);
 }
@@ -503,22 +519,23 @@ hipError_t launch_adj_seed(const Geometry& g, const void* phi, int64_t count, do
 bool tba_supported(const Geometry& g, const Tiling& t, int T)
 {
     if (!tb_supported(g) || !tiling_supported(g, t)) return false;
+    bool has;     // there is a kernel
     if (g.ndim == 3 && tb3l_tiling(t.ty)) {
         const int rw = tb3l_rows_per_wave(t.ty), nw = tb3l_waves(t.ty);
-        return g.f64 ? tba3l_combo_ok<double>(t.vec, T, rw, nw) : tba3l_combo_ok<float>(t.vec, T, rw, nw);
-    }
-    if (g.ndim == 3) {
+        has = g.f64 ? tba3l_combo_ok<double>(t.vec, T, rw, nw) : tba3l_combo_ok<float>(t.vec, T, rw, nw);
+    } else if (g.ndim == 3) {
         const int TY = tb3_rows(t.ty);
-        return g.f64 ? tba3_combo_ok<double>(t.vec, T, TY) : tba3_combo_ok<float>(t.vec, T, TY);
+        has = g.f64 ? tba3_combo_ok<double>(t.vec, T, TY) : tba3_combo_ok<float>(t.vec, T, TY);
+    } else {
+        has = t.ty == 1 && (g.f64 ? tba_combo_ok<double>(t.vec, T) : tba_combo_ok<float>(t.vec, T));
     }
-    if (t.ty != 1) return false;
-    return g.f64 ? tba_combo_ok<double>(t.vec, T) : tba_combo_ok<float>(t.vec, T);
+    return has && tb_tiles(g, t, T) <= kMaxWaveTiles;
 }
 
 bool tb_all_supported(const Geometry& g, const Tiling& t, int T)
 {
     if (g.ndim == 3) return tb_pass_supported(g, t, T);
-    if (!tb_supported(g) || !tiling_supported(g, t) || t.ty != 1) return false;
+    if (!tb_supported(g) || !tiling_supported(g, t) || t.ty != 1 || tb_tiles(g, t, T) > kMaxWaveTiles) return false;
     return g.f64 ? tball_combo_ok<double>(t.vec, T) : tball_combo_ok<float>(t.vec, T);
 }
 
@@ -543,7 +560,8 @@ hipError_t launch_tba(int T, const Geometry& g, const Tiling& t, const void* w_i
 
 bool tb_mid_supported(const Geometry& g, const Tiling& t, int T)
 {
-    if (g.ndim != 2 || !tb_supported(g) || !tiling_supported(g, t) || t.ty != 1) return false;
+    if (g.ndim != 2 || !tb_supported(g) || !tiling_supported(g, t) || t.ty != 1 || tb_tiles(g, t, T) > kMaxWaveTiles)
+        return false;
     return g.f64 ? tbmid_combo_ok<double>(t.vec, T) : tbmid_combo_ok<float>(t.vec, T);
 }
 
@@ -558,7 +576,8 @@ hipError_t launch_tb_mid(int T, const Geometry& g, const Tiling& t, const void* 
 
 bool tbf_supported(const Geometry& g, const Tiling& t, int T)
 {
-    if (g.ndim != 2 || !tb_supported(g) || !tiling_supported(g, t) || t.ty != 1) return false;
+    if (g.ndim != 2 || !tb_supported(g) || !tiling_supported(g, t) || t.ty != 1 || tbf_tiles(g, t, T) > kMaxWaveTiles)
+        return false;
     return g.f64 ? tbf_combo_ok<double>(t.vec, T) : tbf_combo_ok<float>(t.vec, T);
 }
 
@@ -678,6 +697,7 @@ int64_t tb_owned_width(int vec, int T)
 
 bool tb_supported(const Geometry& g)
 {
+    if (g.M > kMaxMarch) return false;
     if (g.ndim == 2) return g.nx <= ((int64_t)1 << 28);
     return g.nx * g.Q * (g.f64 ? 8 : 4) < ((int64_t)1 << 31);
 }
@@ -691,7 +711,7 @@ bool tb_steps_supported(const Geometry& g, int T)
 
 bool tb_pass_supported(const Geometry& g, const Tiling& t, int T)
 {
-    if (!tb_steps_supported(g, T) || !tiling_supported(g, t)) return false;
+    if (!tb_steps_supported(g, T) || !tiling_supported(g, t) || tb_tiles(g, t, T) > kMaxWaveTiles) return false;
     if (g.ndim == 2) return t.ty == 1 && (g.f64 ? tb2_combo_ok<double>(t.vec, T) : tb2_combo_ok<float>(t.vec, T));
     if (tb3l_tiling(t.ty)) {
         const int rw = tb3l_rows_per_wave(t.ty), nw = tb3l_waves(t.ty);
