@@ -285,16 +285,20 @@ static Tiling fit_launch(const Geometry& g, Tiling t, int T)
 
 // 2D marching passes need about three wave tiles per SIMD (1024 SIMDs) to
 // hide a wave's chain of levels: the shortest tiles with one site per lane
-// while that makes no more, else two sites per lane and the height that
-// does.  Eight steps at 256^2: 9.1 us with one site and 8 rows, 14.4 us with
-// four and 8; at 2048^2 21 us with two sites and 13 rows, 24 with 16.
+// while that makes no more, else two sites per lane, where the width is even,
+// and the height that does.  Eight steps at 256^2: 9.1 us with one site and 8
+// rows, 14.4 us with four and 8; at 2048^2 21 us with two sites and 13 rows,
+// 24 with 16.  One site per lane stays at 32 rows or fewer: 40 steps of
+// 4095^2 with a record every four take 1494 us with 8 rows, 1332 with 16,
+// 1334 with 32 and 1403 with 64 (float64 2874, 2585, 2556 and 2625).
 Tiling auto_tile2(const Geometry& g, int T)
 {
     constexpr int64_t kTiles = 3072;
     Tiling t{1, (int)kMinRows, 1};
-    if (g.nx % 2 != 0 || tb_tiles(g, t, T) <= kTiles) return fit_launch(g, t, T);
-    if (!g.f64 || T <= 4) t.vec = 2;
-    while (t.rows < 64 && tb_tiles(g, t, T) > kTiles) ++t.rows;
+    if (tb_tiles(g, t, T) <= kTiles) return t;
+    if (g.nx % 2 == 0 && (!g.f64 || T <= 4)) t.vec = 2;
+    const int most = t.vec == 1 ? 32 : 64;
+    while (t.rows < most && tb_tiles(g, t, T) > kTiles) ++t.rows;
     return fit_launch(g, t, T);
 }
 

@@ -74,6 +74,20 @@ def test_block_passes_fit_a_launch(shape, f64):
 
 
 @pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("shape", [(2047, 2047), (2048, 2048), (1023, 4095), (8191, 8191), (1, 10 ** 6), (255, 255),
+                                   (301, 640)])
+def test_default_2d_tiles_grow_with_the_lattice(shape, f64):
+    """Three tiles per SIMD are enough (1024 SIMDs); beyond, a tile grows to 32
+    rows (64 with two sites a lane): at 8 rows an eight-step pass marches 22
+    rows for the 8 it stores."""
+    g = geometry(shape, f64)
+    for T in (2, 8):
+        t = auto_tile2(g, T)
+        assert shape[0] % t.vec == 0
+        assert t.rows == (32 if t.vec == 1 else 64) or tb_tiles(g, t, T) <= 3072, (T, t.vec, t.rows)
+
+
+@pytest.mark.parametrize("f64", [False, True])
 @pytest.mark.parametrize("shape", [(1, 1, 6 * 10 ** 8), (1, 1, 2 ** 31 - 2 ** 14), (2, 2, 10 ** 9), (5, 3, 6 * 10 ** 8),
                                    (1, 1, 1), (64, 64, 64), (1024, 1024, 1024)])
 def test_3d_passes_fit_a_launch(shape, f64):
