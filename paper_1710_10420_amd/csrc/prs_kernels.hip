@@ -307,6 +307,9 @@ Tiling auto_tile2(const Geometry& g, int T)
 // 200 x 120 x 90 11 us against 34 with 32 planes).  Two rows a wave only where
 // the fields outgrow the last-level cache: 512^3 431 us against 461 and
 // 1024^3 3.59 ms against 3.65, but 384^3 238 us against 212 with one row.
+// The estimate of a small 2D lattice counts the march of its tiles (512^2,
+// 8 and 32 rows: 5.4 and 12.9 us) and the wave rows, most of whose lanes idle
+// on a narrow lattice (1 x 100000, 32 rows: 21.5 us).
 PassChoice auto_step(const Geometry& g)
 {
     const double sites = (double)g.nx * (double)g.Q * (double)g.M, bytes = 4 * sites * (g.f64 ? 8 : 4);
@@ -315,7 +318,13 @@ PassChoice auto_step(const Geometry& g)
     else if (g.nx % 2 == 0) c.til.vec = 2;
     if (g.ndim == 2 && sites < 8e6) c.til = auto_tile2(g, 2);
     c.til = fit_launch(g, c.til, 1);
-    c.us = (float)(4.5 + bytes / (bytes < 300e6 ? 7.0e6 : 4.9e6));
+    const double mem = bytes / (bytes < 300e6 ? 7.0e6 : 4.9e6);
+    if (g.ndim == 2 && sites < 8e6) {
+        const double wave_rows = (double)tile_counts(g, c.til).tiles_x * (double)g.M;
+        c.us = (float)(2.8 + 0.32 * c.til.rows + std::max(mem, 1.1e-4 * wave_rows));
+    } else {
+        c.us = (float)(4.5 + mem);
+    }
     return c;
 }
 

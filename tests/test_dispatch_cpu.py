@@ -87,6 +87,17 @@ def test_default_2d_tiles_grow_with_the_lattice(shape, f64):
         assert t.rows == (32 if t.vec == 1 else 64) or tb_tiles(g, t, T) <= 3072, (T, t.vec, t.rows)
 
 
+@pytest.mark.parametrize("shape,us", [((512, 512), 5.4), ((2048, 2048), 14.0), ((1, 100000), 21.5), ((30, 100000), 25.3),
+                                      ((61, 60000), 20.6)])
+def test_single_step_estimate_counts_narrow_rows(shape, us):
+    """Timed single steps (default tiles, float32), within a third; and two of
+    them do not stand before a block pass of two steps on a narrow lattice,
+    where a block pass takes about 15 us."""
+    g = geometry(shape)
+    assert us / 1.33 < auto_step(g).us < us * 1.33
+    assert blk_choose(g, 2).us < 2 * auto_step(g).us
+
+
 @pytest.mark.parametrize("f64", [False, True])
 @pytest.mark.parametrize("shape", [(1, 1, 6 * 10 ** 8), (1, 1, 2 ** 31 - 2 ** 14), (2, 2, 10 ** 9), (5, 3, 6 * 10 ** 8),
                                    (1, 1, 1), (64, 64, 64), (1024, 1024, 1024)])
