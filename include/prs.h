@@ -493,7 +493,10 @@ prs_status prs_batch_set_tiling(prs_batch* b, int32_t item, int32_t vec, int32_t
  * second phi_dot field multi-step passes need lives in the workspace. */
 prs_status prs_batch_set_time_blocking(prs_batch* b, int32_t item, int32_t steps_per_pass);
 
-/* Current tiling and steps per pass of one item (any pointer may be NULL). */
+/* Tiling and steps per pass of one item in the current mode (any pointer may
+ * be NULL): an item whose tiling was not set has one default tiling in the
+ * stream modes and, on lattices of more than 2^17 sites, a taller one in the
+ * persistent modes. */
 prs_status prs_batch_get_tiling(const prs_batch* b, int32_t item, int32_t* vec, int32_t* rows, int32_t* ty,
                                 int32_t* steps_per_pass);
 

@@ -1562,7 +1562,8 @@ struct prs_batch {
     int32_t count;
     std::vector<prs_batch_item> items;
     std::vector<Geometry> geo;
-    std::vector<Tiling> til;
+    std::vector<Tiling> til;            // set, or the stream modes' default
+    std::vector<uint8_t> til_set;       // tiling was set
     std::vector<int32_t> tblock;        // steps per pass (1: single steps)
     std::vector<uint8_t> own;           // tiling or steps per pass were set
     std::vector<std::unique_ptr<Stretches>> stretches;   // made on first use
@@ -1731,6 +1732,25 @@ bool persistent_mode(int32_t mode)
     return mode == PRS_BATCH_PERSISTENT_GRAPH || mode == PRS_BATCH_PERSISTENT || mode == PRS_BATCH_PER_STEP;
 }
 
+// The tiling of an item in the current mode.  Inside the persistent kernel the
+// other members fill the device, and each item of work costs its ticket and
+// its publication, so only the smallest lattices take the short tiles of a
+// run alone.  Runs of 40 steps, one member (eight), this rule and short tiles
+// everywhere: 1024^2 528 us (854) and 716 (983), 4096^2 2.58 ms (12.0) and
+// 3.50 (14.4), 128^3 1.54 ms (2.83) and 2.15 (3.24); but 64^2 190 us (276)
+// with short tiles and 324 (402) without, 48^3 603 (1084) and 1379 (1677).
+Tiling item_tiling(const prs_batch* b, int32_t r)
+{
+    const Geometry& g = b->geo[r];
+    if (b->til_set[r] || !persistent_mode(b->mode) || g.f64 ||
+        (double)g.nx * (double)g.Q * (double)g.M <= 131072.0)
+        return b->til[r];
+    Tiling t{1, g.ndim == 3 ? 32 : 16, 1};
+    if (g.nx % 4 == 0 && (g.nx < 128 || g.nx >= 256)) t.vec = 4;    // a wave's sites within the row, or full
+    else if (g.nx % 2 == 0) t.vec = 2;
+    return t;
+}
+
 // Most wave tiles any pass of an item can have (single steps and, for T > 1,
 // T-step passes), which its partial buffer must hold.
 int64_t item_tiles_max(const Geometry& g, const Tiling& t, int T)
@@ -1774,7 +1794,8 @@ struct ItemCursor {
 
 const Stretches* batch_stretches(prs_batch* b, int32_t r)
 {
-    if (!b->stretches[r]) b->stretches[r].reset(make_stretches(b->geo[r], b->til[r], b->tblock[r], b->own[r] != 0));
+    if (!b->stretches[r])
+        b->stretches[r].reset(make_stretches(b->geo[r], item_tiling(b, r), b->tblock[r], b->own[r] != 0));
     return b->stretches[r].get();
 }
 
@@ -1782,7 +1803,7 @@ prs_status batch_item_begin(prs_batch* b, int32_t r, ItemCursor& cur, hipStream_
 {
     const prs_batch_item& it = b->items[r];
     cur.item = r;
-    cur.plan = batch_plan(it, b->geo[r], b->til[r], b->part_cap[r], b->tblock[r], batch_stretches(b, r));
+    cur.plan = batch_plan(it, b->geo[r], item_tiling(b, r), b->part_cap[r], b->tblock[r], batch_stretches(b, r));
     b->nlaunches[r] = (int64_t)cur.plan.size();
     cur.next = 0;
     cur.queue = RecordQueue{reinterpret_cast<WavePartial*>(static_cast<char*>(b->ws) + b->off_part + b->part_off[r]),
@@ -1804,7 +1825,7 @@ prs_status batch_item_pass(prs_batch* b, ItemCursor& cur, hipStream_t s)
     const int32_t r = cur.item;
     const prs_batch_item& it = b->items[r];
     const Geometry& g = b->geo[r];
-    const Tiling& t = b->til[r];
+    const Tiling t = item_tiling(b, r);
     const size_t idx = cur.next++;
     const PassEntry& e = cur.plan[idx];
     char* base = static_cast<char*>(b->ws);
@@ -1920,7 +1941,7 @@ prs_status batch_upload(prs_batch* b, int32_t nseq)
     for (int32_t r = 0; r < b->count; ++r) {
         const prs_batch_item& it = b->items[r];
         const Geometry& g = b->geo[r];
-        const Tiling& t = b->til[r];
+        const Tiling t = item_tiling(b, r);
         prs_ctx tmp{};
         tmp.p = it.p;
         tmp.V0 = v0_of(it.p);
@@ -2181,6 +2202,7 @@ prs_status prs_batch_create(const prs_batch_item* items, int32_t count, void* wo
     b->total_recs = L.rec_off[count];
     b->npasses.assign(count, 0);
     b->nlaunches.assign(count, 0);
+    b->til_set.assign(count, 0);
     b->own.assign(count, 0);
     b->stretches.resize(count);
     b->ran = 0;
@@ -2220,6 +2242,7 @@ prs_status prs_batch_set_tiling(prs_batch* b, int32_t item, int32_t vec, int32_t
     if (item_tiles_max(b->geo[item], t, std::max(2, b->tblock[item])) > b->part_cap[item])
         return fail(PRS_EINVAL, "tiling has more wave tiles than the workspace holds");
     b->til[item] = t;
+    b->til_set[item] = 1;
     b->own[item] = 1;
     b->stretches[item].reset();
     batch_release_graph(b);
@@ -2238,7 +2261,7 @@ prs_status prs_batch_set_time_blocking(prs_batch* b, int32_t item, int32_t steps
     if (steps_per_pass > 1 && !tb_steps_supported(b->geo[item], steps_per_pass))
         return fail(PRS_EINVAL, "no %d-step pass kernel for this lattice (2D: 2, 3, 4, 6, 8; "
                     "3D: 2, 3, 4)", steps_per_pass);
-    if (item_tiles_max(b->geo[item], b->til[item], std::max(2, steps_per_pass)) > b->part_cap[item])
+    if (item_tiles_max(b->geo[item], item_tiling(b, item), std::max(2, steps_per_pass)) > b->part_cap[item])
         return fail(PRS_EINVAL, "steps per pass need more wave tiles than the workspace holds");
     b->tblock[item] = steps_per_pass;
     b->own[item] = 1;
@@ -2252,9 +2275,10 @@ prs_status prs_batch_get_tiling(const prs_batch* b, int32_t item, int32_t* vec, 
                                 int32_t* steps_per_pass)
 {
     if (!b || item < 0 || item >= b->count) return fail(PRS_EINVAL, "invalid batch or item");
-    if (vec) *vec = b->til[item].vec;
-    if (rows) *rows = b->til[item].rows;
-    if (ty) *ty = b->til[item].ty;
+    const Tiling t = item_tiling(b, item);
+    if (vec) *vec = t.vec;
+    if (rows) *rows = t.rows;
+    if (ty) *ty = t.ty;
     if (steps_per_pass) *steps_per_pass = b->tblock[item];
     return PRS_OK;
 }
@@ -2283,10 +2307,10 @@ prs_status prs_batch_state(const prs_batch* b, int32_t item, void** phi, void** 
     // changed since
     int64_t np = b->ran == 1 ? b->npasses[item] : b->ran == 2 ? b->nlaunches[item] : 0;
     if (np == 0) {
-        const bool streams = !persistent_mode(b->mode);
+        const Tiling t = item_tiling(b, item);
         std::unique_ptr<Stretches> st;
-        if (streams) st.reset(make_stretches(b->geo[item], b->til[item], b->tblock[item], b->own[item] != 0));
-        np = (int64_t)batch_plan(it, b->geo[item], b->til[item], b->part_cap[item], b->tblock[item], st.get()).size();
+        if (!persistent_mode(b->mode)) st.reset(make_stretches(b->geo[item], t, b->tblock[item], b->own[item] != 0));
+        np = (int64_t)batch_plan(it, b->geo[item], t, b->part_cap[item], b->tblock[item], st.get()).size();
     }
     if (phi) *phi = ((np - 1) & 1) ? it.phi_b : it.phi_a;
     if (dphi) *dphi = it.dphi;
@@ -2308,7 +2332,7 @@ prs_status prs_batch_run(prs_batch* b, prs_stats* series, int64_t cap)
     }
     if (persistent) {
         for (int32_t r = 0; r < b->count; ++r)
-            if (b->items[r].p.precision != PRS_F32 || !ens_supported(b->geo[r], b->til[r], b->tblock[r]))
+            if (b->items[r].p.precision != PRS_F32 || !ens_supported(b->geo[r], item_tiling(b, r), b->tblock[r]))
                 return fail(PRS_EINVAL,
                             "item %d: the persistent modes run float32 items with, in 2D, ty 1 and vec 1 or 2 "
                             "(up to 8 steps per pass) or vec 4 (up to 4); in 3D, single steps with ty 1, or vec 1 "
@@ -2398,16 +2422,16 @@ prs_status prs_batch_autotune(prs_batch* b, double* best_ms)
     std::vector<Group> groups;
     for (int32_t r = 0; r < b->count; ++r) {
         const Geometry& g = b->geo[r];
-        const Tiling& t = b->til[r];
+        const Tiling t = item_tiling(b, r);
         double work = (double)g.nx * (double)g.Q * (double)g.M * (double)b->items[r].nsteps;
         bool placed = false;
         for (Group& G : groups) {
             const int32_t q = G.items[0];
             const Geometry& h = b->geo[q];
-            const Tiling& u = b->til[q];
+            const Tiling u = item_tiling(b, q);
             if (h.ndim == g.ndim && h.f64 == g.f64 && h.nx == g.nx && h.Q == g.Q && h.M == g.M && u.vec == t.vec &&
                 u.rows == t.rows && u.ty == t.ty && b->tblock[q] == b->tblock[r] &&
-                b->own[q] == b->own[r]) {
+                b->own[q] == b->own[r] && b->til_set[q] == b->til_set[r]) {
                 G.items.push_back(r);
                 G.work += work;
                 placed = true;
@@ -2430,20 +2454,26 @@ prs_status prs_batch_autotune(prs_batch* b, double* best_ms)
             if (persistent && !ens_supported(g, t, T)) return false;
             return item_tiles_max(g, t, std::max(2, T)) <= b->part_cap[q];
         };
-        auto apply = [&](const Tiling& t, int T, uint8_t own) {
+        struct Setting {
+            Tiling til;
+            int T;
+            uint8_t til_set, own;
+        };
+        auto apply = [&](const Setting& s) {
             for (int32_t r : G.items) {
-                b->til[r] = t;
-                b->tblock[r] = T;
-                b->own[r] = own;
+                b->til[r] = s.til;
+                b->til_set[r] = s.til_set;
+                b->tblock[r] = s.T;
+                b->own[r] = s.own;
                 b->stretches[r].reset();
             }
             batch_release_graph(b);
             b->dirty = true;
         };
         for (;;) {
-            const Tiling cur = b->til[q];
-            const int T = b->tblock[q];
-            const uint8_t own = b->own[q];
+            const Setting start{b->til[q], b->tblock[q], b->til_set[q], b->own[q]};
+            const Tiling cur = item_tiling(b, q);
+            const int T = start.T;
             // candidates: the marching tile doubled (up to the tuner's
             // longest, 128, and not past the lattice); in 3D, when the
             // current tiling is a workgroup-stacked one, the other
@@ -2465,11 +2495,11 @@ prs_status prs_batch_autotune(prs_batch* b, double* best_ms)
             double round_best = 1e300;
             size_t pick = cand.size();
             for (size_t c = 0; c < cand.size(); ++c) {
-                apply(cand[c].first, cand[c].second, 1);
+                apply(Setting{cand[c].first, cand[c].second, 1, 1});
                 double ms = 0.0;
                 st = time_runs(&ms);
                 if (st != PRS_OK) {
-                    apply(cur, T, own);
+                    apply(start);
                     return st;
                 }
                 if (ms < round_best) {
@@ -2479,11 +2509,11 @@ prs_status prs_batch_autotune(prs_batch* b, double* best_ms)
             }
             // a change must gain more than the runs' spread to be kept
             if (pick < cand.size() && round_best < best * 0.98) {
-                apply(cand[pick].first, cand[pick].second, 1);
+                apply(Setting{cand[pick].first, cand[pick].second, 1, 1});
                 best = round_best;
                 continue;
             }
-            apply(cur, T, own);
+            apply(start);
             break;
         }
     }
