@@ -2546,7 +2546,9 @@ void prs_batch_destroy(prs_batch* b)
 
 namespace {
 
-constexpr const char* kTuneVersion = "k4";
+// Part of every key: raised when the kernels, the candidates or what is timed
+// change, so that a file written before is tuned anew.
+constexpr const char* kTuneVersion = "k5";
 
 std::string tune_key(const prs_params& p, bool batch_set)
 {
