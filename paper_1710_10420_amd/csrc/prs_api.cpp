@@ -356,7 +356,7 @@ struct prs_ctx {
     int32_t tblock;    // steps per pass (1: single steps)
     bool own;          // tiling or steps per pass were set (by the caller or the tuner)
     bool adj_own;      // the same of the reverse sweep
-    mutable std::unique_ptr<Stretches> stretches;   // made on first use
+    std::unique_ptr<Stretches> stretches;   // made on first use
     hipStream_t stream;
     int64_t step;
     // adjoint bookkeeping between prs_adjoint_forward and _backward
@@ -505,7 +505,7 @@ int pass_steps(const prs_ctx* c) { return tb_supported(c->geo) ? c->tblock : 1; 
 
 // The launches of the steps between records, or NULL: passes of the run's
 // tiling and length there too.
-const Stretches* run_stretches(const prs_ctx* c)
+const Stretches* run_stretches(prs_ctx* c)
 {
     if (!c->stretches) c->stretches.reset(make_stretches(c->geo, c->til, pass_steps(c), c->own));
     return c->stretches.get();
@@ -766,8 +766,12 @@ prs_status prs_plan_passes(const prs_ctx* c, int64_t nsteps, int32_t with_record
     if (!c || nsteps < 0) return fail(PRS_EINVAL, "invalid arguments");
     const int64_t K = (with_records && c->p.diag_every > 0) ? c->p.diag_every : 0;
     int64_t m = 0, n1 = 0;
+    // a context that has not run keeps none of this: threads may ask for plans
+    // of one context side by side
+    const std::unique_ptr<Stretches> made(c->stretches ? nullptr
+                                                       : make_stretches(c->geo, c->til, pass_steps(c), c->own));
     for (const Launch& l : plan_launches(c->geo, c->til, c->partial_cap, c->step, nsteps, pass_steps(c), K, K > 0,
-                                         run_stretches(c)))
+                                         c->stretches ? c->stretches.get() : made.get()))
         (l.flips() ? m : n1) += 1;
     if (multi_passes) *multi_passes = m;
     if (single_passes) *single_passes = n1;
