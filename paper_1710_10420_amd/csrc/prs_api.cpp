@@ -503,6 +503,25 @@ int64_t partial_entries(int64_t cap)
 
 int pass_steps(const prs_ctx* c) { return tb_supported(c->geo) ? c->tblock : 1; }
 
+struct PassSetting {
+    Tiling til;
+    int T;
+};
+
+// The tiling and steps per pass of the adjoint's recomputation: its own, else
+// the forward's, which while neither is set are chosen by the lattice's size.
+PassSetting recompute_setting(const prs_ctx* c)
+{
+    if (c->rec_tblock > 0) return PassSetting{c->rec_til, c->rec_tblock};
+    if (!c->own && tb_supported(c->geo)) {
+        if (c->geo.ndim == 2) return PassSetting{auto_tile2(c->geo, kMaxPassSteps), kMaxPassSteps};
+        const PassChoice pc = auto_pass3(c->geo, 4);
+        if (pc.til.vec)
+            return PassSetting{Tiling{pc.til.vec, std::max(pc.til.rows, (int)kMinRows), pc.til.ty}, 4};
+    }
+    return PassSetting{c->til, c->tblock};
+}
+
 // The launches of the steps between records, or NULL: passes of the run's
 // tiling and length there too.
 const Stretches* run_stretches(prs_ctx* c)
@@ -990,11 +1009,11 @@ prs_status prs_set_recompute_tiling(prs_ctx* c, int32_t vec, int32_t rows, int32
 prs_status prs_get_recompute_tiling(prs_ctx* c, int32_t* vec, int32_t* rows, int32_t* ty, int32_t* steps_per_pass)
 {
     if (!c || !vec || !rows || !ty || !steps_per_pass) return fail(PRS_EINVAL, "NULL argument");
-    const Tiling& t = c->rec_tblock > 0 ? c->rec_til : c->til;
-    *vec = t.vec;
-    *rows = t.rows;
-    *ty = t.ty;
-    *steps_per_pass = c->rec_tblock > 0 ? c->rec_tblock : c->tblock;
+    const PassSetting rec = recompute_setting(c);
+    *vec = rec.til.vec;
+    *rows = rec.til.rows;
+    *ty = rec.til.ty;
+    *steps_per_pass = rec.T;
     return PRS_OK;
 }
 
@@ -1331,26 +1350,13 @@ prs_status prs_adjoint_backward(prs_ctx* c, void* work, size_t work_bytes, void*
     const AdjLayout L = adj_layout(c->p, c->adj_nsteps, c->adj_K, c->partial_cap);
     const int64_t n0 = c->adj_n0;
     const size_t bytes = field_bytes(c->p);
-    // the recomputation: its own tuned tiling and pass length, else the forward's
-    Tiling rt = c->rec_tblock > 0 ? c->rec_til : c->til;
-    int T = tb_supported(c->geo) ? (c->rec_tblock > 0 ? c->rec_tblock : c->tblock) : 1;
+    const PassSetting rec = recompute_setting(c);
+    const Tiling rt = rec.til;
+    const int T = tb_supported(c->geo) ? rec.T : 1;
     Tiling at_til = c->adj_til;
     int TA = tb_supported(c->geo) ? c->adj_tblock : 1;
     // what neither the caller nor the tuner set is chosen by the lattice's size
     if (tb_supported(c->geo) && !c->adj_own) at_til = auto_adj_tile(c->geo, &TA);
-    if (tb_supported(c->geo) && !c->own && c->rec_tblock == 0) {
-        if (c->geo.ndim == 2) {
-            T = kMaxPassSteps;
-            rt = auto_tile2(c->geo, T);
-        } else {
-            const PassChoice pc = auto_pass3(c->geo, 4);
-            if (pc.til.vec) {
-                T = 4;
-                rt = pc.til;
-                rt.rows = std::max<int>(rt.rows, (int)kMinRows);
-            }
-        }
-    }
     // The fused scheme (2D): per segment the recomputation keeps only the
     // states at the starts of the reverse passes (TF steps apart, the last
     // pass may be shorter), and each reverse pass recomputes its fields from
@@ -2688,7 +2694,7 @@ namespace {
 
 // Tunes the reverse-sweep kernel's tiling and steps per pass on scratch
 // buffers (w, mu filled from the current phi; phi^n = the current phi).  The
-// recomputation keeps following the forward's setting: timing its passes on
+// recomputation keeps its setting (recompute_setting): timing its passes on
 // scratch fields that stay cache-resident misjudges them (single steps win
 // there and lose by 15 % inside the backward), and the forward's setting
 // was within 2 % of the best one measured inside the backward at 2048^2 and
@@ -2771,7 +2777,7 @@ prs_status autotune_adjoint(prs_ctx* c, const char* cache_path, int32_t flags, v
     // kernel, each timed together with the forward pass that recomputes its
     // pass-start state (the recomputation's tiling) -- what one reverse pass
     // costs inside the backward.
-    const Tiling rt = c->rec_tblock > 0 ? c->rec_til : c->til;
+    const Tiling rt = recompute_setting(c).til;
     const bool fused = c->adj_scheme == PRS_ADJ_FUSED && c->geo.ndim == 2 && tb_supported(c->geo) && nphi >= 6;
     // Besides the power-of-two row tiles, the heights that give the reverse
     // pass a whole number of workgroup rounds (at 2048^2 it has two or three
