@@ -176,15 +176,21 @@ prs_status prs_get_tiling(prs_ctx* ctx, int32_t* vec, int32_t* rows, int32_t* ty
  * by timing on the card in use).  Times every supported tiling and steps per
  * pass for this lattice on the context's own state (saved into the caller's
  * workspace before and restored after each candidate) -- rows 8 to 128 in
- * powers of two and, for 2D multi-step passes (and the 2D reverse pass),
- * the row heights that make a pass's workgroup count a whole number of
- * rounds over the device's compute units where that count is small (up to
- * four workgroups per unit; eight for the reverse pass) -- applies the fastest
+ * powers of two and, for multi-step passes (and the 2D reverse pass), the
+ * row heights that make a pass's workgroup count a whole number of rounds
+ * over the device's compute units where that count is small (up to four
+ * workgroups per unit; eight for the reverse pass) -- applies the fastest
  * to the context and records it in the JSON file cache_path (created or
- * updated; NULL or "" for no cache).  A cached entry for the same GPU
- * architecture, dimension, lattice size and tiling set is applied without
- * timing (and without touching the workspace, which may then be NULL) unless
- * flags has PRS_TUNE_FORCE.  PRS_TUNE_BATCH restricts the candidates
+ * updated; NULL or "" for no cache).  A 2D context with diag_every > 0 is
+ * tuned for runs with records, on intervals between two of them (its tiling
+ * and steps per pass are those of the passes that start at a record; the
+ * recomputation of a gradient keeps the library's choice); any other by
+ * passes without records, as the recomputation and slabs run them.  The file
+ * holds either choice of a lattice.  A cached entry for the same GPU
+ * architecture, dimension, lattice size and tiling set -- of two the
+ * context's kind, else the one there is -- is applied without timing (and
+ * without touching the workspace, which may then be NULL) unless flags has
+ * PRS_TUNE_FORCE.  PRS_TUNE_BATCH restricts the candidates
  * (tilings and steps per pass) to those the persistent batch modes run
  * (prs_batch_run); the STREAMS batch modes take the ordinary choice.
  * PRS_TUNE_ADJOINT tunes the reverse sweep's tiling and steps per pass
@@ -229,7 +235,8 @@ prs_status prs_get_launch_timing(prs_ctx* ctx, double* total_ms, int64_t* launch
  * argument, PRS_EDEVICE on a launch failure. */
 prs_status prs_copy(void* dst, const void* src, size_t bytes, void* hip_stream);
 
-/* Cached tiling for these parameters (no GPU work); PRS_ESTATE if absent. */
+/* Cached tiling for these parameters (no GPU work), of two the one for runs
+ * with records if diag_every > 0; PRS_ESTATE if absent. */
 prs_status prs_tuned_tiling(const prs_params* p, const char* cache_path, int32_t flags, int32_t* vec,
                             int32_t* rows, int32_t* ty);
 

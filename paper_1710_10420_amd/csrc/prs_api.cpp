@@ -355,6 +355,7 @@ struct prs_ctx {
     int32_t rec_tblock;   // (0: those of the forward)
     int32_t tblock;    // steps per pass (1: single steps)
     bool own;          // tiling or steps per pass were set (by the caller or the tuner)
+    bool for_records;  // ... by the tuner, for the record passes of a 2D run
     bool adj_own;      // the same of the reverse sweep
     std::unique_ptr<Stretches> stretches;   // made on first use
     hipStream_t stream;
@@ -509,11 +510,12 @@ struct PassSetting {
 };
 
 // The tiling and steps per pass of the adjoint's recomputation: its own, else
-// the forward's, which while neither is set are chosen by the lattice's size.
+// the forward's; chosen by the lattice's size while neither is set, and in 2D
+// where the forward's were tuned for record passes, whose tiles are short.
 PassSetting recompute_setting(const prs_ctx* c)
 {
     if (c->rec_tblock > 0) return PassSetting{c->rec_til, c->rec_tblock};
-    if (!c->own && tb_supported(c->geo)) {
+    if ((!c->own || c->for_records) && tb_supported(c->geo)) {
         if (c->geo.ndim == 2) return PassSetting{auto_tile2(c->geo, kMaxPassSteps), kMaxPassSteps};
         const PassChoice pc = auto_pass3(c->geo, 4);
         if (pc.til.vec)
@@ -547,6 +549,29 @@ hipError_t enqueue(const Launch& l, const Geometry& g, const Tiling& til, const 
     if (l.steps > 1)
         return launch_tb(l.steps, g, t, phi_in, phi_out, pi_in, pi_out, k, false, nullptr, DiagCoef{}, s);
     return launch_step(g, t, phi_in, phi_out, pi_in, pi_out, k[0], true, false, nullptr, DiagCoef{}, s);
+}
+
+// One launch of a run from step n, from the current fields to the other
+// buffers: with a record, its partials go to a part of the queue's buffer and
+// its reduction writes `rec`.
+hipError_t run_launch(prs_ctx* c, const Launch& l, const Tiling& til, int64_t n, RecordQueue* queue, prs_stats* rec,
+                      const void* pi_in, void* pi_out)
+{
+    const void* in = c->phi[c->cur];
+    void* out = c->phi[c->cur ^ 1];
+    if (!rec)
+        return enqueue(l, c->geo, til, in, out, pi_in, pi_out, [&](int i) { return coef_for(c, n + i); }, c->stream);
+    const int L = l.steps;
+    const int64_t ntiles = L > 1 ? tb_tiles(c->geo, til, L) : tile_counts(c->geo, til).ntiles;
+    WavePartial* parts = nullptr;
+    const hipError_t e = queue->add(ntiles, rec, n, c->p.eta0 + (double)n * c->p.deta, c->stream, &parts);
+    if (e != hipSuccess) return e;
+    if (L == 1)
+        return launch_step(c->geo, til, in, out, pi_in, pi_out, coef_for(c, n), true, true, parts, diag_coef(c, n),
+                           c->stream);
+    StepCoef64 k[kMaxPassSteps];
+    for (int i = 0; i < L; ++i) k[i] = coef_for(c, n + i);
+    return launch_tb(L, c->geo, til, in, out, pi_in, pi_out, k, true, parts, diag_coef(c, n), c->stream);
 }
 
 prs_status flush(prs_ctx* c, int64_t count, prs_stats* dst)
@@ -678,28 +703,9 @@ prs_status prs_step_n(prs_ctx* c, int64_t nsteps, prs_stats* series, int64_t cap
             }
             if (dom) ++c->lt_count[spans];
         }
-        WavePartial* parts = nullptr;
-        if (diag) {
-            const int64_t ntiles = L > 1 ? tb_tiles(c->geo, c->til, L) : tile_counts(c->geo, c->til).ntiles;
-            HIP_TRY(queue.add(ntiles, c->hrec + pending, n, c->p.eta0 + (double)n * c->p.deta, c->stream, &parts),
-                    "finalize launch");
-        }
-        void* pi_out = l.flips() ? pi_oth : pi_cur;
-        if (!diag) {
-            HIP_TRY(enqueue(l, c->geo, c->til, c->phi[c->cur], c->phi[c->cur ^ 1], pi_cur, pi_out,
-                            [&](int i) { return coef_for(c, n + i); }, c->stream),
-                    "pass launch");
-        } else if (L > 1) {
-            StepCoef64 k[kMaxPassSteps];
-            for (int i = 0; i < L; ++i) k[i] = coef_for(c, n + i);
-            HIP_TRY(launch_tb(L, c->geo, c->til, c->phi[c->cur], c->phi[c->cur ^ 1], pi_cur, pi_out, k, true, parts,
-                              diag_coef(c, n), c->stream),
-                    "multi-step kernel launch");
-        } else {
-            HIP_TRY(launch_step(c->geo, c->til, c->phi[c->cur], c->phi[c->cur ^ 1], pi_cur, pi_out, coef_for(c, n),
-                                true, true, parts, diag_coef(c, n), c->stream),
-                    "step kernel launch");
-        }
+        HIP_TRY(run_launch(c, l, c->til, n, &queue, diag ? c->hrec + pending : nullptr, pi_cur,
+                           l.flips() ? pi_oth : pi_cur),
+                "pass launch");
         if (l.flips()) std::swap(pi_cur, pi_oth);
         if (diag && ++pending == kRecCap) {
             HIP_TRY(queue.reduce(c->stream), "finalize launch");
@@ -775,6 +781,7 @@ prs_status prs_set_time_blocking(prs_ctx* c, int32_t steps_per_pass)
                     "3D: 2, 3, 4)", steps_per_pass);
     c->tblock = steps_per_pass;
     c->own = true;
+    c->for_records = false;
     c->stretches.reset();
     return PRS_OK;
 }
@@ -853,6 +860,7 @@ prs_status prs_set_tiling(prs_ctx* c, int32_t vec, int32_t rows, int32_t ty)
                     (long long)kMinRows);
     c->til = t;
     c->own = true;
+    c->for_records = false;
     c->stretches.reset();
     return PRS_OK;
 }
@@ -2560,6 +2568,12 @@ namespace {
 // change, so that a file written before is tuned anew.
 constexpr const char* kTuneVersion = "k5";
 
+// A choice for 2D runs with records has a key of its own.
+bool tunes_records(const prs_params& p, bool batch_set)
+{
+    return p.ndim == 2 && !batch_set && p.diag_every > 0 && blk_supported(geometry_of(p));
+}
+
 std::string tune_key(const prs_params& p, bool batch_set)
 {
     int dev = 0;
@@ -2581,6 +2595,18 @@ struct TuneEntry {
     int vec, rows, ty, tb;
     double us;
 };
+
+constexpr const char* kRecordsKey = "|records";
+
+// The entry of a lattice: of two, the one made for runs with (without)
+// records, else the one there is.
+const TuneEntry* tune_find(const std::map<std::string, TuneEntry>& m, const prs_params& p, bool batch_set)
+{
+    const std::string key = tune_key(p, batch_set);
+    const auto plain = m.find(key), rec = batch_set ? m.end() : m.find(key + kRecordsKey);
+    const auto it = rec != m.end() && (tunes_records(p, batch_set) || plain == m.end()) ? rec : plain;
+    return it == m.end() ? nullptr : &it->second;
+}
 
 // The cache is written by tune_write only: one entry per line,
 //   "key": {"vec": V, "rows": R, "ty": T, "steps_per_pass": P, "us": U},
@@ -2680,11 +2706,11 @@ prs_status prs_tuned_tiling(const prs_params* p, const char* cache_path, int32_t
     prs_status st = validate(p);
     if (st != PRS_OK) return st;
     const auto m = tune_read(cache_path);
-    const auto it = m.find(tune_key(*p, (flags & PRS_TUNE_BATCH) != 0));
-    if (it == m.end()) return fail(PRS_ESTATE, "no cached tiling for this lattice");
-    if (vec) *vec = it->second.vec;
-    if (rows) *rows = it->second.rows;
-    if (ty) *ty = it->second.ty;
+    const TuneEntry* it = tune_find(m, *p, (flags & PRS_TUNE_BATCH) != 0);
+    if (!it) return fail(PRS_ESTATE, "no cached tiling for this lattice");
+    if (vec) *vec = it->vec;
+    if (rows) *rows = it->rows;
+    if (ty) *ty = it->ty;
     return PRS_OK;
 }
 
@@ -2950,16 +2976,18 @@ prs_status prs_autotune(prs_ctx* c, const char* cache_path, int32_t flags, void*
     if (!c) return fail(PRS_EINVAL, "ctx is NULL");
     if (flags & PRS_TUNE_ADJOINT) return autotune_adjoint(c, cache_path, flags, work, work_bytes, best_us);
     const bool batch_set = (flags & PRS_TUNE_BATCH) != 0;
-    const std::string key = tune_key(c->p, batch_set);
+    const bool records = tunes_records(c->p, batch_set);
+    const std::string key = tune_key(c->p, batch_set) + (records ? kRecordsKey : "");
     auto cache = tune_read(cache_path);
     if (!(flags & PRS_TUNE_FORCE)) {
-        const auto it = cache.find(key);
-        if (it != cache.end()) {
-            prs_status st = prs_set_tiling(c, it->second.vec, it->second.rows, it->second.ty);
+        const TuneEntry* it = tune_find(cache, c->p, batch_set);
+        if (it) {
+            prs_status st = prs_set_tiling(c, it->vec, it->rows, it->ty);
             // the cached steps per pass, also when it is 1 (single steps)
-            if (st == PRS_OK) st = prs_set_time_blocking(c, std::max(1, it->second.tb));
+            if (st == PRS_OK) st = prs_set_time_blocking(c, std::max(1, it->tb));
             if (st == PRS_OK) {
-                if (best_us) *best_us = it->second.us;
+                c->for_records = records;
+                if (best_us) *best_us = it->us;
                 return PRS_OK;
             }
         }
@@ -2986,8 +3014,15 @@ prs_status prs_autotune(prs_ctx* c, const char* cache_path, int32_t flags, void*
     Tiling best = c->til;
     double best_t = 1e300;
     prs_status result = PRS_OK;
-    // 2D single runs also choose the steps per pass: a candidate with T > 1
-    // is timed on T-step passes and its per-step time is a pass over T
+    // A candidate with T > 1 is timed on T-step passes and its per-step time
+    // is a pass over T; but a 2D run takes its multi-step passes at records
+    // only, and block passes between them, so with records a candidate is
+    // timed on intervals of the run itself.  40 steps with a record every ten
+    // in the setting that passes without records rank first, and that
+    // intervals do: float64 1024^2 164 and 122 us (130 untuned), 4096^2 1316
+    // and 964 (989); float32 4096^2 620 and 526 (547), 2048^2 202 and 194.
+    // With a record every 64 steps the two are within 3 % from 256^2 to 8192^2
+    // in float32, and float64 gains 2 to 7 %.
     int per = 1;
     auto run = [&](const Tiling& t, int passes) -> hipError_t {
         void* pa = c->pi;
@@ -3009,13 +3044,74 @@ prs_status prs_autotune(prs_ctx* c, const char* cache_path, int32_t flags, void*
         }
         return hipSuccess;
     };
+    const bool blocks = !batch_set && c->geo.ndim == 2 && use_stretches(c->geo, c->til, 2, true);
+    std::unique_ptr<Stretches> between(blocks ? make_stretches(c->geo, c->til, 2, true) : nullptr);
+    // two intervals (their launches leave phi_dot where it was), whole ones
+    // where that takes no more than a few ms: how the steps after the record
+    // divide into block passes is a few per cent (2048^2 with a record every
+    // 64 steps: 56 steps in four passes of 14, 60 in four of 15)
+    const int64_t K = std::min<int64_t>(records ? c->p.diag_every : 32, sites > 1e9 ? 16 : sites > 1e8 ? 64 : 128);
+    auto run_plan = [&](const std::vector<Launch>& plan, const Tiling& t) -> hipError_t {
+        void* pa = c->pi;
+        void* pb = c->pi_alt;
+        RecordQueue queue{c->partials, c->partial_total, area_scale(c->p)};
+        int64_t n = 0, rec = 0;
+        for (const Launch& l : plan) {
+            const bool diag = records && n % K == 0;
+            const hipError_t err = run_launch(c, l, t, n0 + n, &queue, diag ? c->hrec + rec++ : nullptr, pa,
+                                              l.flips() ? pb : pa);
+            if (err != hipSuccess) return err;
+            if (l.flips()) std::swap(pa, pb);
+            c->cur ^= 1;
+            n += l.steps;
+        }
+        return queue.reduce(c->stream);
+    };
+    // Time of one step of the plan (ms), where it is short the best of three
+    // after a first run.
+    auto plan_time = [&](const std::vector<Launch>& plan, const Tiling& t, double* ms_step) -> hipError_t {
+        const bool brief = sites < 2e7;
+        const int reps = (int)std::max(1.0, std::min({8.0, 96.0 / (double)K, 2e8 / (sites * (double)K)}));
+        hipError_t err = brief ? run_plan(plan, t) : hipSuccess;
+        *ms_step = 1e300;
+        for (int i = 0; i < (brief ? 3 : 1) && err == hipSuccess; ++i) {
+            err = hipEventRecord(e0, c->stream);
+            for (int j = 0; j < reps && err == hipSuccess; ++j) err = run_plan(plan, t);
+            if (err == hipSuccess) err = hipEventRecord(e1, c->stream);
+            if (err == hipSuccess) err = hipEventSynchronize(e1);
+            float ms = 0.0f;
+            if (err == hipSuccess) err = hipEventElapsedTime(&ms, e0, e1);
+            *ms_step = std::min(*ms_step, (double)ms / (double)(2 * K * reps));
+        }
+        return err;
+    };
+    auto restore = [&](hipError_t err) -> hipError_t {
+        c->cur = cur0;
+        if (err == hipSuccess)
+            err = hipMemcpyAsync(c->phi[cur0], save_phi, bytes, hipMemcpyDeviceToDevice, c->stream);
+        if (err == hipSuccess) err = hipMemcpyAsync(c->pi, save_pi, bytes, hipMemcpyDeviceToDevice, c->stream);
+        return err;
+    };
     const int max_T = tb_supported(c->geo) ? kMaxPassSteps : 1;
     int best_T = c->tblock;
     e = hipMemcpyAsync(save_phi, c->phi[cur0], bytes, hipMemcpyDeviceToDevice, c->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(save_pi, c->pi, bytes, hipMemcpyDeviceToDevice, c->stream);
     const int ncu = device_compute_units();
+    // without records a 2D run of any T > 1 takes block passes alone: single
+    // steps have to be faster than those, the other candidates are ranked by
+    // the passes that the recomputation of a gradient and slabs run
+    double block_t = 0.0;
+    bool singles = false;
+    if (blocks && !records && e == hipSuccess) {
+        e = plan_time(plan_launches(c->geo, c->til, c->partial_cap, 0, 2 * K, 2, 0, false, between.get()), c->til,
+                      &block_t);
+        e = restore(e);
+    }
     for (int T = 1; T <= max_T; ++T) {
         if (T > 1 && !tb_steps_supported(c->geo, T)) continue;
+        if (records && T > 1 && T > K) continue;      // would run as a shorter length
+        if (T == 2) singles = block_t > 0.0 && best_t < 1e300;
+        if (singles) break;
         per = T;
         // multi-step passes (in 3D the LDS pass) also try the heights that
         // give a whole number of workgroup rounds, up to four per compute
@@ -3040,27 +3136,40 @@ prs_status prs_autotune(prs_ctx* c, const char* cache_path, int32_t flags, void*
             if (batch_set && !ens_supported(c->geo, t, T)) continue;
             if (tile_counts(c->geo, t).ntiles > c->partial_cap) continue;
             if (T > 1 && tb_tiles(c->geo, t, T) > c->partial_cap) continue;
-            e = run(t, 2);
-            if (e == hipSuccess) e = hipEventRecord(e0, c->stream);
-            if (e == hipSuccess) e = run(t, timed);
-            if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
-            if (e == hipSuccess) e = hipEventSynchronize(e1);
-            float ms = 0.0f;
-            if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-            const double per_step = ms / ((double)timed * per);
+            double per_step = 0.0;
+            if (records) {
+                // a record costs most where every wave has walls, as at a
+                // random start, and least in a coarse network, where most of
+                // a long run's records lie: both count alike (the second on
+                // fields of one sign, which walls never form in)
+                const std::vector<Launch> plan =
+                    plan_launches(c->geo, t, c->partial_cap, 0, 2 * K, T, K, true, T > 1 ? between.get() : nullptr);
+                double coarse = 0.0;
+                e = plan_time(plan, t, &per_step);
+                if (e == hipSuccess) e = hipMemsetAsync(c->phi[c->cur], 0x3F, bytes, c->stream);
+                if (e == hipSuccess) e = hipMemsetAsync(c->pi, 0, bytes, c->stream);
+                if (e == hipSuccess) e = plan_time(plan, t, &coarse);
+                per_step = 0.5 * (per_step + coarse);
+            } else {
+                e = run(t, 2);
+                if (e == hipSuccess) e = hipEventRecord(e0, c->stream);
+                if (e == hipSuccess) e = run(t, timed);
+                if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
+                if (e == hipSuccess) e = hipEventSynchronize(e1);
+                float ms = 0.0f;
+                if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+                per_step = ms / ((double)timed * per);
+            }
             if (e == hipSuccess && log_each)
                 std::fprintf(stderr, "prs_autotune: vec=%d rows=%d ty=%d steps/pass=%d %.2f us/step\n", t.vec,
                              t.rows, t.ty, per, per_step * 1e3);
-            if (e == hipSuccess && per_step < best_t) {
+            if (e == hipSuccess && per_step < best_t && !(T == 1 && block_t > 0.0 && per_step >= block_t)) {
                 best_t = per_step;
                 best = t;
                 best_T = T;
             }
             // restore the state for the next candidate (and for the caller)
-            c->cur = cur0;
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(c->phi[cur0], save_phi, bytes, hipMemcpyDeviceToDevice, c->stream);
-            if (e == hipSuccess) e = hipMemcpyAsync(c->pi, save_pi, bytes, hipMemcpyDeviceToDevice, c->stream);
+            e = restore(e);
         }
     }
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -3073,6 +3182,7 @@ prs_status prs_autotune(prs_ctx* c, const char* cache_path, int32_t flags, void*
     c->til = best;
     c->tblock = best_T;
     c->own = true;
+    c->for_records = records;
     c->stretches.reset();
     if (best_us) *best_us = best_t * 1e3;
     if (cache_path && cache_path[0]) {
