@@ -109,10 +109,14 @@ prs_status validate(const prs_params* p)
 }
 
 // The tiling of a run that neither the caller nor the tuner gave one: of the
-// passes of the default length.
+// passes of the default length.  A 3D run's single steps with a record keep
+// one row a wave up to 1e8 sites (255^3 76 us a step, 85 with two).
 Tiling default_tiling(const Geometry& g)
 {
-    return g.ndim == 2 && tb_supported(g) ? auto_tile2(g, 2) : auto_step(g).til;
+    if (g.ndim == 2 && tb_supported(g)) return auto_tile2(g, 2);
+    Tiling t = auto_step(g).til;
+    if (g.ndim == 3 && (double)g.nx * (double)g.Q * (double)g.M <= 1e8) t.ty = 1;
+    return t;
 }
 
 int64_t partial_capacity(const Geometry& g)
@@ -517,7 +521,8 @@ PassSetting recompute_setting(const prs_ctx* c)
     if (c->rec_tblock > 0) return PassSetting{c->rec_til, c->rec_tblock};
     if ((!c->own || c->for_records) && tb_supported(c->geo)) {
         if (c->geo.ndim == 2) return PassSetting{auto_tile2(c->geo, kMaxPassSteps), kMaxPassSteps};
-        const PassChoice pc = auto_pass3(c->geo, 4);
+        const PassChoice pc = auto_pass3(c->geo, 4), one = auto_step(c->geo);
+        if (pc.us > 8.0f * one.us) return PassSetting{one.til, 1};    // a few rows: as auto_adj_tile
         if (pc.til.vec)
             return PassSetting{Tiling{pc.til.vec, std::max(pc.til.rows, (int)kMinRows), pc.til.ty}, 4};
     }
@@ -1365,6 +1370,7 @@ prs_status prs_adjoint_backward(prs_ctx* c, void* work, size_t work_bytes, void*
     int TA = tb_supported(c->geo) ? c->adj_tblock : 1;
     // what neither the caller nor the tuner set is chosen by the lattice's size
     if (tb_supported(c->geo) && !c->adj_own) at_til = auto_adj_tile(c->geo, &TA);
+    const Tiling one_til = c->adj_own ? at_til : auto_adj_step(c->geo);
     // The fused scheme (2D): per segment the recomputation keeps only the
     // states at the starts of the reverse passes (TF steps apart, the last
     // pass may be shorter), and each reverse pass recomputes its fields from
@@ -1478,7 +1484,7 @@ prs_status prs_adjoint_backward(prs_ctx* c, void* work, size_t work_bytes, void*
                             "adjoint launch");
                     std::swap(mu, mu_oth);
                 } else {
-                    HIP_TRY(launch_adjoint(c->geo, at_til, wcur, wnxt, mu, pass_start(sg, q, false), gacc,
+                    HIP_TRY(launch_adjoint(c->geo, one_til, wcur, wnxt, mu, pass_start(sg, q, false), gacc,
                                            adj_coef(c, st, st == n0), c->stream),
                             "adjoint launch");
                 }
@@ -1501,7 +1507,7 @@ prs_status prs_adjoint_backward(prs_ctx* c, void* work, size_t work_bytes, void*
                         "adjoint launch");
                 std::swap(mu, mu_oth);
             } else {
-                HIP_TRY(launch_adjoint(c->geo, at_til, wcur, wnxt, mu, phi_at(k), gacc,
+                HIP_TRY(launch_adjoint(c->geo, one_til, wcur, wnxt, mu, phi_at(k), gacc,
                                        adj_coef(c, ns + k, ns + k == n0), c->stream),
                         "adjoint launch");
             }
@@ -1519,8 +1525,10 @@ prs_status prs_adjoint_backward(prs_ctx* c, void* work, size_t work_bytes, void*
     // the fused scheme overlaps: its kernels are bound by arithmetic and leave
     // room for each other, while the stored scheme's recomputation and
     // reverse passes are both bound by HBM and gain nothing side by side, so
-    // they run in line on the one stream.
-    const bool overlap = L.nseg > 1 && fused;
+    // they run in line on the one stream.  A segment of one reverse pass has
+    // nothing to recompute, and its events would be its longest part (24 steps
+    // of 16^2, checkpoints every step: 380 us with them, 235 without).
+    const bool overlap = L.nseg > 1 && fused && L.K > TF;
     if (overlap) {
         prs_status st = adj_aux_ready(c);
         if (st != PRS_OK) return st;

@@ -135,6 +135,7 @@ PassChoice auto_step(const Geometry& g);                 // single steps
 PassChoice auto_pass3(const Geometry& g, int T);         // 3D passes of T = 2 .. kDeepSteps steps
 PassChoice own_pass3(const Geometry& g, const Tiling& t, int T);
 Tiling auto_adj_tile(const Geometry& g, int* T);         // reverse passes (2D fused, 3D stored)
+Tiling auto_adj_step(const Geometry& g);                 // single reverse steps
 
 // A T-step pass over a slab along the last axis (the per-device kernel of a
 // lattice sharded along y in 2D, z in 3D): the fields are stored with T halo

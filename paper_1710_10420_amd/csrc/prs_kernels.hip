@@ -306,21 +306,23 @@ Tiling auto_tile2(const Geometry& g, int T)
 // lattices that would not fill the device (128^3: 9 us a step with 8 planes;
 // 200 x 120 x 90 11 us against 34 with 32 planes).  Two rows a wave only where
 // the fields outgrow the last-level cache: 512^3 431 us against 461 and
-// 1024^3 3.59 ms against 3.65, but 384^3 238 us against 212 with one row.
-// The estimate of a small 2D lattice counts the march of its tiles (512^2,
-// 8 and 32 rows: 5.4 and 12.9 us) and the wave rows, most of whose lanes idle
-// on a narrow lattice (1 x 100000, 32 rows: 21.5 us).
+// 1024^3 3.59 ms against 3.65, but 384^3 238 us against 212 with one row --
+// and with one site per lane (255^3 46.8 us, 58.5 with one row).
+// The estimate of a small lattice counts the march of its tiles (512^2, 8 and
+// 32 rows: 5.4 and 12.9 us) and the wave rows, most of whose lanes idle on a
+// narrow lattice (1 x 100000, 32 rows: 21.5 us).
 PassChoice auto_step(const Geometry& g)
 {
     const double sites = (double)g.nx * (double)g.Q * (double)g.M, bytes = 4 * sites * (g.f64 ? 8 : 4);
     PassChoice c{1, 0.0f, false, Tiling{1, sites < 8e6 ? 8 : 32, g.ndim == 3 && sites > 1e8 ? 2 : 1}};
     if (g.nx % 4 == 0 && !g.f64) c.til.vec = 4;
     else if (g.nx % 2 == 0) c.til.vec = 2;
+    else if (g.ndim == 3 && !g.f64 && sites >= 8e6) c.til.ty = 2;
     if (g.ndim == 2 && sites < 8e6) c.til = auto_tile2(g, 2);
     c.til = fit_launch(g, c.til, 1);
-    const double mem = bytes / (bytes < 300e6 ? 7.0e6 : 4.9e6);
-    if (g.ndim == 2 && sites < 8e6) {
-        const double wave_rows = (double)tile_counts(g, c.til).tiles_x * (double)g.M;
+    const double mem = bytes / (bytes < 300e6 ? 7.0e6 : g.ndim == 2 ? 5.6e6 : 4.9e6);
+    if (sites < 8e6) {
+        const double wave_rows = (double)tile_counts(g, c.til).tiles_x * (double)g.Q * (double)g.M;
         c.us = (float)(2.8 + 0.32 * c.til.rows + std::max(mem, 1.1e-4 * wave_rows));
     } else {
         c.us = (float)(4.5 + mem);
@@ -481,6 +483,9 @@ Tiling auto_adj_tile(const Geometry& g, int* T)
                 best = til;
             }
         }
+        // Lattices of a few rows leave most of a workgroup's waves idle: 1 x 1
+        // x 20000 33 us a step in passes of two, 9 in single steps.
+        if (least > 2.0 * auto_step(g).us) *T = 1;
         return best;
     }
     *T = 4;
@@ -496,6 +501,23 @@ Tiling auto_adj_tile(const Geometry& g, int* T)
     t.rows = (int)kMinRows;
     while (t.rows < 64 && tbf_tiles(g, t, 4) > 2048) ++t.rows;
     return t;
+}
+
+// Single reverse steps (checkpoints every step, and remainders): not the
+// passes' tiles, whose one site per lane is for their chains.  Short tiles
+// with 16 bytes a lane where the row allows them and a field takes 4 MB
+// (2048^2 float32 18.4 us with four sites and 8 rows, 19.2 with one; float64
+// 32.4 with two, 40.5 with one; but 256^2 6.6 with one, 8.0 with four), 16
+// rows on large 2D lattices (4096^2 63 us, 68 with 8), and on large float32
+// boxes of odd width four rows a wave (255^3 94 us, 97 with one; float64 399^3
+// 695 with one, 748 with two).
+Tiling auto_adj_step(const Geometry& g)
+{
+    const double sites = (double)g.nx * (double)g.Q * (double)g.M;
+    Tiling t{1, g.ndim == 2 && sites >= 8e6 ? 16 : (int)kMinRows, 1};
+    if (sites * (g.f64 ? 8 : 4) >= 4e6) t.vec = g.nx % 4 == 0 && !g.f64 ? 4 : g.nx % 2 == 0 ? 2 : 1;
+    if (g.ndim == 3 && !g.f64 && t.vec == 1 && sites >= 8e6) t.ty = 4;
+    return fit_launch(g, t, 1);
 }
 
 hipError_t launch_blk2d(int steps, const BlkShape& b, const Geometry& g, const void* phi_in, void* phi_out,

@@ -129,3 +129,29 @@ def test_default_single_steps_fit_a_launch(shape, f64):
 def test_rows_past_32_bits_run_single_steps(shape):
     """The multi-step passes count rows (2D) and planes (3D) in 32 bits."""
     assert not tb_supported(geometry(shape))
+
+
+auto_adj_step = rule("_ZN3prs13auto_adj_stepERKNS_8GeometryE", Tiling, _G)
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("shape", [(16, 16), (2048, 2048), (4096, 4096), (4095, 4095), (1, 10 ** 9), (33, 50, 21),
+                                   (256, 256, 256), (255, 255, 255), (1, 1, 2 ** 33)])
+def test_single_reverse_steps_have_a_tiling_of_their_own(shape, f64):
+    """Short tiles with 16 bytes a lane on large lattices, whatever the reverse
+    passes take, in a launch that holds them."""
+    g = geometry(shape, f64)
+    t = auto_adj_step(g)
+    assert shape[0] % t.vec == 0 and tile_counts(g, t).ntiles * 64 < WORK_ITEMS
+    field = g.nx * g.Q * g.M * (8 if f64 else 4)
+    widest = 4 if shape[0] % 4 == 0 and not f64 else 2 if shape[0] % 2 == 0 else 1
+    assert t.vec == (widest if field >= 4e6 else 1)
+    assert t.rows in (8, 16) or tile_counts(g, Tiling(t.vec, 16, t.ty)).ntiles * 64 >= WORK_ITEMS
+
+
+@pytest.mark.parametrize("shape,T", [((1, 1, 20000), 1), ((64, 1, 2000), 4), ((64, 64, 64), 4), ((10, 10, 1000), 4)])
+def test_lattices_of_a_few_rows_take_single_reverse_steps(shape, T):
+    """1 x 1 x 20000: 33 us a step in passes of two, 9 in single steps."""
+    n = ctypes.c_int()
+    auto_adj_tile(geometry(shape), n)
+    assert n.value == T
