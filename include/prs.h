@@ -182,9 +182,10 @@ prs_status prs_get_tiling(prs_ctx* ctx, int32_t* vec, int32_t* rows, int32_t* ty
  * workgroups per unit; eight for the reverse pass) -- applies the fastest
  * to the context and records it in the JSON file cache_path (created or
  * updated; NULL or "" for no cache).  A 2D context with diag_every > 0 is
- * tuned for runs with records, on intervals between two of them (its tiling
- * and steps per pass are those of the passes that start at a record; the
- * recomputation of a gradient keeps the library's choice); any other by
+ * tuned for runs with records, on its own intervals between two of them (its
+ * tiling and steps per pass are those of the passes that start at a record;
+ * the recomputation of a gradient keeps the library's choice; runs with other
+ * intervals are tuned anew with PRS_TUNE_FORCE); any other by
  * passes without records, as the recomputation and slabs run them.  The file
  * holds either choice of a lattice.  A cached entry for the same GPU
  * architecture, dimension, lattice size and tiling set -- of two the
