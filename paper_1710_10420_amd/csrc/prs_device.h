@@ -746,7 +746,22 @@ __device__ __forceinline__ void step_plane(const StepArgsT<R>& A, const TileSetu
                 kick_drift<D, UNIT>(c, ns, pic[t][j], A.k, out_pi[j], out_phi[j]);
             }
         }
-        if constexpr (DIAG) sites_diag<D, VEC>(Pc.v[t], pic[t], nms, nps, S.active, A.dc, acc);
+        if constexpr (DIAG) {
+            // In 3D float64 the terms of two sites at once take 129 VGPRs, one
+            // at a time 121, which leaves room for a fourth wave: 256^3 with a
+            // record every step, 32 planes a tile, 141 us a step and 120 (64^3
+            // 12.8 and 13.1).
+            if constexpr (D == 3 && sizeof(R) == 8 && VEC > 1) {
+#pragma unroll
+                for (int j = 0; j < VEC; ++j)
+                    sites_diag<D, 1>(reinterpret_cast<const R(&)[1]>(Pc.v[t][j]),
+                                     reinterpret_cast<const R(&)[1]>(pic[t][j]),
+                                     reinterpret_cast<const R(&)[1][D]>(nms[j]),
+                                     reinterpret_cast<const R(&)[1][D]>(nps[j]), S.active, A.dc, acc);
+            } else {
+                sites_diag<D, VEC>(Pc.v[t], pic[t], nms, nps, S.active, A.dc, acc);
+            }
+        }
         if constexpr (UPDATE) {
             if (S.active) {
                 store_vec<VEC>(phi_out + S.off[t], out_phi);
