@@ -122,14 +122,14 @@ prs_status prs_init(const prs_params* p, void* phi_a, void* phi_b, void* dphi,
 int64_t prs_records_in(const prs_params* p, int64_t n0, int64_t nsteps);
 
 /* Advance nsteps steps (Eqs. 3-6).  The Laplacian, kick and drift of a step
- * run fused in one kernel, and a launch advances up to steps_per_pass steps
- * at once (prs_set_time_blocking: default 2 in 2D, 1 in 3D; the autotuner
- * may choose up to 8 in 2D and 4 in 3D; 2D passes without a record up to 16),
- * never with a recorded state inside a pass.  When series is non-NULL the
- * diagnostics (Eqs. 7-8) of every state n with n % diag_every == 0 are
- * computed inside the pass that starts at n (on its input state) and written to series[0 .. *n_written-1]; cap must be
- * at least prs_records_in(...), else PRS_EINVAL.  With series == NULL no
- * diagnostics are computed.  Splitting a call into two consecutive calls
+ * run fused in one kernel, and a launch advances several steps at once
+ * (prs_set_time_blocking: the passes that start at a recorded state up to 8
+ * in 2D and 4 in 3D, those between them up to 16 and 5), never with a
+ * recorded state inside a pass.  When series is non-NULL the diagnostics
+ * (Eqs. 7-8) of every state n with n % diag_every == 0 are computed inside
+ * the pass that starts at n (on its input state) and written to
+ * series[0 .. *n_written-1]; cap must be at least prs_records_in(...), else
+ * PRS_EINVAL.  With series == NULL no diagnostics are computed.  Splitting a call into two consecutive calls
  * gives bit-identical fields and records.  Synchronises the stream when
  * series is non-NULL or launch timing is on. */
 prs_status prs_step_n(prs_ctx* ctx, int64_t nsteps, prs_stats* series, int64_t cap,
@@ -219,10 +219,12 @@ prs_status prs_autotune(prs_ctx* ctx, const char* cache_path, int32_t flags, voi
                         double* best_us);
 
 /* Launch timing, for measurement.  With on != 0, prs_step_n brackets every
- * run of consecutive launches of its pass kernel (the steps_per_pass-step
- * pass without diagnostics; in 2D the block passes) with a pair of HIP
- * events on the context's stream, synchronises the stream before returning and adds the runs'
- * durations and launch counts to two totals.  prs_get_launch_timing reads
+ * run of consecutive passes without diagnostics -- the multi-step launches
+ * between records, whatever their lengths (in 2D the block passes, in 3D LDS
+ * passes of 2 to 5 steps), or, where a run takes the steps between records in
+ * its own tiling and steps per pass, the launches of that many steps -- with a
+ * pair of HIP events on the context's stream, synchronises the stream before
+ * returning and adds the runs' durations and launch counts to two totals.  prs_get_launch_timing reads
  * the totals (milliseconds and launches; either pointer may be NULL) and
  * clears them when reset != 0.  Off by default; timing adds two event
  * records per run of launches and changes no result. */
@@ -243,14 +245,23 @@ prs_status prs_tuned_tiling(const prs_params* p, const char* cache_path, int32_t
 
 /* Temporal blocking: with steps_per_pass = T > 1, prs_step_n advances up to
  * T steps per pass over HBM -- a pass never has a recorded state inside it --
- * so each value is read about once per T steps.  In 2D the passes that start
- * at a recorded state (and the adjoint's, slab's and persistent ensemble's)
- * have T steps and the context's tiling; the steps between them run in block
- * passes of up to 16 steps, whose shape and length the library chooses by
- * the lattice's size, for any T > 1.  In 3D a context whose tiling and steps
- * per pass were neither set nor tuned takes the steps between two records
- * in passes of 2, 3 or 4 steps with tilings the library chooses by the
- * lattice's size; set, they are used as they are (1: single steps).  T may be 2, 3, 4, 6 or 8 for
+ * so each value is read about once per T steps.  The passes that start at a
+ * recorded state have T steps and the context's tiling, as have the slab's
+ * (their own arguments), the persistent ensemble's and, where the settings
+ * were set, the adjoint's recomputation.  The steps between two records:
+ *   2D, T > 1: block passes of up to 16 steps, whose shape and length the
+ *     library chooses by the lattice's size;
+ *   3D, nothing set or tuned: LDS passes of 2 to 4 steps, and of 5 on lattices
+ *     beyond the last-level cache, in tilings chosen by the lattice's size,
+ *     and single steps;
+ *   3D, an LDS tiling and T > 1 set or tuned: passes of that tiling and
+ *     length, passes of five steps where those are estimated faster, and the
+ *     library's shorter ones for the remainder;
+ *   else (T = 1; 3D one-wave tilings set): passes of the context's tiling and
+ *     up to T steps.
+ * The getters return what was set or tuned, else the setting of the passes at
+ * records; setting that same value counts as set (in 3D, T = 1 then means
+ * single steps throughout).  T may be 2, 3, 4, 6 or 8 for
  * 2D lattices (default 2), and 2, 3 or 4 for 3D lattices (default 1); other
  * values give PRS_EINVAL.  A pass uses T steps only when the tiling has a
  * T-step kernel, and otherwise the longest length that has one:
@@ -277,19 +288,23 @@ prs_status prs_plan_passes(const prs_ctx* ctx, int64_t nsteps, int32_t with_reco
 /* Tiling and steps per pass of the reverse sweep (adjoint), chosen
  * independently of the forward ones (same parameters and rules as
  * prs_set_tiling; PRS_TUNE_ADJOINT tunes both).  The forward-with-checkpoints
- * inside prs_adjoint_forward uses the forward tiling and steps per pass, and
- * so does the recomputation inside prs_adjoint_backward unless
+ * inside prs_adjoint_forward takes the steps between two checkpoints as
+ * prs_step_n those between two records, and the recomputation inside
+ * prs_adjoint_backward the forward's tiling and steps per pass unless
  * prs_set_recompute_tiling sets its own (results depend on neither).
- * Multi-step reverse passes exist for 2D lattices with
- * T = 2, 4 and, in float32, 8 and tilings with vec 1 or 2, and for 3D
- * lattices with T = 2 on the one-wave tilings of the 3D multi-step passes
- * and, in float32, T = 3 with vec 1 and ty 1 or 2 (the LDS tilings, ty >= 8,
- * have no reverse pass and run single reverse steps); a pass runs the longest supported
- * length up to the setting, down to single reverse steps.  The default
- * tiling is the forward's at prs_init; the default steps per pass 4 in 2D,
- * 1 in 3D.  While neither of the two is set or tuned the backward uses a
- * reverse tiling and pass length chosen by the lattice's size, and so does
- * the recomputation while the forward's settings are the default ones. */
+ * Multi-step reverse passes exist for 2D lattices with T = 2, 4 and, in
+ * float32, 8 and tilings with vec 1 or 2 (fused scheme: T = 2, 3, 4), and for
+ * 3D lattices with T = 2, 3 and 4 on the eight-wave LDS tilings (ty 8 and 16;
+ * vec 2 with ty 16, and float64 with ty 16, up to T = 3), with T = 2 on the
+ * one-wave tilings of the 3D multi-step passes and, in float32, T = 3 with
+ * vec 1 and ty 1 or 2; a pass runs the longest supported length up to the
+ * setting, down to single reverse steps.  The getters return what was set or
+ * tuned, else the forward's tiling at prs_init and 4 steps per pass in 2D, 1
+ * in 3D.  While neither of the two is set or tuned the backward uses a
+ * reverse tiling and pass length chosen by the lattice's size (and a tiling
+ * for its single reverse steps), and so does the recomputation while the
+ * forward's settings are the default ones or were tuned for runs with
+ * records; prs_get_recompute_tiling returns that choice. */
 prs_status prs_set_adjoint_tiling(prs_ctx* ctx, int32_t vec, int32_t rows, int32_t ty);
 prs_status prs_get_adjoint_tiling(prs_ctx* ctx, int32_t* vec, int32_t* rows, int32_t* ty);
 prs_status prs_set_adjoint_time_blocking(prs_ctx* ctx, int32_t steps_per_pass);

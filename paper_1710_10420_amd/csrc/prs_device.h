@@ -67,8 +67,9 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t b, int64_t nb)
 
 // 3D tilings with ty 8, 16, 32 or 64 select the LDS-staged multi-step pass
 // (eight waves of 2 or 4 rows for ty 8, 16; sixteen waves of 2 or 4 rows for
-// ty 32, 64); their single steps and reverse steps run the one-row kernels
-// of ty 1 (whose registers stay low enough for the ensemble kernel).
+// ty 32, 64), and ty 8 and 16 the reverse pass of the same workgroup; their
+// single steps and single reverse steps run the one-row kernels of ty 1
+// (whose registers stay low enough for the ensemble kernel).
 __host__ __device__ __forceinline__ bool tb3l_tiling(int ty) { return ty == 8 || ty == 16 || ty == 32 || ty == 64; }
 
 __host__ __device__ __forceinline__ int step_ty(int ty) { return ty > 4 ? 1 : ty; }
@@ -1096,11 +1097,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t span_rsrc(const R* base, uint3
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<R*>(base), (short)0, (int)bytes, kRawBufferWord3);
 }
 
-// VEC values of this lane at byte offset voff of the span [base, base+bytes).
 // Cache policy of fields that stream once through a working set that the
 // last-level cache could hold without them (the adjoint's stored fields).
 constexpr int kStream = 2;      // nontemporal
 
+// VEC values of this lane at byte offset voff of the span [base, base+bytes).
 template <int VEC, int AUX = 0, typename R>
 __device__ __forceinline__ void buf_load(const R* base, uint32_t bytes, uint32_t voff, R (&v)[VEC])
 {

@@ -93,12 +93,12 @@ bool tb_supported(const Geometry& g);
 // three waves without a tile.
 constexpr int64_t kMaxWaveTiles = ((int64_t)1 << 32) / 64 - 4;
 // Steps per multi-step pass with a kernel for some tiling: 2D 2, 3, 4, 6, 8;
-// 3D 2 and, in float32, 3.
+// 3D 2, 3, 4.
 bool tb_steps_supported(const Geometry& g, int T);
 // ... and for this tiling (2D float64: 6 and 8 with vec 1 only; 3D: vec 1
 // or 2, and only some row counts; at most kMaxWaveTiles tiles).
 bool tb_pass_supported(const Geometry& g, const Tiling& t, int T);
-constexpr int kMaxPassSteps = 8;   // most leapfrog steps fused into one pass
+constexpr int kMaxPassSteps = 8;   // most steps of a pass whose length a caller may set
 
 // Block passes (2D, prs_block2d.h): `steps` (1 .. kBlkSteps) steps in one
 // launch, each workgroup a block of 64 vec columns by waves * rows rows.
