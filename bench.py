@@ -34,19 +34,19 @@ BYTES_PER_SITE_PASS = 16
 # The same 16 bytes per site-update is the traffic of a single-step pass: the
 # figure the site-update rate is compared with as "effective" bandwidth
 BYTES_PER_UPDATE = 16
-# HBM bytes of one launch of a pass kernel, by (lattice, vec, rows, ty, steps
-# per pass): rocprofv3 FETCH_SIZE + WRITE_SIZE (KiB per dispatch) scaled by
-# what the same counters read for a plain copy of known size (factors 2.00 and
-# 1.00), from the profile named in each entry, taken on kernel sources whose
+# HBM bytes of one launch of the passes between two records, by lattice (2D
+# block passes of about 12 steps; 3D LDS passes of five, four move the same
+# fields): rocprofv3 FETCH_SIZE + WRITE_SIZE (KiB per dispatch) scaled by what
+# the same counters read for a plain copy of known size (factors 2.00 and
+# 1.00), and what those counters and the vector unit's show to limit the
+# launch, from the profile named in each entry, taken on kernel sources whose
 # digest (kernel_digest()) is recorded with it.  When the sources differ now
 # the counters no longer describe the kernel and the bench reports null.
 TRAFFIC_PER_LAUNCH = {
-    ("2d8192", 4, 71, 1, 8): {"bytes": 1132171638, "profile": "profiles/k_tb2d_2d8192.md",
-                              "sources": "b7b7a7ed00d3f01c"},
-    ("2d8192", 2, 64, 1, 8): {"bytes": 1158439244, "profile": "profiles/k_tb2d_2d8192.md",
-                              "sources": "b7b7a7ed00d3f01c"},
-    ("3d1024", 2, 32, 16, 4): {"bytes": 23574425145, "profile": "profiles/k_tb3l_3d1024.md",
-                               "sources": "b7b7a7ed00d3f01c"},
+    "2d8192": {"bytes": 1171000000, "limited_by": "vector issue", "profile": "profiles/cases_kernels.md",
+               "sources": "2752c6549fdd3c63"},
+    "3d1024": {"bytes": 20100000000, "limited_by": "HBM and vector issue alike",
+               "profile": "profiles/cases_kernels.md", "sources": "2752c6549fdd3c63"},
 }
 
 WORKLOAD = {
@@ -211,6 +211,12 @@ def pass_valu_lane_ops(shape, tiling, T, counts):
                       "loop_instructions": c}
 
 
+def timed_steps_per_launch(steps, records, steps_per_record, single, launches):
+    """Average steps of a run's timed launches (prs_set_launch_timing): all
+    its steps but those of the passes with a record and the single steps."""
+    return (steps - records * steps_per_record - single) / launches
+
+
 def forward_leg(prs, torch, w, runs, warmup, tiling=None, steps_per_pass=None, extra=True):
     """Whole runs of a forward workload: tuned (or given) tiling and steps per
     pass, `warmup` untimed runs, then `runs` timed runs bracketed by stream
@@ -258,22 +264,27 @@ def forward_leg(prs, torch, w, runs, warmup, tiling=None, steps_per_pass=None, e
     per_launch_bytes = BYTES_PER_SITE_PASS * sites           # algorithmic bytes of one pass
     achieved = per_launch_bytes / avg_launch_s / 1e9 if avg_launch_s else None
     digest = kernel_digest()
-    # 2D: the steps between two diagnostic passes (T steps from each record)
-    # run in block passes of up to 16 steps, which are what is timed; their
-    # average length stands for the steps per launch
+    # The steps between two diagnostic passes (T steps from each record) run in
+    # launches whose lengths the library mixes -- 2D block passes of up to 16
+    # steps, 3D LDS passes of up to 5 -- and these are what is timed (single
+    # steps among them are not): their average length stands for the steps per
+    # launch.
     blocks = len(w["shape"]) == 2 and T > 1
-    nrec = prs.prs_records_in(sim.p, 0, S)
-    steps_launch = (S - nrec * min(T, w["diag_every"])) * runs / k_launches if blocks and k_launches else T
-    tr = TRAFFIC_PER_LAUNCH.get((w["key"], "block") if blocks else (w["key"],) + til + (T,))
+    mixed = blocks or (len(w["shape"]) == 3 and T > 1 and til[2] in (8, 16, 32, 64))
+    steps_launch = T
+    if mixed and k_launches:
+        steps_launch = timed_steps_per_launch(S, prs.prs_records_in(sim.p, 0, S), min(T, w["diag_every"]), single,
+                                              k_launches / runs)
+    tr = TRAFFIC_PER_LAUNCH.get(w["key"]) if mixed else None
     traffic = tr["bytes"] if tr and tr["sources"] == digest else None
-    lane_ops, isa = pass_valu_lane_ops(w["shape"], til, T, isa_counts()) if T > 1 and not blocks else (None, None)
+    lane_ops, isa = pass_valu_lane_ops(w["shape"], til, T, isa_counts()) if T > 1 and not mixed else (None, None)
     if blocks:
         kernel = "k_blk2d (block pass, %.2f fused leapfrog steps per pass on average)" % steps_launch
     elif T == 1:
         kernel = "k_step (one fused leapfrog step per pass)"
-    elif len(w["shape"]) == 3 and til[2] in (8, 16, 32, 64):
-        kernel = ("k_tb3l<vec=%d,T=%d,waves=%d> (%d fused leapfrog steps per pass, row halos through LDS)"
-                  % (til[0], T, 16 if til[2] >= 32 else 8, T))
+    elif mixed:
+        kernel = ("k_tb3l (row halos through LDS; passes of up to 5 fused leapfrog steps, %.2f on average)"
+                  % steps_launch)
     else:
         kernel = "k_tb%dd<vec=%d,T=%d> (%d fused leapfrog steps per pass)" % (len(w["shape"]), til[0], T, T)
     recs, mu, nu = results[-1]
@@ -297,6 +308,7 @@ def forward_leg(prs, torch, w, runs, warmup, tiling=None, steps_per_pass=None, e
                                            if avg_launch_s else None),
             "passes_per_run": {"multi_step": multi, "single_step": single}}
     if traffic:
+        roof["limited_by"] = tr["limited_by"]
         roof["dram_gbs"] = traffic / avg_launch_s / 1e9
         roof["dram_frac"] = roof["dram_gbs"] / HBM_PEAK_GBS
         roof["traffic_over_algorithmic"] = traffic / per_launch_bytes
