@@ -688,7 +688,7 @@ prs_status prs_step_n(prs_ctx* c, int64_t nsteps, prs_stats* series, int64_t cap
         const int64_t n = c->step;
         const bool diag = want && (n % K == 0);
         if (c->lt_on) {
-            const bool dom = !diag && (between ? l.flips() : L == T);
+            const bool dom = !diag && (between ? L > 1 : L == T);
             if (dom && !open) {
                 if (2 * spans + 2 > c->lt_ev.size()) {
                     for (int j = 0; j < 2; ++j) {
@@ -803,7 +803,7 @@ prs_status prs_plan_passes(const prs_ctx* c, int64_t nsteps, int32_t with_record
                                                        : make_stretches(c->geo, c->til, pass_steps(c), c->own));
     for (const Launch& l : plan_launches(c->geo, c->til, c->partial_cap, c->step, nsteps, pass_steps(c), K, K > 0,
                                          c->stretches ? c->stretches.get() : made.get()))
-        (l.flips() ? m : n1) += 1;
+        (l.steps > 1 ? m : n1) += 1;
     if (multi_passes) *multi_passes = m;
     if (single_passes) *single_passes = n1;
     return PRS_OK;
