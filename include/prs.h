@@ -95,8 +95,8 @@ typedef struct prs_ctx prs_ctx;
 /* ---- single run ------------------------------------------------------- */
 
 /* Bytes of device workspace prs_init needs for these parameters (per-wave
- * diagnostic partial sums, the record buffer and a second phi_dot field for
- * multi-step passes); 0 if p is invalid. */
+ * diagnostic partial sums, of several records where they are small, and a
+ * second phi_dot field for multi-step passes); 0 if p is invalid. */
 size_t prs_workspace_bytes(const prs_params* p);
 
 /* Create a run context over caller-owned device buffers.
